@@ -20,8 +20,13 @@ LIB = os.path.join(PKG, "libmobius.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
-SOURCES = ["mobius_kernels.hip", "mobius_force.hip", "mobius_api.cpp", "mobius_solver.cpp",
-           "mobius_tune.cpp"]
+# (source, extra flags, object): the hop kernels compile once per storage
+# precision and launch form
+UNITS = [("mobius_kernels.hip", [f"-DMOBIUS_HOP_PREC={p}", f"-DMOBIUS_HOP_BATCH={b}"], f"hop_p{p}_b{b}.o")
+         for p in range(3) for b in range(2)]
+UNITS += [(s, [], os.path.splitext(s)[0] + ".o")
+          for s in ("mobius_kernels.hip", "mobius_force.hip", "mobius_api.cpp", "mobius_solver.cpp",
+                    "mobius_tune.cpp")]
 
 COMMON = ["-x", "hip", f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC",
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -31,12 +36,13 @@ COMMON = ["-x", "hip", f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC",
           "-Wall", "-Wno-unused-function", "-I", os.path.join(ROOT, "include")]
 
 
-def _compile(src: str) -> str:
-    obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
-    cmd = [HIPCC] + COMMON + ["-c", os.path.join(CSRC, src), "-o", obj]
+def _compile(unit) -> str:
+    src, flags, obj = unit
+    obj = os.path.join(BUILD, obj)
+    cmd = [HIPCC] + COMMON + flags + ["-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
-        raise RuntimeError(f"hipcc failed for {src}:\n{r.stdout}\n{r.stderr}")
+        raise RuntimeError(f"hipcc failed for {src} {flags}:\n{r.stdout}\n{r.stderr}")
     # surface real warnings, drop the host pass's note about the GPU-only feature flag
     lines = [l for l in (r.stdout + r.stderr).splitlines()
              if l.strip() and "packed-fp32-ops" not in l and "warning generated" not in l
@@ -49,8 +55,8 @@ def _compile(src: str) -> str:
 def build(verbose: bool = True) -> str:
     """Compile every source and link libmobius.so (always rebuilds)."""
     os.makedirs(BUILD, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
-        objs = list(ex.map(_compile, SOURCES))
+    with ThreadPoolExecutor(max_workers=os.cpu_count() or 1) as ex:
+        objs = list(ex.map(_compile, UNITS))
     tmp = LIB + ".tmp"
     cmd = [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp] + objs
     r = subprocess.run(cmd, capture_output=True, text=True)

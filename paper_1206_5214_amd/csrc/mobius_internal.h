@@ -197,6 +197,22 @@ hipError_t launch_hop(const Geometry &g, const OpCoeffs &c, const void *links, c
                       const HopArgs &a, hipStream_t st);
 HopParams make_hop_params(const Geometry &g, const OpCoeffs &c, const void *links,
                           const int32_t *nbr, const HopArgs &a);
+// the hop kernel of (P, dag, epi) on one lattice, and its persistent form over
+// a batch; false for an epilogue that has no kernel
+template <int P>
+bool run_hop(int dag, int epi, const HopParams &hp, hipStream_t st);
+template <int P>
+bool run_hop_batch(int dag, int epi, const HopParams *groups, int n, const int64_t *prefix, size_t dyn,
+                   int grid, int pf, hipStream_t st);
+#define MOBIUS_DECLARE_HOP(P)                                                                      \
+    template <>                                                                                    \
+    bool run_hop<P>(int, int, const HopParams &, hipStream_t);                                     \
+    template <>                                                                                    \
+    bool run_hop_batch<P>(int, int, const HopParams *, int, const int64_t *, size_t, int, int, hipStream_t);
+MOBIUS_DECLARE_HOP(MOBIUS_F64)
+MOBIUS_DECLARE_HOP(MOBIUS_F32)
+MOBIUS_DECLARE_HOP(MOBIUS_F16)
+#undef MOBIUS_DECLARE_HOP
 size_t hop_link_lds_bytes(int prec, int Ls, bool rows);
 // bytes of the I^-1 epilogue's LDS buffer (one block) for a storage precision
 size_t m5_epilogue_lds_bytes(int prec);

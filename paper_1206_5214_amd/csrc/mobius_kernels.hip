@@ -23,6 +23,16 @@
 namespace mobius {
 namespace {
 
+int sites_per_wave(int Ls) { return 64 / Ls; }
+
+// dynamic LDS of one block for the staged links: [8][sites per block][record]
+template <int P>
+size_t link_lds_bytes(int spw, bool rows)
+{
+    // FP16: the dot2 operand form, or the matrix-core rows (pf 3)
+    return (size_t)8 * WAVES * spw * (P == MOBIUS_F16 ? (rows ? LINKROW_REC : LINKH2_REC) : Link<P>::REC);
+}
+
 // ---------------------------------------------------------------------------
 // hop kernel: out = epilogue( -1/2 sum_mu [...] )  on every s-slice
 
@@ -360,6 +370,174 @@ __global__ __launch_bounds__(BLOCK) void hop_batch_kernel(const HopParams *group
         __syncthreads();  // LDS of this item is dead before the next item stages
     }
 }
+
+}  // namespace
+
+// ---------------------------------------------------------------------------
+// Launch of the hop kernels.  Their instantiations are most of this file's
+// compile time, so each storage precision, single and batched launch is a
+// compilation unit of its own (MOBIUS_HOP_PREC, MOBIUS_HOP_BATCH; build.py),
+// reached through run_hop<P> and run_hop_batch<P>.
+#ifdef MOBIUS_HOP_PREC
+namespace {
+
+template <int P, bool DAG, int EPI>
+void hop_launch(const HopParams &hp0, hipStream_t st)
+{
+    HopParams hp = hp0;
+    const size_t links = hp.stage_links ? link_lds_bytes<P>(hp.spw, hp.pf == 3) : 0;
+    size_t dyn = links;
+    if constexpr ((EPI & EPI_M5INV) != 0) {
+        hp.m5_off = hp.nrhs > 1 ? (int)links : 0;
+        dyn = std::max(links, (size_t)hp.m5_off + sizeof(M5Lds<typename Spin<P>::T>));
+    }
+    const dim3 grid((unsigned)hp.nblocks), blk(BLOCK);
+    switch (hp.pf) {
+    case 0: hipLaunchKernelGGL((hop_kernel<P, DAG, EPI, 0>), grid, blk, dyn, st, hp); break;
+    case 1: hipLaunchKernelGGL((hop_kernel<P, DAG, EPI, 1>), grid, blk, dyn, st, hp); break;
+    case 3:
+        if constexpr (P == MOBIUS_F16) {
+            hipLaunchKernelGGL((hop_kernel<P, DAG, EPI, 3>), grid, blk, dyn, st, hp);
+            break;
+        }
+        [[fallthrough]];
+    default: hipLaunchKernelGGL((hop_kernel<P, DAG, EPI, 2>), grid, blk, dyn, st, hp); break;
+    }
+}
+
+template <int P, bool DAG, int EPI>
+void hop_batch_launch(const HopParams *groups, int n, const int64_t *prefix, size_t dyn, int grid,
+                      int pf, hipStream_t st)
+{
+    switch (pf) {
+    case 0: hipLaunchKernelGGL((hop_batch_kernel<P, DAG, EPI, 0>), dim3(grid), dim3(BLOCK), dyn, st, groups, n, prefix); break;
+    case 1: hipLaunchKernelGGL((hop_batch_kernel<P, DAG, EPI, 1>), dim3(grid), dim3(BLOCK), dyn, st, groups, n, prefix); break;
+    case 3:
+        if constexpr (P == MOBIUS_F16) {
+            hipLaunchKernelGGL((hop_batch_kernel<P, DAG, EPI, 3>), dim3(grid), dim3(BLOCK), dyn, st, groups, n, prefix);
+            break;
+        }
+        [[fallthrough]];
+    default: hipLaunchKernelGGL((hop_batch_kernel<P, DAG, EPI, 2>), dim3(grid), dim3(BLOCK), dyn, st, groups, n, prefix); break;
+    }
+}
+
+// Calls F<P, DAG, EPI>() for the runtime (dag, epi); false if unsupported.
+template <int P, template <int, bool, int> class F, class... A>
+bool dispatch_hop(int dag, int epi, A &&...args)
+{
+#define MOBIUS_EPI_CASES(P, D)                                                                     \
+    switch (epi) {                                                                                 \
+    case 0: F<P, D, 0>::run(args...); return true;                                                 \
+    case EPI_M5INV: F<P, D, EPI_M5INV>::run(args...); return true;                                 \
+    case EPI_M5INV | EPI_POSTSUB: F<P, D, EPI_M5INV | EPI_POSTSUB>::run(args...); return true;     \
+    case EPI_POSTSUB: F<P, D, EPI_POSTSUB>::run(args...); return true;                             \
+    case EPI_M5INV | EPI_POSTSUB | EPI_NORM:                                                       \
+        F<P, D, EPI_M5INV | EPI_POSTSUB | EPI_NORM>::run(args...);                                 \
+        return true;                                                                               \
+    case EPI_PRESUB | EPI_M5INV: F<P, D, EPI_PRESUB | EPI_M5INV>::run(args...); return true;       \
+    case EPI_POSTSUB | EPI_NORM: F<P, D, EPI_POSTSUB | EPI_NORM>::run(args...); return true;       \
+    case EPI_M5ADD: F<P, D, EPI_M5ADD>::run(args...); return true;                                 \
+    case EPI_M5ADD | EPI_PRESUB: F<P, D, EPI_M5ADD | EPI_PRESUB>::run(args...); return true;       \
+    case EPI_M5ADD | EPI_PRESUB | EPI_NORM:                                                        \
+        F<P, D, EPI_M5ADD | EPI_PRESUB | EPI_NORM>::run(args...);                                  \
+        return true;                                                                               \
+    case EPI_M5INV | EPI_BMIX:                                                                     \
+        if constexpr (!D) F<P, D, EPI_M5INV | EPI_BMIX>::run(args...);                             \
+        return !D;                                                                                 \
+    case EPI_PREMIXED | EPI_M5INV | EPI_POSTSUB | EPI_NORM:                                        \
+        if constexpr (!D) F<P, D, EPI_PREMIXED | EPI_M5INV | EPI_POSTSUB | EPI_NORM>::run(args...); \
+        return !D;                                                                                 \
+    case EPI_PREMIXED | EPI_M5INV | EPI_POSTSUB:                                                   \
+        if constexpr (!D) F<P, D, EPI_PREMIXED | EPI_M5INV | EPI_POSTSUB>::run(args...);           \
+        return !D;                                                                                 \
+    case EPI_PREMIXED | EPI_POSTSUB | EPI_NORM:                                                    \
+        if constexpr (!D) F<P, D, EPI_PREMIXED | EPI_POSTSUB | EPI_NORM>::run(args...);            \
+        return !D;                                                                                 \
+    case EPI_PREMIXED | EPI_POSTSUB:                                                               \
+        if constexpr (!D) F<P, D, EPI_PREMIXED | EPI_POSTSUB>::run(args...);                       \
+        return !D;                                                                                 \
+    case EPI_PREMIXED | EPI_BMIX:                                                                  \
+        if constexpr (!D) F<P, D, EPI_PREMIXED | EPI_BMIX>::run(args...);                          \
+        return !D;                                                                                 \
+    case EPI_PREMIXED | EPI_M5INV | EPI_BMIX:                                                      \
+        if constexpr (!D) F<P, D, EPI_PREMIXED | EPI_M5INV | EPI_BMIX>::run(args...);              \
+        return !D;                                                                                 \
+    case EPI_PREMIXED | EPI_M5INV | EPI_BMIX | EPI_POSTSUB:                                        \
+        if constexpr (!D) F<P, D, EPI_PREMIXED | EPI_M5INV | EPI_BMIX | EPI_POSTSUB>::run(args...); \
+        return !D;                                                                                 \
+    case EPI_PREMIXED | EPI_M5INV | EPI_BMIX | EPI_POSTSUB | EPI_NORM:                             \
+        if constexpr (!D)                                                                          \
+            F<P, D, EPI_PREMIXED | EPI_M5INV | EPI_BMIX | EPI_POSTSUB | EPI_NORM>::run(args...);   \
+        return !D;                                                                                 \
+    case EPI_NOBOUT:                                                                               \
+        if constexpr (D) F<P, D, EPI_NOBOUT>::run(args...);                                        \
+        return D;                                                                                  \
+    case EPI_PREMIXED | EPI_M5SUB:                                                                 \
+        if constexpr (!D) F<P, D, EPI_PREMIXED | EPI_M5SUB>::run(args...);                         \
+        return !D;                                                                                 \
+    case EPI_PREMIXED | EPI_M5SUB | EPI_NORM:                                                      \
+        if constexpr (!D) F<P, D, EPI_PREMIXED | EPI_M5SUB | EPI_NORM>::run(args...);              \
+        return !D;                                                                                 \
+    case EPI_M5SUB:                                                                                \
+        if constexpr (D) F<P, D, EPI_M5SUB>::run(args...);                                         \
+        return D;                                                                                  \
+    case EPI_M5SUB | EPI_NORM:                                                                     \
+        if constexpr (D) F<P, D, EPI_M5SUB | EPI_NORM>::run(args...);                              \
+        return D;                                                                                  \
+    case EPI_NOBOUT | EPI_M5INV | EPI_BMIX:                                                        \
+        if constexpr (D) F<P, D, EPI_NOBOUT | EPI_M5INV | EPI_BMIX>::run(args...);                 \
+        return D;                                                                                  \
+    case EPI_NOBOUT | EPI_POSTSUB:                                                                 \
+        if constexpr (D) F<P, D, EPI_NOBOUT | EPI_POSTSUB>::run(args...);                          \
+        return D;                                                                                  \
+    case EPI_NOBOUT | EPI_POSTSUB | EPI_NORM:                                                      \
+        if constexpr (D) F<P, D, EPI_NOBOUT | EPI_POSTSUB | EPI_NORM>::run(args...);               \
+        return D;                                                                                  \
+    }                                                                                              \
+    return false;
+    if (dag) {
+        MOBIUS_EPI_CASES(P, true)
+    } else {
+        MOBIUS_EPI_CASES(P, false)
+    }
+#undef MOBIUS_EPI_CASES
+    return false;
+}
+
+template <int P, bool D, int E>
+struct RunHop {
+    static void run(const HopParams &hp, hipStream_t st) { hop_launch<P, D, E>(hp, st); }
+};
+template <int P, bool D, int E>
+struct RunHopBatch {
+    static void run(const HopParams *g, int n, const int64_t *prefix, size_t dyn, int grid, int pf,
+                    hipStream_t st)
+    {
+        hop_batch_launch<P, D, E>(g, n, prefix, dyn, grid, pf, st);
+    }
+};
+
+}  // namespace
+
+#if MOBIUS_HOP_BATCH
+template <>
+bool run_hop_batch<MOBIUS_HOP_PREC>(int dag, int epi, const HopParams *groups, int n, const int64_t *prefix,
+                                    size_t dyn, int grid, int pf, hipStream_t st)
+{
+    return dispatch_hop<MOBIUS_HOP_PREC, RunHopBatch>(dag, epi, groups, n, prefix, dyn, grid, pf, st);
+}
+#else
+template <>
+bool run_hop<MOBIUS_HOP_PREC>(int dag, int epi, const HopParams &hp, hipStream_t st)
+{
+    return dispatch_hop<MOBIUS_HOP_PREC, RunHop>(dag, epi, hp, st);
+}
+#endif
+
+#else  // !MOBIUS_HOP_PREC: everything else
+
+namespace {
 
 // per-site s-direction operators: kind 0 -> I (or I^+), kind 1 -> I^-1 (or I^-+)
 template <int P, bool DAG, int KIND>
@@ -980,8 +1158,6 @@ __global__ void cg_scalar_batch(CgScalars *sc, int nsys, int op, const int32_t *
     }
 }
 
-int sites_per_wave(int Ls) { return 64 / Ls; }
-
 }  // namespace
 
 // ---------------------------------------------------------------------------
@@ -1135,159 +1311,6 @@ hipError_t launch_unpack_spinor(const Geometry &g, int prec, const void *even, c
     return hipGetLastError();
 }
 
-namespace {
-
-// dynamic LDS of one block for the staged links: [8][sites per block][record]
-template <int P>
-size_t link_lds_bytes(int spw, bool rows)
-{
-    // FP16: the dot2 operand form, or the matrix-core rows (pf 3)
-    return (size_t)8 * WAVES * spw * (P == MOBIUS_F16 ? (rows ? LINKROW_REC : LINKH2_REC) : Link<P>::REC);
-}
-
-template <int P, bool DAG, int EPI>
-void hop_launch(const HopParams &hp0, hipStream_t st)
-{
-    HopParams hp = hp0;
-    const size_t links = hp.stage_links ? link_lds_bytes<P>(hp.spw, hp.pf == 3) : 0;
-    size_t dyn = links;
-    if constexpr ((EPI & EPI_M5INV) != 0) {
-        hp.m5_off = hp.nrhs > 1 ? (int)links : 0;
-        dyn = std::max(links, (size_t)hp.m5_off + sizeof(M5Lds<typename Spin<P>::T>));
-    }
-    const dim3 grid((unsigned)hp.nblocks), blk(BLOCK);
-    switch (hp.pf) {
-    case 0: hipLaunchKernelGGL((hop_kernel<P, DAG, EPI, 0>), grid, blk, dyn, st, hp); break;
-    case 1: hipLaunchKernelGGL((hop_kernel<P, DAG, EPI, 1>), grid, blk, dyn, st, hp); break;
-    case 3:
-        if constexpr (P == MOBIUS_F16) {
-            hipLaunchKernelGGL((hop_kernel<P, DAG, EPI, 3>), grid, blk, dyn, st, hp);
-            break;
-        }
-        [[fallthrough]];
-    default: hipLaunchKernelGGL((hop_kernel<P, DAG, EPI, 2>), grid, blk, dyn, st, hp); break;
-    }
-}
-
-template <int P, bool DAG, int EPI>
-void hop_batch_launch(const HopParams *groups, int n, const int64_t *prefix, size_t dyn, int grid,
-                      int pf, hipStream_t st)
-{
-    switch (pf) {
-    case 0: hipLaunchKernelGGL((hop_batch_kernel<P, DAG, EPI, 0>), dim3(grid), dim3(BLOCK), dyn, st, groups, n, prefix); break;
-    case 1: hipLaunchKernelGGL((hop_batch_kernel<P, DAG, EPI, 1>), dim3(grid), dim3(BLOCK), dyn, st, groups, n, prefix); break;
-    case 3:
-        if constexpr (P == MOBIUS_F16) {
-            hipLaunchKernelGGL((hop_batch_kernel<P, DAG, EPI, 3>), dim3(grid), dim3(BLOCK), dyn, st, groups, n, prefix);
-            break;
-        }
-        [[fallthrough]];
-    default: hipLaunchKernelGGL((hop_batch_kernel<P, DAG, EPI, 2>), dim3(grid), dim3(BLOCK), dyn, st, groups, n, prefix); break;
-    }
-}
-
-// Calls F<P, DAG, EPI>() for the runtime (prec, dag, epi); false if unsupported.
-template <template <int, bool, int> class F, class... A>
-bool dispatch_hop(int prec, int dag, int epi, A &&...args)
-{
-#define MOBIUS_EPI_CASES(P, D)                                                                     \
-    switch (epi) {                                                                                 \
-    case 0: F<P, D, 0>::run(args...); return true;                                                 \
-    case EPI_M5INV: F<P, D, EPI_M5INV>::run(args...); return true;                                 \
-    case EPI_M5INV | EPI_POSTSUB: F<P, D, EPI_M5INV | EPI_POSTSUB>::run(args...); return true;     \
-    case EPI_POSTSUB: F<P, D, EPI_POSTSUB>::run(args...); return true;                             \
-    case EPI_M5INV | EPI_POSTSUB | EPI_NORM:                                                       \
-        F<P, D, EPI_M5INV | EPI_POSTSUB | EPI_NORM>::run(args...);                                 \
-        return true;                                                                               \
-    case EPI_PRESUB | EPI_M5INV: F<P, D, EPI_PRESUB | EPI_M5INV>::run(args...); return true;       \
-    case EPI_POSTSUB | EPI_NORM: F<P, D, EPI_POSTSUB | EPI_NORM>::run(args...); return true;       \
-    case EPI_M5ADD: F<P, D, EPI_M5ADD>::run(args...); return true;                                 \
-    case EPI_M5ADD | EPI_PRESUB: F<P, D, EPI_M5ADD | EPI_PRESUB>::run(args...); return true;       \
-    case EPI_M5ADD | EPI_PRESUB | EPI_NORM:                                                        \
-        F<P, D, EPI_M5ADD | EPI_PRESUB | EPI_NORM>::run(args...);                                  \
-        return true;                                                                               \
-    case EPI_M5INV | EPI_BMIX:                                                                     \
-        if constexpr (!D) F<P, D, EPI_M5INV | EPI_BMIX>::run(args...);                             \
-        return !D;                                                                                 \
-    case EPI_PREMIXED | EPI_M5INV | EPI_POSTSUB | EPI_NORM:                                        \
-        if constexpr (!D) F<P, D, EPI_PREMIXED | EPI_M5INV | EPI_POSTSUB | EPI_NORM>::run(args...); \
-        return !D;                                                                                 \
-    case EPI_PREMIXED | EPI_M5INV | EPI_POSTSUB:                                                   \
-        if constexpr (!D) F<P, D, EPI_PREMIXED | EPI_M5INV | EPI_POSTSUB>::run(args...);           \
-        return !D;                                                                                 \
-    case EPI_PREMIXED | EPI_POSTSUB | EPI_NORM:                                                    \
-        if constexpr (!D) F<P, D, EPI_PREMIXED | EPI_POSTSUB | EPI_NORM>::run(args...);            \
-        return !D;                                                                                 \
-    case EPI_PREMIXED | EPI_POSTSUB:                                                               \
-        if constexpr (!D) F<P, D, EPI_PREMIXED | EPI_POSTSUB>::run(args...);                       \
-        return !D;                                                                                 \
-    case EPI_PREMIXED | EPI_BMIX:                                                                  \
-        if constexpr (!D) F<P, D, EPI_PREMIXED | EPI_BMIX>::run(args...);                          \
-        return !D;                                                                                 \
-    case EPI_PREMIXED | EPI_M5INV | EPI_BMIX:                                                      \
-        if constexpr (!D) F<P, D, EPI_PREMIXED | EPI_M5INV | EPI_BMIX>::run(args...);              \
-        return !D;                                                                                 \
-    case EPI_PREMIXED | EPI_M5INV | EPI_BMIX | EPI_POSTSUB:                                        \
-        if constexpr (!D) F<P, D, EPI_PREMIXED | EPI_M5INV | EPI_BMIX | EPI_POSTSUB>::run(args...); \
-        return !D;                                                                                 \
-    case EPI_PREMIXED | EPI_M5INV | EPI_BMIX | EPI_POSTSUB | EPI_NORM:                             \
-        if constexpr (!D)                                                                          \
-            F<P, D, EPI_PREMIXED | EPI_M5INV | EPI_BMIX | EPI_POSTSUB | EPI_NORM>::run(args...);   \
-        return !D;                                                                                 \
-    case EPI_NOBOUT:                                                                               \
-        if constexpr (D) F<P, D, EPI_NOBOUT>::run(args...);                                        \
-        return D;                                                                                  \
-    case EPI_PREMIXED | EPI_M5SUB:                                                                 \
-        if constexpr (!D) F<P, D, EPI_PREMIXED | EPI_M5SUB>::run(args...);                         \
-        return !D;                                                                                 \
-    case EPI_PREMIXED | EPI_M5SUB | EPI_NORM:                                                      \
-        if constexpr (!D) F<P, D, EPI_PREMIXED | EPI_M5SUB | EPI_NORM>::run(args...);              \
-        return !D;                                                                                 \
-    case EPI_M5SUB:                                                                                \
-        if constexpr (D) F<P, D, EPI_M5SUB>::run(args...);                                         \
-        return D;                                                                                  \
-    case EPI_M5SUB | EPI_NORM:                                                                     \
-        if constexpr (D) F<P, D, EPI_M5SUB | EPI_NORM>::run(args...);                              \
-        return D;                                                                                  \
-    case EPI_NOBOUT | EPI_M5INV | EPI_BMIX:                                                        \
-        if constexpr (D) F<P, D, EPI_NOBOUT | EPI_M5INV | EPI_BMIX>::run(args...);                 \
-        return D;                                                                                  \
-    case EPI_NOBOUT | EPI_POSTSUB:                                                                 \
-        if constexpr (D) F<P, D, EPI_NOBOUT | EPI_POSTSUB>::run(args...);                          \
-        return D;                                                                                  \
-    case EPI_NOBOUT | EPI_POSTSUB | EPI_NORM:                                                      \
-        if constexpr (D) F<P, D, EPI_NOBOUT | EPI_POSTSUB | EPI_NORM>::run(args...);               \
-        return D;                                                                                  \
-    }                                                                                              \
-    return false;
-    if (dag) {
-        if (prec == MOBIUS_F64) { MOBIUS_EPI_CASES(MOBIUS_F64, true) }
-        if (prec == MOBIUS_F32) { MOBIUS_EPI_CASES(MOBIUS_F32, true) }
-        if (prec == MOBIUS_F16) { MOBIUS_EPI_CASES(MOBIUS_F16, true) }
-    } else {
-        if (prec == MOBIUS_F64) { MOBIUS_EPI_CASES(MOBIUS_F64, false) }
-        if (prec == MOBIUS_F32) { MOBIUS_EPI_CASES(MOBIUS_F32, false) }
-        if (prec == MOBIUS_F16) { MOBIUS_EPI_CASES(MOBIUS_F16, false) }
-    }
-#undef MOBIUS_EPI_CASES
-    return false;
-}
-
-template <int P, bool D, int E>
-struct RunHop {
-    static void run(const HopParams &hp, hipStream_t st) { hop_launch<P, D, E>(hp, st); }
-};
-template <int P, bool D, int E>
-struct RunHopBatch {
-    static void run(const HopParams *g, int n, const int64_t *prefix, size_t dyn, int grid, int pf,
-                    hipStream_t st)
-    {
-        hop_batch_launch<P, D, E>(g, n, prefix, dyn, grid, pf, st);
-    }
-};
-
-}  // namespace
-
 size_t m5_epilogue_lds_bytes(int prec)
 {
     return prec == MOBIUS_F64 ? sizeof(M5Lds<double>) : sizeof(M5Lds<float>);
@@ -1342,18 +1365,28 @@ hipError_t launch_hop(const Geometry &g, const OpCoeffs &c, const void *links, c
                       const HopArgs &a, hipStream_t st)
 {
     const HopParams hp = make_hop_params(g, c, links, nbr, a);
-    if (!dispatch_hop<RunHop>(a.prec, a.dag, a.epi & ~EPI_BDAG, hp, st)) return hipErrorInvalidValue;
-    return hipGetLastError();
+    const int epi = a.epi & ~EPI_BDAG;
+    bool ok = false;
+    switch (a.prec) {
+    case MOBIUS_F64: ok = run_hop<MOBIUS_F64>(a.dag, epi, hp, st); break;
+    case MOBIUS_F32: ok = run_hop<MOBIUS_F32>(a.dag, epi, hp, st); break;
+    case MOBIUS_F16: ok = run_hop<MOBIUS_F16>(a.dag, epi, hp, st); break;
+    }
+    return ok ? hipGetLastError() : hipErrorInvalidValue;
 }
 
 hipError_t launch_hop_batch(int prec, int dag, int epi, const HopParams *groups_dev, int ngroups,
                             const int64_t *prefix_dev, size_t lds_bytes, int grid, int pf,
                             hipStream_t st)
 {
-    if (!dispatch_hop<RunHopBatch>(prec, dag, epi & ~EPI_BDAG, groups_dev, ngroups, prefix_dev,
-                                   lds_bytes, grid, pf, st))
-        return hipErrorInvalidValue;
-    return hipGetLastError();
+    epi &= ~EPI_BDAG;
+    bool ok = false;
+    switch (prec) {
+    case MOBIUS_F64: ok = run_hop_batch<MOBIUS_F64>(dag, epi, groups_dev, ngroups, prefix_dev, lds_bytes, grid, pf, st); break;
+    case MOBIUS_F32: ok = run_hop_batch<MOBIUS_F32>(dag, epi, groups_dev, ngroups, prefix_dev, lds_bytes, grid, pf, st); break;
+    case MOBIUS_F16: ok = run_hop_batch<MOBIUS_F16>(dag, epi, groups_dev, ngroups, prefix_dev, lds_bytes, grid, pf, st); break;
+    }
+    return ok ? hipGetLastError() : hipErrorInvalidValue;
 }
 
 namespace {
@@ -1540,5 +1573,7 @@ hipError_t launch_ring_batch(int kind, int prec, int prec2, const VecSys *sys_de
     }
     return hipGetLastError();
 }
+
+#endif  // MOBIUS_HOP_PREC
 
 }  // namespace mobius
