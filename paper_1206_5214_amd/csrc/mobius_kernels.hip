@@ -37,6 +37,20 @@ size_t link_lds_bytes(int spw, bool rows)
 // hop kernel: out = epilogue( -1/2 sum_mu [...] )  on every s-slice
 
 
+// Order in which a lane visits its eight directions (index d of the neighbour
+// and link records: 0..3 forward x, y, z, t; 4..7 backward).  A neighbour
+// spinor is read by eight sites; the reader one t-slice earlier starts a slice
+// time before the readers in the spinor's own slice, the one a t-slice later a
+// slice time after them.  With t- first and t+ last the reads fall close
+// together, while the line is still in the XCD's L2 (at 24^3 x 64, Ls = 12 the
+// L2 turns over about every 5 us and a wavefront lives 10 to 19 us): the FP64
+// hop reads 3.04 GB from memory instead of 4.48.  The pairs -mu, +mu in between
+// are adjacent because the two reads of one wavefront overlap in the L1.
+// Against x+ y+ z+ t+ x- y- z- t-, D_pre and D_pre^+ there: FP64 2090 and 2265
+// to 2010 and 2215 us, FP16 600 and 650 to 565 and 607 us; FP64 hop at
+// 16^3 x 32, Ls = 16: 160 to 147 us (the reverse order: 166 us).
+__device__ constexpr int HOP_DIR[8] = {7, 4, 0, 5, 1, 6, 2, 3};
+
 // PF: software pipelining of the direction loop.  0: operands of direction d
 // are loaded in segment d; 1: the neighbour spinor of direction d+1 is loaded
 // while direction d computes; 2: its link as well.  The eight neighbour
@@ -147,33 +161,34 @@ __device__ __forceinline__ void hop_block(const HopParams &hp, int64_t lb)
         RawH nx, nx2;
         LinkH2 unx;
         LinkRows rnx;
-        load_raw_f16(bin, N5, jn[0], nx);
+        load_raw_f16(bin, N5, jn[HOP_DIR[0]], nx);
         if constexpr (MF) {
-            load_raw_f16(bin, N5, jn[1], nx2);
-            ls.get_rows(0, quad, rnx);
+            load_raw_f16(bin, N5, jn[HOP_DIR[1]], nx2);
+            ls.get_rows(HOP_DIR[0], quad, rnx);
         } else if constexpr (PF >= 2) {
-            ls.template get_h2<true>(0, unx);
+            ls.template get_h2<(HOP_DIR[0] < 4)>(HOP_DIR[0], unx);
         }
 #pragma unroll
-        for (int d = 0; d < 8; ++d) {
+        for (int q = 0; q < 8; ++q) {
+            const int d = HOP_DIR[q], d1 = HOP_DIR[q < 7 ? q + 1 : 7], d2 = HOP_DIR[q < 6 ? q + 2 : 7];
             const RawH o = nx;
             if constexpr (MF) {
                 nx = nx2;
-                if (d < 6) load_raw_f16(bin, N5, jn[d + 2], nx2);
+                if (q < 6) load_raw_f16(bin, N5, jn[d2], nx2);
             } else {
-                if (d < 7) load_raw_f16(bin, N5, jn[d + 1], nx);
+                if (q < 7) load_raw_f16(bin, N5, jn[d1], nx);
             }
             LinkH2 u;
             LinkRows ur;
             if constexpr (MF) {
                 ur = rnx;
-                if (d < 7) ls.get_rows(d + 1, quad, rnx);
+                if (q < 7) ls.get_rows(d1, quad, rnx);
             } else if constexpr (PF >= 2) {
                 u = unx;
-                if (d < 3)
-                    ls.template get_h2<true>(d + 1, unx);
-                else if (d < 7)
-                    ls.template get_h2<false>(d + 1, unx);
+                if (q < 7 && d1 < 4)
+                    ls.template get_h2<true>(d1, unx);
+                else if (q < 7)
+                    ls.template get_h2<false>(d1, unx);
             } else {
                 if (d < 4)
                     ls.template get_h2<true>(d, u);
@@ -229,23 +244,24 @@ __device__ __forceinline__ void hop_block(const HopParams &hp, int64_t lb)
         }
     } else {
     cx<T> nxt[12], unx[9];
-    if constexpr (PF >= 1) S::load(bin, N5, jn[0], nxt);
-    if constexpr (PF >= 2) ls.get(0, unx);
+    if constexpr (PF >= 1) S::load(bin, N5, jn[HOP_DIR[0]], nxt);
+    if constexpr (PF >= 2) ls.get(HOP_DIR[0], unx);
 
 #pragma unroll
-    for (int d = 0; d < 8; ++d) {
+    for (int q = 0; q < 8; ++q) {
+        const int d = HOP_DIR[q], d1 = HOP_DIR[q < 7 ? q + 1 : 7];
         cx<T> chi[12], u[9];
         if constexpr (PF >= 1) {
 #pragma unroll
             for (int c = 0; c < 12; ++c) chi[c] = nxt[c];
-            if (d < 7) S::load(bin, N5, jn[d + 1], nxt);
+            if (q < 7) S::load(bin, N5, jn[d1], nxt);
         } else {
             S::load(bin, N5, jn[d], chi);
         }
         if constexpr (PF >= 2) {
 #pragma unroll
             for (int e = 0; e < 9; ++e) u[e] = unx[e];
-            if (d < 7) ls.get(d + 1, unx);
+            if (q < 7) ls.get(d1, unx);
         } else {
             ls.get(d, u);
         }
