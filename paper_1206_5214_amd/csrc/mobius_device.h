@@ -899,9 +899,13 @@ __device__ __forceinline__ SiteMap site_map_lb(int Ls, int spw, int64_t Vh, int6
     m.wave = threadIdx.x >> 6;
     m.g = m.lane / Ls;
     m.s = m.lane - m.g * Ls;
-    int64_t i = (lb * WAVES + m.wave) * spw + m.g;
+    const int64_t first = (lb * WAVES + m.wave) * spw, i = first + m.g;
     m.site_ok = (m.g < spw) && (i < Vh);
-    m.i = m.site_ok ? i : 0;
+    // lanes without a site repeat their wavefront's first site, whose data the
+    // wavefront reads anyway (packed site 0 for all of them is a far cache line
+    // in every load: 24^3 x 64, Ls = 12, four idle lanes of 64: FP64 adjoint hop
+    // 824 to 791 us, FP32 413 to 394 us, FP16 260 to 247 us)
+    m.i = m.site_ok ? i : first < Vh ? first : 0;
     const int base = m.g * Ls;
     m.lm = base + (m.s == 0 ? Ls - 1 : m.s - 1);
     m.lp = base + (m.s == Ls - 1 ? 0 : m.s + 1);
