@@ -25,6 +25,9 @@ namespace {
 
 int sites_per_wave(int Ls) { return 64 / Ls; }
 
+// most workgroups of a launch in the y direction
+[[maybe_unused]] constexpr int MAX_GRID_Y = 65535;
+
 // dynamic LDS of one block for the staged links: [8][sites per block][record]
 template <int P>
 size_t link_lds_bytes(int spw, bool rows)
@@ -719,56 +722,116 @@ __global__ __launch_bounds__(256) void bulk_assemble_kernel(int64_t V, int Ls, i
     }
 }
 
-// canonical [s][t][z][y][x][12] complex128 <-> packed halves
-template <int P>
-__global__ __launch_bounds__(256) void pack_spinor_kernel(int64_t Vh, int Ls,
-                                                          const int32_t *canon_of,
-                                                          const double2 *canon, char *even,
-                                                          char *odd)
+// canonical [s][t][z][y][x][12] complex128 <-> packed halves, blockIdx.y the
+// right-hand side.  Memory bound: a lane of the packed side owns one 5d site
+// (64 of them in a row of each chunk), while a 5d site is a 192-byte record of
+// the canonical side, records of neighbouring lanes far apart.  The two sides
+// meet in LDS: on the canonical side twelve lanes move one record, so every
+// access covers whole 64-byte sectors.  (One lane per record on both sides
+// spread each access over 64 cache lines: at 24^3 x 64, Ls = 12 FP64 pack 969
+// and unpack 1666 us, now 764 and 802 us, 5.2 TB/s as a device copy; FP16
+// 663 and 1425 us, now 475 and 562 us.)  One wavefront per workgroup: 256
+// threads hold 55 KB of LDS and wait for each other (8^3 x 16: 8.1 against
+// 6.7 us).  The two parities' workgroups of one stretch of sites follow each
+// other on one XCD, whose L2 joins the records' shared lines; the canonical
+// field is not read back from there, so unpack stores it non-temporally (FP16
+// 629 to 562 us).
+constexpr int PACK_BLOCK = 64;
+
+template <typename T>
+struct PackLds {
+    static constexpr int STRIDE = 13;  // complex per 5d site: 12 and one against bank conflicts
+    cx<T> v[PACK_BLOCK * STRIDE];
+    int64_t rec[PACK_BLOCK];           // canonical index of each lane's record, -1: none
+};
+
+struct PackMap {
+    int p;
+    int64_t k5;  // packed 5d site of this lane
+    bool ok;
+};
+
+template <typename T>
+__device__ __forceinline__ PackMap pack_map(int64_t Vh, int Ls, const int32_t *canon_of, PackLds<T> &lds)
 {
-    using S = Spin<P>;
-    using T = typename S::T;
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t N5 = Vh * Ls;
-    if (t >= 2 * N5) return;
-    const int p = (int)(t / N5);
-    const int64_t k5 = t - p * N5;
-    const int64_t i = k5 / Ls;
-    const int s = (int)(k5 - i * Ls);
-    const int64_t V = 2 * Vh;
-    const int64_t c = canon_of[p * Vh + i];
-    const double2 *src = canon + ((int64_t)s * V + c) * 12;
-    cx<T> v[12];
-#pragma unroll
-    for (int q = 0; q < 12; ++q) {
-        double2 z = src[q];
-        v[q] = {(T)z.x, (T)z.y};
+    const int64_t lb = logical_block(1);
+    PackMap m;
+    m.p = (int)(lb & 1);
+    m.k5 = (lb >> 1) * PACK_BLOCK + threadIdx.x;
+    m.ok = m.k5 < Vh * Ls;
+    int64_t rec = -1;
+    if (m.ok) {
+        const uint32_t i = (uint32_t)m.k5 / (uint32_t)Ls, s = (uint32_t)m.k5 - i * (uint32_t)Ls;
+        rec = (int64_t)s * 2 * Vh + canon_of[m.p * Vh + i];
     }
-    S::store(Buf(p == 0 ? even : odd, S::bytes(N5)), (uint32_t)N5, (uint32_t)k5, v);
+    lds.rec[threadIdx.x] = rec;
+    return m;
 }
 
 template <int P>
-__global__ __launch_bounds__(256) void unpack_spinor_kernel(int64_t Vh, int Ls,
-                                                            const int32_t *canon_of,
-                                                            const char *even, const char *odd,
-                                                            double2 *canon)
+__global__ __launch_bounds__(PACK_BLOCK) void pack_spinor_kernel(int64_t Vh, int Ls,
+                                                                 const int32_t *canon_of,
+                                                                 const double2 *canon, char *even,
+                                                                 char *odd)
 {
     using S = Spin<P>;
     using T = typename S::T;
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    __shared__ PackLds<T> lds;
     const int64_t N5 = Vh * Ls;
-    if (t >= 2 * N5) return;
-    const int p = (int)(t / N5);
-    const int64_t k5 = t - p * N5;
-    const int64_t i = k5 / Ls;
-    const int s = (int)(k5 - i * Ls);
-    const int64_t V = 2 * Vh;
-    const int64_t c = canon_of[p * Vh + i];
-    cx<T> v[12];
-    S::load(Buf(p == 0 ? even : odd, S::bytes(N5)), (uint32_t)N5, (uint32_t)k5, v);
-    double2 *dst = canon + ((int64_t)s * V + c) * 12;
+    const PackMap m = pack_map(Vh, Ls, canon_of, lds);
+    canon += (int64_t)blockIdx.y * 2 * N5 * 12;
+    __syncthreads();
+    double2 z[12];
 #pragma unroll
-    for (int q = 0; q < 12; ++q) dst[q] = make_double2((double)v[q].r, (double)v[q].i);
+    for (int j = 0; j < 12; ++j) {  // (all in flight together; lanes past the end read record 0)
+        const uint32_t u = (uint32_t)j * PACK_BLOCK + threadIdx.x, r = u / 12u, c = u - r * 12u;
+        const int64_t rec = lds.rec[r];
+        z[j] = canon[(rec < 0 ? 0 : rec) * 12 + c];
+    }
+#pragma unroll
+    for (int j = 0; j < 12; ++j) {
+        const uint32_t u = (uint32_t)j * PACK_BLOCK + threadIdx.x, r = u / 12u, c = u - r * 12u;
+        lds.v[r * PackLds<T>::STRIDE + c] = {(T)z[j].x, (T)z[j].y};
+    }
+    __syncthreads();
+    if (!m.ok) return;
+    cx<T> v[12];
+#pragma unroll
+    for (int c = 0; c < 12; ++c) v[c] = lds.v[threadIdx.x * PackLds<T>::STRIDE + c];
+    S::store(Buf((m.p == 0 ? even : odd) + blockIdx.y * S::bytes(N5), S::bytes(N5)), (uint32_t)N5,
+             (uint32_t)m.k5, v);
+}
+
+template <int P>
+__global__ __launch_bounds__(PACK_BLOCK) void unpack_spinor_kernel(int64_t Vh, int Ls,
+                                                                   const int32_t *canon_of,
+                                                                   const char *even, const char *odd,
+                                                                   double2 *canon)
+{
+    using S = Spin<P>;
+    using T = typename S::T;
+    __shared__ PackLds<T> lds;
+    const int64_t N5 = Vh * Ls;
+    const PackMap m = pack_map(Vh, Ls, canon_of, lds);
+    canon += (int64_t)blockIdx.y * 2 * N5 * 12;
+    if (m.ok) {
+        cx<T> v[12];
+        S::load(Buf((m.p == 0 ? even : odd) + blockIdx.y * S::bytes(N5), S::bytes(N5)), (uint32_t)N5,
+                (uint32_t)m.k5, v);
+#pragma unroll
+        for (int c = 0; c < 12; ++c) lds.v[threadIdx.x * PackLds<T>::STRIDE + c] = v[c];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 12; ++j) {
+        const uint32_t u = (uint32_t)j * PACK_BLOCK + threadIdx.x, r = u / 12u, c = u - r * 12u;
+        const int64_t rec = lds.rec[r];
+        if (rec >= 0) {
+            const cx<T> z = lds.v[r * PackLds<T>::STRIDE + c];
+            typedef double f64x2 __attribute__((ext_vector_type(2)));
+            __builtin_nontemporal_store(f64x2{(double)z.r, (double)z.i}, reinterpret_cast<f64x2 *>(canon + rec * 12 + c));
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1287,20 +1350,27 @@ hipError_t launch_bulk_assemble(const Geometry &g, const void *psi4, const void 
     return hipGetLastError();
 }
 
+namespace {
+// one block per PACK_BLOCK packed 5d sites of a parity, the parities alternating
+dim3 pack_grid(const Geometry &g, int nrhs)
+{
+    return dim3((unsigned)(2 * ((g.N5 + PACK_BLOCK - 1) / PACK_BLOCK)), (unsigned)nrhs);
+}
+}  // namespace
+
 hipError_t launch_pack_spinor(const Geometry &g, int prec, const void *canon, void *even, void *odd,
                               int nrhs, hipStream_t st)
 {
-    const int64_t n = 2 * g.N5;
-    dim3 grid((unsigned)((n + 255) / 256));
+    const dim3 blk(PACK_BLOCK);
     const int64_t fb = field_bytes(g, prec);
-    for (int r = 0; r < nrhs; ++r) {
+    for (int r = 0; r < nrhs; r += MAX_GRID_Y) {
+        const dim3 grid = pack_grid(g, std::min(nrhs - r, MAX_GRID_Y));
         const double2 *c = static_cast<const double2 *>(canon) + (int64_t)r * 2 * g.N5 * 12;
-        char *e = static_cast<char *>(even) + r * fb;
-        char *o = static_cast<char *>(odd) + r * fb;
+        char *e = static_cast<char *>(even) + r * fb, *o = static_cast<char *>(odd) + r * fb;
         switch (prec) {
-        case MOBIUS_F64: hipLaunchKernelGGL(pack_spinor_kernel<MOBIUS_F64>, grid, dim3(256), 0, st, g.Vh, g.Ls, g.canon_of, c, e, o); break;
-        case MOBIUS_F32: hipLaunchKernelGGL(pack_spinor_kernel<MOBIUS_F32>, grid, dim3(256), 0, st, g.Vh, g.Ls, g.canon_of, c, e, o); break;
-        case MOBIUS_F16: hipLaunchKernelGGL(pack_spinor_kernel<MOBIUS_F16>, grid, dim3(256), 0, st, g.Vh, g.Ls, g.canon_of, c, e, o); break;
+        case MOBIUS_F64: hipLaunchKernelGGL(pack_spinor_kernel<MOBIUS_F64>, grid, blk, 0, st, g.Vh, g.Ls, g.canon_of, c, e, o); break;
+        case MOBIUS_F32: hipLaunchKernelGGL(pack_spinor_kernel<MOBIUS_F32>, grid, blk, 0, st, g.Vh, g.Ls, g.canon_of, c, e, o); break;
+        case MOBIUS_F16: hipLaunchKernelGGL(pack_spinor_kernel<MOBIUS_F16>, grid, blk, 0, st, g.Vh, g.Ls, g.canon_of, c, e, o); break;
         default: return hipErrorInvalidValue;
         }
     }
@@ -1310,17 +1380,16 @@ hipError_t launch_pack_spinor(const Geometry &g, int prec, const void *canon, vo
 hipError_t launch_unpack_spinor(const Geometry &g, int prec, const void *even, const void *odd,
                                 void *canon, int nrhs, hipStream_t st)
 {
-    const int64_t n = 2 * g.N5;
-    dim3 grid((unsigned)((n + 255) / 256));
+    const dim3 blk(PACK_BLOCK);
     const int64_t fb = field_bytes(g, prec);
-    for (int r = 0; r < nrhs; ++r) {
+    for (int r = 0; r < nrhs; r += MAX_GRID_Y) {
+        const dim3 grid = pack_grid(g, std::min(nrhs - r, MAX_GRID_Y));
         double2 *c = static_cast<double2 *>(canon) + (int64_t)r * 2 * g.N5 * 12;
-        const char *e = static_cast<const char *>(even) + r * fb;
-        const char *o = static_cast<const char *>(odd) + r * fb;
+        const char *e = static_cast<const char *>(even) + r * fb, *o = static_cast<const char *>(odd) + r * fb;
         switch (prec) {
-        case MOBIUS_F64: hipLaunchKernelGGL(unpack_spinor_kernel<MOBIUS_F64>, grid, dim3(256), 0, st, g.Vh, g.Ls, g.canon_of, e, o, c); break;
-        case MOBIUS_F32: hipLaunchKernelGGL(unpack_spinor_kernel<MOBIUS_F32>, grid, dim3(256), 0, st, g.Vh, g.Ls, g.canon_of, e, o, c); break;
-        case MOBIUS_F16: hipLaunchKernelGGL(unpack_spinor_kernel<MOBIUS_F16>, grid, dim3(256), 0, st, g.Vh, g.Ls, g.canon_of, e, o, c); break;
+        case MOBIUS_F64: hipLaunchKernelGGL(unpack_spinor_kernel<MOBIUS_F64>, grid, blk, 0, st, g.Vh, g.Ls, g.canon_of, e, o, c); break;
+        case MOBIUS_F32: hipLaunchKernelGGL(unpack_spinor_kernel<MOBIUS_F32>, grid, blk, 0, st, g.Vh, g.Ls, g.canon_of, e, o, c); break;
+        case MOBIUS_F16: hipLaunchKernelGGL(unpack_spinor_kernel<MOBIUS_F16>, grid, blk, 0, st, g.Vh, g.Ls, g.canon_of, e, o, c); break;
         default: return hipErrorInvalidValue;
         }
     }

@@ -1,0 +1,54 @@
+"""Kernels at the sizes where their tiling can go wrong: partial last
+workgroups, idle lanes, several right-hand sides (GPU)."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch_cuda():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    return torch
+
+
+def _setup(torch, dims, Ls, nrhs, seed=3, **kw):
+    from paper_1206_5214_amd import inputs, mobius
+    rng = np.random.default_rng(seed)
+    U = inputs.random_links(dims, 0.4, rng)
+    eta = inputs.gaussian_spinor(dims, Ls, rng, nrhs if nrhs > 1 else None)
+    op = mobius.Operator(dims, Ls, 1.8, 0.05, 1.5, 0.5, torch.from_numpy(U).cuda(), **kw)
+    return mobius, op, torch.from_numpy(eta).cuda()
+
+
+# 5d sites per parity below, at and past one workgroup's 64, and one site per
+# wavefront (Ls > 32)
+@pytest.mark.parametrize("dims,Ls", [((2, 2, 2, 2), 2), ((2, 2, 2, 4), 4), ((4, 2, 2, 6), 5),
+                                     ((6, 4, 2, 4), 33), ((4, 4, 4, 4), 8)])
+@pytest.mark.parametrize("nrhs", [1, 3])
+def test_pack_unpack_exact(torch_cuda, dims, Ls, nrhs):
+    """FP64 is a permutation, FP32 one rounding, FP16 within one binary16 step
+    of the site's largest component (half a step of rounding and the norm's)."""
+    torch = torch_cuda
+    mobius, op, eta = _setup(torch, dims, Ls, nrhs)
+    for prec in (mobius.F64, mobius.F32, mobius.F16):
+        even, odd = op.pack(eta, prec, nrhs)
+        got = op.unpack(even, odd, prec, nrhs)
+        assert got.shape == eta.shape
+        if prec == mobius.F64:
+            assert torch.equal(got, eta)
+        elif prec == mobius.F32:
+            assert torch.equal(got, eta.to(torch.complex64).to(torch.complex128))
+        else:
+            v = torch.view_as_real(eta)
+            top = v.abs().amax(dim=(-3, -2, -1), keepdim=True)
+            assert ((torch.view_as_real(got) - v).abs() <= 2.0**-11 * top).all()
+        if nrhs > 1:  # each right-hand side as by itself
+            fb = op.field_bytes(prec)
+            for r in range(nrhs):
+                e1, o1 = op.pack(eta[r].contiguous(), prec)
+                assert torch.equal(e1, even[r * fb:(r + 1) * fb])
+                assert torch.equal(o1, odd[r * fb:(r + 1) * fb])
+    op.close()
