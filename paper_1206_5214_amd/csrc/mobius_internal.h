@@ -239,16 +239,24 @@ void *noalloc_scratch(int device);
 hipError_t launch_zero(void *ptr, int64_t bytes, hipStream_t st);
 // a packed field of n5 5d sites with seeded values of Gaussian-field magnitude
 hipError_t launch_fill_random(int prec, void *ptr, int64_t n5, uint32_t seed, hipStream_t st);
-// Scalar updates of CGLS, on device (one thread per system):
 // Most search directions one chunk of a mixed-precision CGLS keeps for its
 // deferred x update.
 constexpr int RING_MAX = 16;
 
+// A kernel that needs a norm sums its partials itself, in every workgroup, up
+// to RED_DIRECT of them (8 loads a thread, about the latency of one reduction
+// launch less); longer ones are first reduced to RED_PARTS sums by a launch of
+// their own (24^3 x 64: 22118 partials).
+constexpr int64_t RED_DIRECT = 2048;
+constexpr int RED_PARTS = 64;
+
+// CG scalars of one system, kept by the kernels that use them: the p update
+// sets gamma_new and beta, the r update qq, alpha and gamma = gamma_new.
 struct CgScalars {
-    double gamma;      // |s|^2 of the current direction
+    double gamma;      // |s|^2 of the previous direction (before the p update)
     double qq;         // |q|^2
-    double rr;         // |r|^2
-    double gamma_new;
+    double rr;         // |r|^2 (at the end of a chunk)
+    double gamma_new;  // |s|^2 of the current direction
     double alpha, beta;
     // Coefficient history for the Lanczos estimate of the condition number:
     // hist[k] = (beta_{k-1}, alpha_k) of iteration k (beta_{k-1} = 0 at the
@@ -262,15 +270,15 @@ struct CgScalars {
 
 // One system (one lattice, one right-hand side) of a batched vector kernel.
 // Field roles per kernel:
-//   VEC_CG_XR       a = x (prec2; null: no x update), b = p, c = r, d = q, s0 = alpha; |r|^2 partials
+//   VEC_CG_XR       a = x (prec2; null: no x update), b = p, c = r, d = q; |r|^2 partials
 //   VEC_AXPBY(_NORM) d = s0 a + s1 b (null scalar = 1) [; |d|^2 partials]
 //   VEC_NORM2       |a|^2 partials
 //   VEC_CONVERT     b (prec2) = a (prec)
 //   VEC_ACCUMULATE  d (FP64) += a (prec); a = 0
 //   VEC_DOT         Re <a, b> partials (a and b in precision prec)
-//   VEC_PUPD_X      c (prec2) += s0 b;  b = a + s1 b          (x += alpha p_old; p = s + beta p_old)
+//   VEC_PUPD_X      c (prec2) += s0 b;  b = a + beta b        (x += alpha p_old; p = s + beta p_old)
 //   VEC_XFLUSH      c (prec2) += s0 a                          (x += alpha p)
-//   VEC_PUPD_RING   p[slot] = a + s1 p[prev]                   (b = p[0]; slots sstride bytes apart)
+//   VEC_PUPD_RING   p[slot] = a + beta p[prev]                 (b = p[0]; slots sstride bytes apart)
 //   VEC_XRING       c (prec2) += sum_{i < n} s0[i] p[i]        (b = p[0]; slots sstride bytes apart)
 struct VecSys {
     char *a, *b, *c, *d;
@@ -278,6 +286,9 @@ struct VecSys {
     int64_t sstride;       // bytes between the slots of a ring of directions
     double *partials;      // this system's partial slots
     int64_t nparts;        // number of valid partial slots (for the reduction)
+    const double *red;     // partial sums of the norm that gives beta (p update) or alpha (r
+    int64_t nred;          // update), and their number; never the slots the kernel writes
+    CgScalars *cg;         // this system's scalars
     int64_t N5;
     int32_t flag;          // index into the active flags (-1: always active)
     int32_t Ls;            // fifth-dimension extent of the system's lattice
@@ -292,21 +303,26 @@ hipError_t launch_vec_batch(int kind, int prec, int prec2, const VecSys *sys_dev
 hipError_t launch_reduce_batch(const VecSys *sys_dev, int nsys, const int32_t *active,
                                int64_t count_override, double *out, int64_t out_stride,
                                hipStream_t st);
-// VEC_PUPD_RING (a0 = slot, a1 = prev) or VEC_XRING (a0 = n) over a ring of
-// directions; prec: the directions, prec2: x
-hipError_t launch_ring_batch(int kind, int prec, int prec2, const VecSys *sys_dev, int nsys,
-                             int64_t max_n5, const int32_t *active, int a0, int a1, hipStream_t st);
-// op 0: alpha = gamma / qq (also kept in aring[slot] when slot >= 0);
-// op 1: beta, gamma;  op 2: alpha = 0
-hipError_t launch_cg_scalar_batch(CgScalars *sc, int nsys, int op, const int32_t *active,
-                                  int32_t *restart, hipStream_t st, int slot = -1);
-// r = a -= s0 b (|r|^2 partials per site block) and c = I^-+ r (mode 0), c =
-// I^-1 r (mode 1), nothing (mode 2) or c = B^+ I^-+ r (mode 3, constant
-// coefficients), in the site-lane mapping of the hop
+// out[sys * RED_PARTS + b] = sum of the b-th part of the system's nparts partials
+hipError_t launch_reduce_parts(const VecSys *sys_dev, int nsys, const int32_t *active, double *out,
+                               hipStream_t st);
+// alpha = 0 (no x update pending)
+hipError_t launch_clear_alpha(CgScalars *sc, int nsys, const int32_t *active, hipStream_t st);
+// The updates that compute a CG scalar from v.red: VEC_PUPD_X, VEC_PUPD_RING
+// (beta; a set restart flag makes it 0) and VEC_CG_XR (alpha, also kept in
+// aring[slot] when slot >= 0; clears the restart flag)
+hipError_t launch_cg_update(int kind, int prec, int prec2, const VecSys *sys_dev, int nsys, int64_t max_n5,
+                            const int32_t *active, int32_t *restart, int slot, int prev, hipStream_t st);
+// VEC_XRING over n directions (prec: the directions, prec2: x)
+hipError_t launch_xring(int prec, int prec2, const VecSys *sys_dev, int nsys, int64_t max_n5,
+                        const int32_t *active, int n, hipStream_t st);
+// r = a -= alpha b (alpha from v.red as VEC_CG_XR; |r|^2 partials per site block)
+// and c = I^-+ r (mode 0), c = I^-1 r (mode 1), nothing (mode 2) or c =
+// B^+ I^-+ r (mode 3, constant coefficients), in the site-lane mapping of the hop
 // (one workgroup per site block and system); max_blocks is the largest number
 // of site blocks of any system
 hipError_t launch_rupd_m5inv_batch(int prec, const VecSys *sys_dev, int nsys, int64_t max_blocks,
-                                   const int32_t *active, int mode, hipStream_t st);
+                                   const int32_t *active, int32_t *restart, int slot, int mode, hipStream_t st);
 
 // Link derivative of the pseudofermion action (mobius_force.hip): for the
 // sites y of one parity p, grad[mu][canon(y)] (complex128 3x3, canonical link

@@ -897,10 +897,72 @@ __device__ __forceinline__ bool sys_inactive(const VecSys &v, const int32_t *act
     return v.flag >= 0 && active && active[v.flag] == 0;
 }
 
-// x (PX) += alpha p;  r -= alpha q;  partials of |r|^2.  a = x, b = p, c = r, d = q, s0 = alpha
+// The CG scalars.  The kernel that needs beta or alpha sums the norm it depends
+// on itself, every workgroup the same partial sums in the same order, and its
+// first workgroup keeps the scalars: a reduction launch and a scalar launch
+// per norm (4.6 us each) were a fifth of an iteration on an 8^3 x 16 lattice.
+// Nothing a kernel reads here is written by the same kernel (beta's reads gamma
+// and the restart flag, which alpha's writes; alpha's reads gamma_new, which
+// beta's writes), so no workgroup waits for another.
+
+// sum of n partial sums by the whole workgroup (BLAS_BLOCK threads), in every thread
+static_assert(BLOCK == BLAS_BLOCK, "the r update runs in the site kernels' workgroups");
+__device__ __forceinline__ double block_total(const double *part, int64_t n)
+{
+    __shared__ double red[BLAS_BLOCK / 64];
+    double t = 0;
+#pragma unroll 4
+    for (int64_t k = threadIdx.x; k < n; k += BLAS_BLOCK) t += part[k];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = t;
+    __syncthreads();
+    t = 0;
+#pragma unroll
+    for (int w = 0; w < BLAS_BLOCK / 64; ++w) t += red[w];
+    return t;
+}
+
+// beta = gamma_new / gamma (0 when the system restarts) with gamma_new = the sum
+// of v.red
+__device__ __forceinline__ double cg_beta(const VecSys &v, const int32_t *restart)
+{
+    CgScalars &s = *v.cg;
+    const double gamma = s.gamma;
+    const bool rs = restart[v.flag] != 0;
+    const double g = block_total(v.red, v.nred);
+    const double beta = (!rs && gamma > 0) ? g / gamma : 0.0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        s.gamma_new = g;
+        s.beta = beta;
+        if (s.hist && s.nhist < s.hmax) s.hist[2 * s.nhist] = beta;
+    }
+    return beta;
+}
+
+// alpha = gamma_new / |q|^2 with |q|^2 = the sum of v.red; slot: see aring
+__device__ __forceinline__ double cg_alpha(const VecSys &v, int32_t *restart, int slot)
+{
+    CgScalars &s = *v.cg;
+    const double g = s.gamma_new;
+    const double qq = block_total(v.red, v.nred);
+    const double alpha = qq > 0 ? g / qq : 0.0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        s.qq = qq;
+        s.alpha = alpha;
+        s.gamma = g;
+        if (s.hist && s.nhist < s.hmax) s.hist[2 * s.nhist++ + 1] = alpha;
+        if (slot >= 0) s.aring[slot] = alpha;
+        restart[v.flag] = 0;
+    }
+    return alpha;
+}
+
+// x (PX) += alpha p;  r -= alpha q;  partials of |r|^2.  a = x, b = p, c = r, d = q
 // (a null: r and its norm only, x is updated elsewhere).
 template <int P, int PX>
-__global__ __launch_bounds__(BLAS_BLOCK) void cg_xr_batch(const VecSys *sys, const int32_t *active)
+__global__ __launch_bounds__(BLAS_BLOCK) void cg_xr_batch(const VecSys *sys, const int32_t *active,
+                                                          int32_t *restart, int slot)
 {
     const VecSys v = sys[blockIdx.y];
     if (sys_inactive(v, active)) return;
@@ -910,26 +972,29 @@ __global__ __launch_bounds__(BLAS_BLOCK) void cg_xr_batch(const VecSys *sys, con
     using TX = typename SX::T;
     const int64_t k = (int64_t)blockIdx.x * BLAS_BLOCK + threadIdx.x;
     if ((int64_t)blockIdx.x * BLAS_BLOCK >= v.N5) return;
+    const bool ok = k < v.N5;
+    const int64_t fb = S::bytes(v.N5);
+    const uint32_t n5 = (uint32_t)v.N5, kk = (uint32_t)(ok ? k : v.N5 - 1);
+    const Buf bx(v.a, SX::bytes(v.N5)), bp(v.b, fb), br(v.c, fb), bq(v.d, fb);
+    cx<T> rv[12], qv[12];
+    S::load(br, n5, kk, rv);
+    S::load(bq, n5, kk, qv);
+    const double alpha = cg_alpha(v, restart, slot);
     double n = 0;
-    if (k < v.N5) {
-        const T al = (T)*v.s0;
-        const TX alx = (TX)*v.s0;
-        const int64_t fb = S::bytes(v.N5);
-        const uint32_t n5 = (uint32_t)v.N5, kk = (uint32_t)k;
-        const Buf bx(v.a, SX::bytes(v.N5)), bp(v.b, fb), br(v.c, fb), bq(v.d, fb);
-        cx<TX> xv[12];
-        cx<T> pv[12], rv[12];
+    if (ok) {
+        const T al = (T)alpha;
         if (v.a) {
+            const TX alx = (TX)alpha;
+            cx<TX> xv[12];
+            cx<T> pv[12];
             SX::load(bx, n5, kk, xv);
             S::load(bp, n5, kk, pv);
 #pragma unroll
             for (int c = 0; c < 12; ++c) xv[c] = xv[c] + alx * cx<TX>{(TX)pv[c].r, (TX)pv[c].i};
             SX::store(bx, n5, kk, xv);
         }
-        S::load(br, n5, kk, rv);
-        S::load(bq, n5, kk, pv);
 #pragma unroll
-        for (int c = 0; c < 12; ++c) rv[c] = rv[c] - al * pv[c];
+        for (int c = 0; c < 12; ++c) rv[c] = rv[c] - al * qv[c];
         n = S::store_norm2(br, n5, kk, rv);
     }
     block_sum_store(n, v.partials, blockIdx.x);
@@ -1020,10 +1085,11 @@ __global__ __launch_bounds__(BLAS_BLOCK) void accumulate_batch(const VecSys *sys
     Spin<PI>::store(Buf(v.a, Spin<PI>::bytes(v.N5)), (uint32_t)v.N5, (uint32_t)k, z);
 }
 
-// x (PX) += alpha p_old;  p = s + beta p_old.  a = s, b = p, c = x, s0 = alpha, s1 = beta.
+// x (PX) += alpha p_old;  p = s + beta p_old.  a = s, b = p, c = x, s0 = alpha.
 // (The x update of a CG step moved here from the r update: p_old is read anyway.)
 template <int P, int PX>
-__global__ __launch_bounds__(BLAS_BLOCK) void pupd_x_batch(const VecSys *sys, const int32_t *active)
+__global__ __launch_bounds__(BLAS_BLOCK) void pupd_x_batch(const VecSys *sys, const int32_t *active,
+                                                           const int32_t *restart)
 {
     const VecSys v = sys[blockIdx.y];
     if (sys_inactive(v, active)) return;
@@ -1032,20 +1098,21 @@ __global__ __launch_bounds__(BLAS_BLOCK) void pupd_x_batch(const VecSys *sys, co
     using T = typename S::T;
     using TX = typename SX::T;
     const int64_t k = (int64_t)blockIdx.x * BLAS_BLOCK + threadIdx.x;
-    if (k >= v.N5) return;
-    const TX al = (TX)*v.s0;
-    const T be = (T)*v.s1;
+    if ((int64_t)blockIdx.x * BLAS_BLOCK >= v.N5) return;
     const int64_t fb = S::bytes(v.N5);
-    const uint32_t n5 = (uint32_t)v.N5, kk = (uint32_t)k;
+    const uint32_t n5 = (uint32_t)v.N5, kk = (uint32_t)(k < v.N5 ? k : v.N5 - 1);
     const Buf bs(v.a, fb), bp(v.b, fb), bx(v.c, SX::bytes(v.N5));
     cx<T> sv[12], pv[12];
     cx<TX> xv[12];
     S::load(bp, n5, kk, pv);
     SX::load(bx, n5, kk, xv);
+    S::load(bs, n5, kk, sv);
+    const TX al = (TX)*v.s0;
+    const T be = (T)cg_beta(v, restart);
+    if (k >= v.N5) return;
 #pragma unroll
     for (int c = 0; c < 12; ++c) xv[c] = xv[c] + al * cx<TX>{(TX)pv[c].r, (TX)pv[c].i};
     SX::store(bx, n5, kk, xv);
-    S::load(bs, n5, kk, sv);
 #pragma unroll
     for (int c = 0; c < 12; ++c) pv[c] = sv[c] + be * pv[c];
     S::store(bp, n5, kk, pv);
@@ -1075,24 +1142,26 @@ __global__ __launch_bounds__(BLAS_BLOCK) void xflush_batch(const VecSys *sys, co
 }
 
 // p[slot] = s + beta p[prev] in a ring of directions (the deferred x update
-// keeps one chunk's directions).  a = s, b = p[0], slots sstride bytes apart,
-// s1 = beta.
+// keeps one chunk's directions; slot = prev: in place).  a = s, b = p[0], slots
+// sstride bytes apart.
 template <int P>
 __global__ __launch_bounds__(BLAS_BLOCK) void pupd_ring_batch(const VecSys *sys, const int32_t *active,
-                                                              int slot, int prev)
+                                                              const int32_t *restart, int slot,
+                                                              int prev)
 {
     const VecSys v = sys[blockIdx.y];
     if (sys_inactive(v, active)) return;
     using S = Spin<P>;
     using T = typename S::T;
     const int64_t k = (int64_t)blockIdx.x * BLAS_BLOCK + threadIdx.x;
-    if (k >= v.N5) return;
-    const T be = (T)*v.s1;
+    if ((int64_t)blockIdx.x * BLAS_BLOCK >= v.N5) return;
     const int64_t fb = S::bytes(v.N5);
-    const uint32_t n5 = (uint32_t)v.N5, kk = (uint32_t)k;
-    cx<T> sv[12], pv[12];
+    const uint32_t n5 = (uint32_t)v.N5, kk = (uint32_t)(k < v.N5 ? k : v.N5 - 1);
+    cx<T> sv[12], pv[12];  // (in flight while beta is summed)
     S::load(Buf(v.b + prev * v.sstride, fb), n5, kk, pv);
     S::load(Buf(v.a, fb), n5, kk, sv);
+    const T be = (T)cg_beta(v, restart);
+    if (k >= v.N5) return;
 #pragma unroll
     for (int c = 0; c < 12; ++c) pv[c] = sv[c] + be * pv[c];
     S::store(Buf(v.b + slot * v.sstride, fb), n5, kk, pv);
@@ -1133,10 +1202,10 @@ __global__ __launch_bounds__(BLAS_BLOCK) void xring_batch(const VecSys *sys, con
 
 // r -= alpha q, |r|^2 per site block, and u = I^-+ r of the stored r, in the
 // site-lane mapping of the hop so that the Ls-direction solve stays inside a
-// wavefront.  a = r, b = q, c = u, s0 = alpha; one workgroup per site block.
+// wavefront.  a = r, b = q, c = u; one workgroup per site block.
 template <int P>
 __global__ __launch_bounds__(BLOCK) void rupd_m5inv_batch(const VecSys *sys, const int32_t *active,
-                                                          int mode)
+                                                          int32_t *restart, int slot, int mode)
 {
     const VecSys v = sys[blockIdx.y];
     if (sys_inactive(v, active)) return;
@@ -1154,7 +1223,7 @@ __global__ __launch_bounds__(BLOCK) void rupd_m5inv_batch(const VecSys *sys, con
     cx<T> rv[12], qv[12];
     S::load(br, n5, k5, rv);
     S::load(Buf(v.b, fb), n5, k5, qv);
-    const T al = (T)*v.s0;
+    const T al = (T)cg_alpha(v, restart, slot);
 #pragma unroll
     for (int c = 0; c < 12; ++c) rv[c] = rv[c] - al * qv[c];
     double n = 0;
@@ -1211,30 +1280,23 @@ __global__ __launch_bounds__(1024) void reduce_batch(const VecSys *sys, const in
     if (threadIdx.x == 0) out[blockIdx.x * out_stride] = sm[0];
 }
 
-// Per-system CG scalars.  op 0: alpha = gamma / qq;  op 1: beta = gamma_new /
-// gamma (0 when the system restarts), gamma = gamma_new.  Inactive systems get
-// alpha = beta = 0.
-__global__ void cg_scalar_batch(CgScalars *sc, int nsys, int op, const int32_t *active,
-                                int32_t *restart, int slot)
+// First level of a long sum: slot b of out[sys * RED_PARTS + b] = the b-th part
+// of the system's partials.
+__global__ __launch_bounds__(BLAS_BLOCK) void reduce_parts_batch(const VecSys *sys, const int32_t *active,
+                                                                 double *out)
+{
+    const VecSys v = sys[blockIdx.y];
+    if (sys_inactive(v, active) || v.nparts <= RED_DIRECT) return;
+    const int64_t n = v.nparts, a = n * blockIdx.x / RED_PARTS, b = n * (blockIdx.x + 1) / RED_PARTS;
+    const double t = block_total(v.partials + a, b - a);
+    if (threadIdx.x == 0) out[(int64_t)blockIdx.y * RED_PARTS + blockIdx.x] = t;
+}
+
+// alpha = 0 for every active system: no x update is pending
+__global__ void clear_alpha_batch(CgScalars *sc, int nsys, const int32_t *active)
 {
     const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= nsys) return;
-    CgScalars &s = sc[j];
-    const bool on = !active || active[j];
-    const bool rec = on && s.hist && s.nhist < s.hmax;
-    if (op == 2) {
-        if (on) s.alpha = 0.0;
-    } else if (op == 0) {
-        s.alpha = (on && s.qq > 0) ? s.gamma / s.qq : 0.0;
-        if (rec) s.hist[2 * s.nhist++ + 1] = s.alpha;
-        if (slot >= 0) s.aring[slot] = s.alpha;
-    } else {
-        const bool rs = restart && restart[j];
-        s.beta = (on && !rs && s.gamma > 0) ? s.gamma_new / s.gamma : 0.0;
-        s.gamma = s.gamma_new;
-        if (restart) restart[j] = 0;
-        if (rec) s.hist[2 * s.nhist] = s.beta;
-    }
+    if (j < nsys && (!active || active[j])) sc[j].alpha = 0.0;
 }
 
 }  // namespace
@@ -1544,12 +1606,6 @@ hipError_t launch_vec_batch(int kind, int prec, int prec2, const VecSys *sys_dev
     default: return hipErrorInvalidValue;                                               \
     }
     switch (kind) {
-    case VEC_CG_XR:
-        if (prec == MOBIUS_F64 && prec2 == MOBIUS_F64) MOBIUS_L((cg_xr_batch<MOBIUS_F64, MOBIUS_F64>));
-        else if (prec == MOBIUS_F32 && prec2 == MOBIUS_F32) MOBIUS_L((cg_xr_batch<MOBIUS_F32, MOBIUS_F32>));
-        else if (prec == MOBIUS_F16 && prec2 == MOBIUS_F32) MOBIUS_L((cg_xr_batch<MOBIUS_F16, MOBIUS_F32>));
-        else return hipErrorInvalidValue;
-        break;
     case VEC_AXPBY:
         switch (prec) {
         case MOBIUS_F64: MOBIUS_L((axpby_batch<MOBIUS_F64, false>)); break;
@@ -1568,12 +1624,6 @@ hipError_t launch_vec_batch(int kind, int prec, int prec2, const VecSys *sys_dev
         break;
     case VEC_NORM2: MOBIUS_P3(norm2_batch) break;
     case VEC_DOT: MOBIUS_P3(dot_batch) break;
-    case VEC_PUPD_X:
-        if (prec == MOBIUS_F64 && prec2 == MOBIUS_F64) MOBIUS_L((pupd_x_batch<MOBIUS_F64, MOBIUS_F64>));
-        else if (prec == MOBIUS_F32 && prec2 == MOBIUS_F32) MOBIUS_L((pupd_x_batch<MOBIUS_F32, MOBIUS_F32>));
-        else if (prec == MOBIUS_F16 && prec2 == MOBIUS_F32) MOBIUS_L((pupd_x_batch<MOBIUS_F16, MOBIUS_F32>));
-        else return hipErrorInvalidValue;
-        break;
     case VEC_XFLUSH:
         if (prec == MOBIUS_F64 && prec2 == MOBIUS_F64) MOBIUS_L((xflush_batch<MOBIUS_F64, MOBIUS_F64>));
         else if (prec == MOBIUS_F32 && prec2 == MOBIUS_F32) MOBIUS_L((xflush_batch<MOBIUS_F32, MOBIUS_F32>));
@@ -1614,47 +1664,74 @@ hipError_t launch_reduce_batch(const VecSys *sys_dev, int nsys, const int32_t *a
 }
 
 hipError_t launch_rupd_m5inv_batch(int prec, const VecSys *sys_dev, int nsys, int64_t max_blocks,
-                                   const int32_t *active, int mode, hipStream_t st)
+                                   const int32_t *active, int32_t *restart, int slot, int mode, hipStream_t st)
 {
+    if (slot >= RING_MAX) return hipErrorInvalidValue;
     const dim3 grid((unsigned)max_blocks, (unsigned)nsys), blk(BLOCK);
     switch (prec) {
-    case MOBIUS_F64: hipLaunchKernelGGL(rupd_m5inv_batch<MOBIUS_F64>, grid, blk, 0, st, sys_dev, active, mode); break;
-    case MOBIUS_F32: hipLaunchKernelGGL(rupd_m5inv_batch<MOBIUS_F32>, grid, blk, 0, st, sys_dev, active, mode); break;
-    case MOBIUS_F16: hipLaunchKernelGGL(rupd_m5inv_batch<MOBIUS_F16>, grid, blk, 0, st, sys_dev, active, mode); break;
+    case MOBIUS_F64: hipLaunchKernelGGL(rupd_m5inv_batch<MOBIUS_F64>, grid, blk, 0, st, sys_dev, active, restart, slot, mode); break;
+    case MOBIUS_F32: hipLaunchKernelGGL(rupd_m5inv_batch<MOBIUS_F32>, grid, blk, 0, st, sys_dev, active, restart, slot, mode); break;
+    case MOBIUS_F16: hipLaunchKernelGGL(rupd_m5inv_batch<MOBIUS_F16>, grid, blk, 0, st, sys_dev, active, restart, slot, mode); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
-hipError_t launch_cg_scalar_batch(CgScalars *sc, int nsys, int op, const int32_t *active,
-                                  int32_t *restart, hipStream_t st, int slot)
+hipError_t launch_reduce_parts(const VecSys *sys_dev, int nsys, const int32_t *active, double *out,
+                               hipStream_t st)
 {
-    if (slot >= RING_MAX) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(cg_scalar_batch, dim3((nsys + 63) / 64), dim3(64), 0, st, sc, nsys, op,
-                       active, restart, slot);
+    hipLaunchKernelGGL(reduce_parts_batch, dim3(RED_PARTS, (unsigned)nsys), dim3(BLAS_BLOCK), 0, st, sys_dev,
+                       active, out);
     return hipGetLastError();
 }
 
-hipError_t launch_ring_batch(int kind, int prec, int prec2, const VecSys *sys_dev, int nsys,
-                             int64_t max_n5, const int32_t *active, int a0, int a1, hipStream_t st)
+hipError_t launch_clear_alpha(CgScalars *sc, int nsys, const int32_t *active, hipStream_t st)
+{
+    hipLaunchKernelGGL(clear_alpha_batch, dim3((nsys + 63) / 64), dim3(64), 0, st, sc, nsys, active);
+    return hipGetLastError();
+}
+
+hipError_t launch_cg_update(int kind, int prec, int prec2, const VecSys *sys_dev, int nsys, int64_t max_n5,
+                            const int32_t *active, int32_t *restart, int slot, int prev, hipStream_t st)
 {
     const dim3 grid((unsigned)((max_n5 + BLAS_BLOCK - 1) / BLAS_BLOCK), (unsigned)nsys), blk(BLAS_BLOCK);
-    if (kind == VEC_PUPD_RING) {
-        if (a0 < 0 || a0 >= RING_MAX || a1 < 0 || a1 >= RING_MAX) return hipErrorInvalidValue;
+    if (slot >= RING_MAX || prev >= RING_MAX) return hipErrorInvalidValue;
+#define MOBIUS_PX(K, ...)                                                               \
+    if (prec == MOBIUS_F64 && prec2 == MOBIUS_F64)                                      \
+        hipLaunchKernelGGL((K<MOBIUS_F64, MOBIUS_F64>), grid, blk, 0, st, __VA_ARGS__); \
+    else if (prec == MOBIUS_F32 && prec2 == MOBIUS_F32)                                 \
+        hipLaunchKernelGGL((K<MOBIUS_F32, MOBIUS_F32>), grid, blk, 0, st, __VA_ARGS__); \
+    else if (prec == MOBIUS_F16 && prec2 == MOBIUS_F32)                                 \
+        hipLaunchKernelGGL((K<MOBIUS_F16, MOBIUS_F32>), grid, blk, 0, st, __VA_ARGS__); \
+    else                                                                                \
+        return hipErrorInvalidValue
+    switch (kind) {
+    case VEC_CG_XR: MOBIUS_PX(cg_xr_batch, sys_dev, active, restart, slot); break;
+    case VEC_PUPD_X: MOBIUS_PX(pupd_x_batch, sys_dev, active, restart); break;
+    case VEC_PUPD_RING:
+        if (slot < 0 || prev < 0) return hipErrorInvalidValue;
         switch (prec) {
-        case MOBIUS_F32: hipLaunchKernelGGL(pupd_ring_batch<MOBIUS_F32>, grid, blk, 0, st, sys_dev, active, a0, a1); break;
-        case MOBIUS_F16: hipLaunchKernelGGL(pupd_ring_batch<MOBIUS_F16>, grid, blk, 0, st, sys_dev, active, a0, a1); break;
+        case MOBIUS_F64: hipLaunchKernelGGL(pupd_ring_batch<MOBIUS_F64>, grid, blk, 0, st, sys_dev, active, restart, slot, prev); break;
+        case MOBIUS_F32: hipLaunchKernelGGL(pupd_ring_batch<MOBIUS_F32>, grid, blk, 0, st, sys_dev, active, restart, slot, prev); break;
+        case MOBIUS_F16: hipLaunchKernelGGL(pupd_ring_batch<MOBIUS_F16>, grid, blk, 0, st, sys_dev, active, restart, slot, prev); break;
         default: return hipErrorInvalidValue;
         }
-    } else if (kind == VEC_XRING) {
-        if (a0 < 1 || a0 > RING_MAX || prec2 != MOBIUS_F32) return hipErrorInvalidValue;
-        switch (prec) {
-        case MOBIUS_F32: hipLaunchKernelGGL((xring_batch<MOBIUS_F32, MOBIUS_F32>), grid, blk, 0, st, sys_dev, active, a0); break;
-        case MOBIUS_F16: hipLaunchKernelGGL((xring_batch<MOBIUS_F16, MOBIUS_F32>), grid, blk, 0, st, sys_dev, active, a0); break;
-        default: return hipErrorInvalidValue;
-        }
-    } else {
-        return hipErrorInvalidValue;
+        break;
+    default: return hipErrorInvalidValue;
+    }
+#undef MOBIUS_PX
+    return hipGetLastError();
+}
+
+hipError_t launch_xring(int prec, int prec2, const VecSys *sys_dev, int nsys, int64_t max_n5,
+                        const int32_t *active, int n, hipStream_t st)
+{
+    const dim3 grid((unsigned)((max_n5 + BLAS_BLOCK - 1) / BLAS_BLOCK), (unsigned)nsys), blk(BLAS_BLOCK);
+    if (n < 1 || n > RING_MAX || prec2 != MOBIUS_F32) return hipErrorInvalidValue;
+    switch (prec) {
+    case MOBIUS_F32: hipLaunchKernelGGL((xring_batch<MOBIUS_F32, MOBIUS_F32>), grid, blk, 0, st, sys_dev, active, n); break;
+    case MOBIUS_F16: hipLaunchKernelGGL((xring_batch<MOBIUS_F16, MOBIUS_F32>), grid, blk, 0, st, sys_dev, active, n); break;
+    default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }

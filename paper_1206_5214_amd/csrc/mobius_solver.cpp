@@ -85,8 +85,8 @@ struct HopPattern {
 // H0A/H0B = D_pre x_hi in FP64; normal equations: D1Q = D_pre^+ q (no norm),
 // N64B/N64C = D_pre^+ of an FP64 field
 enum HopPid { HP_D0A, HP_D0B, HP_D1B, HP_D1C, HP_H0A, HP_H0B, HP_D1Q, HP_N64B, HP_N64C, NHOP };
-enum VecPid { VP_CONV_RH_R, VP_ACC, VP_RES, VP_HOPRED, VP_BLASRED, VP_NORM_B,
-              VP_NORM_EE, VP_NORM_EO, VP_CONV_B_RH, VP_XR_N, VP_PUPD_N, VP_RES_N, VP_DOT_B_XH,
+enum VecPid { VP_CONV_RH_R, VP_ACC, VP_RES, VP_HOPRED, VP_CGRED, VP_BLASRED, VP_NORM_B,
+              VP_NORM_EE, VP_NORM_EO, VP_CONV_B_RH, VP_XR_N, VP_RES_N, VP_DOT_B_XH,
               VP_TWO_XH, VP_PUPD_X, VP_XFLUSH, VP_RUPD, VP_NORM_Q, VP_NORM_S, VP_NORM_T64, VP_NORM_Q64,
               VP_PUPD_R, VP_XRING, VP_PUPD_RN, VP_R_N, NVEC };
 
@@ -111,7 +111,10 @@ struct Batch {
     hipStream_t st = nullptr;
     int64_t pstride = 0, max_n5 = 0, max_site_blocks = 0;
     // device state (in the first context's buffers)
-    double *part = nullptr;
+    double *part = nullptr;    // [nsys][pstride] partial sums of the hops' |out|^2
+    double *part_v = nullptr;  // the same for the vector kernels (read and written while part is read)
+    double *part2 = nullptr;   // [nsys][RED_PARTS] first level of a long sum of part or part_v
+    bool two_level = false;    // some system's sums are longer than RED_DIRECT: through part2
     CgScalars *sc = nullptr;
     double *hist = nullptr;         // [nsys][HIST_MAX][2] CG coefficients (kappa estimate)
     double *extra = nullptr;
@@ -195,11 +198,12 @@ struct Batch {
     HopArgs hop_args_for(const Group &g, const HopPattern &p) const;
     hipError_t hop(int pid);
     hipError_t launch_pattern(const HopPattern &p, int pid);
-    int norm_red() const { return fused_norm ? VP_HOPRED : VP_BLASRED; }
     hipError_t hop_group(const Group &g, int prec, int dag, int epi, int out_parity, Field in,
                          Field out, Field x, Field y, bool norm);
     hipError_t vec(int pid, int kind, int prec, int prec2, bool all = false);
-    hipError_t ring_vec(int pid, int kind, int a0, int a1);
+    hipError_t cg_update(int pid, int kind, int slot, int prev);
+    hipError_t xring(int n);
+    hipError_t first_level(int pid);     // partials -> part2 where the sums are long
     hipError_t reduce(int pid, double *out, int64_t stride, bool all = false);
     hipError_t m5inv_dag_all(int prec, Field in, Field out, bool only_active = false)
     {
@@ -210,7 +214,7 @@ struct Batch {
     hipError_t next_u(bool only_active);   // the solve of r the next step's A^+ starts from
     hipError_t psi_odd();                  // psi_o from the iterate (right form: I^-1 z)
     hipError_t body(int q, int k);       // iteration q of a chunk of k CG iterations
-    hipError_t rupd();                   // r -= alpha q (|r|^2), u = I^-+ r
+    hipError_t rupd(int slot);           // r -= alpha q (|r|^2), u = I^-+ r
     hipError_t body_normal(int q, int k);  // the same on the normal equations
     hipError_t reliable_update();        // x_hi += x, r = b - D x_hi (FP64), r_lo = r
     hipError_t finalize_group(const Group &g);
@@ -312,8 +316,11 @@ int Batch::setup(mobius_ctx *const *ctxs, int n, const void *const *src, void *c
 
     // device state in the first context
     mobius_ctx *c0 = groups[0].ctx;
-    CK(c0->partials.ensure((int64_t)nsys * pstride * (int64_t)sizeof(double)));
+    CK(c0->partials.ensure((int64_t)nsys * (2 * pstride + RED_PARTS) * (int64_t)sizeof(double)));
     part = static_cast<double *>(c0->partials.p);
+    part_v = part + (int64_t)nsys * pstride;
+    part2 = part_v + (int64_t)nsys * pstride;
+    two_level = pstride > RED_DIRECT;
     const int ng = n;
     size_t off = 0;
     auto carve = [&](size_t bytes) {
@@ -406,8 +413,19 @@ int Batch::setup(mobius_ctx *const *ctxs, int n, const void *const *src, void *c
             v.flag = j;
             v.Ls = g.ctx->g.Ls;
             v.coef = coef + (&g - groups.data());
-            v.partials = part + (int64_t)j * pstride;
+            v.partials = part_v + (int64_t)j * pstride;
             v.nparts = g.blas_blocks;
+            v.cg = &sc[j];
+            // beta and alpha come from the |out|^2 partials of the hops (or of the
+            // separate norm pass) -- in the normal equations beta from those of r
+            VecSys h = v;
+            h.partials = part + (int64_t)j * pstride;
+            h.nparts = fused_norm ? g.hop_blocks : g.blas_blocks;
+            auto reads = [&](VecSys &w, const VecSys &from) {
+                const bool two = from.nparts > RED_DIRECT;  // (by the system alone: a batch sums as its solo solves)
+                w.red = two ? part2 + (int64_t)j * RED_PARTS : from.partials;
+                w.nred = two ? RED_PARTS : from.nparts;
+            };
             VecSys t = v;
             t = v; t.a = F(F_RH); t.b = F(F_R);
             h_vec[(size_t)VP_CONV_RH_R * nsys + j] = t;
@@ -415,8 +433,9 @@ int Batch::setup(mobius_ctx *const *ctxs, int n, const void *const *src, void *c
             h_vec[(size_t)VP_ACC * nsys + j] = t;
             t = v; t.a = F(F_B); t.b = F(F_Q64); t.s1 = &extra[j * NEXTRA + X_MINUS1]; t.d = F(F_RH);
             h_vec[(size_t)VP_RES * nsys + j] = t;
-            t = v; t.nparts = g.hop_blocks;
+            t = h; t.nparts = g.hop_blocks;
             h_vec[(size_t)VP_HOPRED * nsys + j] = t;
+            h_vec[(size_t)VP_CGRED * nsys + j] = h;
             h_vec[(size_t)VP_BLASRED * nsys + j] = v;
             t = v; t.a = F(F_B);
             h_vec[(size_t)VP_NORM_B * nsys + j] = t;
@@ -426,36 +445,34 @@ int Batch::setup(mobius_ctx *const *ctxs, int n, const void *const *src, void *c
             h_vec[(size_t)VP_NORM_EO * nsys + j] = t;
             t = v; t.a = F(F_B); t.b = F(F_RH);
             h_vec[(size_t)VP_CONV_B_RH * nsys + j] = t;
-            t = v; t.a = F(F_X); t.b = F(F_P); t.c = F(F_R); t.d = F(F_S); t.s0 = &sc[j].alpha;
+            t = v; t.a = F(F_X); t.b = F(F_P); t.c = F(F_R); t.d = F(F_S); reads(t, h);
             h_vec[(size_t)VP_XR_N * nsys + j] = t;
-            t = v; t.a = F(F_R); t.b = F(F_P); t.d = F(F_P); t.s1 = &sc[j].beta;
-            h_vec[(size_t)VP_PUPD_N * nsys + j] = t;
             t = v; t.a = F(F_B); t.b = F(F_PE); t.s1 = &extra[j * NEXTRA + X_MINUS1]; t.d = F(F_RH);
             h_vec[(size_t)VP_RES_N * nsys + j] = t;
             t = v; t.a = F(F_B); t.b = F(F_XH);
             h_vec[(size_t)VP_DOT_B_XH * nsys + j] = t;
             t = v; t.a = F(F_XH); t.b = F(F_XH); t.d = F(F_RH);
             h_vec[(size_t)VP_TWO_XH * nsys + j] = t;
-            t = v; t.a = F(F_S); t.b = F(F_P); t.c = F(F_X); t.s0 = &sc[j].alpha; t.s1 = &sc[j].beta;
+            t = v; t.a = F(F_S); t.b = F(F_P); t.c = F(F_X); t.s0 = &sc[j].alpha; reads(t, h);
             h_vec[(size_t)VP_PUPD_X * nsys + j] = t;
             t = v; t.a = F(F_P); t.c = F(F_X); t.s0 = &sc[j].alpha;
             h_vec[(size_t)VP_XFLUSH * nsys + j] = t;
             t = v; t.a = F(F_S); t.b = g.pring + r * g.fb[F_P]; t.sstride = g.fb[F_P] * g.nrhs;
-            t.s1 = &sc[j].beta;
+            reads(t, h);
             h_vec[(size_t)VP_PUPD_R * nsys + j] = t;
             t = v; t.b = g.pring + r * g.fb[F_P]; t.sstride = g.fb[F_P] * g.nrhs; t.c = F(F_X);
             t.s0 = &sc[j].aring[0];
             h_vec[(size_t)VP_XRING * nsys + j] = t;
             t = v; t.a = F(F_R); t.b = g.pring + r * g.fb[F_P]; t.sstride = g.fb[F_P] * g.nrhs;
-            t.s1 = &sc[j].beta;
+            reads(t, v);
             h_vec[(size_t)VP_PUPD_RN * nsys + j] = t;
-            t = v; t.c = F(F_R); t.d = F(F_S); t.s0 = &sc[j].alpha;
+            t = v; t.c = F(F_R); t.d = F(F_S); reads(t, h);
             h_vec[(size_t)VP_R_N * nsys + j] = t;
-            t = v; t.a = F(F_R); t.b = F(F_Q); t.c = F(F_U); t.s0 = &sc[j].alpha; t.nparts = g.hop_blocks;
+            t = v; t.a = F(F_R); t.b = F(F_Q); t.c = F(F_U); t.nparts = g.hop_blocks; reads(t, h);
             h_vec[(size_t)VP_RUPD * nsys + j] = t;
-            t = v; t.a = F(F_Q);
+            t = h; t.a = F(F_Q);
             h_vec[(size_t)VP_NORM_Q * nsys + j] = t;
-            t = v; t.a = F(F_S);
+            t = h; t.a = F(F_S);
             h_vec[(size_t)VP_NORM_S * nsys + j] = t;
             t = v; t.a = F(F_T64);
             h_vec[(size_t)VP_NORM_T64 * nsys + j] = t;
@@ -588,23 +605,12 @@ hipError_t Batch::vec(int pid, int kind, int prec, int prec2, bool all)
 {
     const double fb = sum_fb(prec, true), fb2 = sum_fb(prec2, true), n5 = sum_n5(true);
     switch (kind) {
-    case VEC_CG_XR:
-        if (pid == VP_R_N) {  // r -= alpha s only
-            abytes += 3 * fb;
-            aflops += 96 * n5;
-        } else {
-            abytes += 2 * fb2 + 4 * fb;
-            aflops += 144 * n5;
-        }
-        break;
     case VEC_AXPBY: abytes += 3 * fb; aflops += 48 * n5; break;
     case VEC_AXPBY_NORM: abytes += 3 * fb; aflops += 96 * n5; break;
     case VEC_NORM2: abytes += fb; aflops += 48 * n5; break;
     case VEC_CONVERT: abytes += fb + fb2; break;
     case VEC_ACCUMULATE: abytes += 2 * fb + 2 * sum_fb(MOBIUS_F64, true); aflops += 24 * n5; break;
     case VEC_DOT: abytes += 2 * fb; aflops += 48 * n5; break;
-    // x (prec2) += alpha p, p = s + beta p: reads s, p, x; writes p, x
-    case VEC_PUPD_X: abytes += 3 * fb + 2 * fb2; aflops += 96 * n5; break;
     // x (prec2) += alpha p: reads p, x; writes x
     case VEC_XFLUSH: abytes += fb + 2 * fb2; aflops += 48 * n5; break;
     }
@@ -613,22 +619,45 @@ hipError_t Batch::vec(int pid, int kind, int prec, int prec2, bool all)
                             all ? nullptr : active, st);
 }
 
-// p[slot] = s + beta p[prev] (kind VEC_PUPD_RING: reads s and p[prev], writes
-// p[slot]) or x += sum_{i < a0} alpha_i p[i] (VEC_XRING: reads a0 directions
-// and x, writes x)
-hipError_t Batch::ring_vec(int pid, int kind, int a0, int a1)
+// The vector updates that compute beta or alpha: p[slot] = s + beta p[prev]
+// (VEC_PUPD_RING: reads s and p[prev], writes p[slot]), with x += alpha p_old
+// (VEC_PUPD_X: x read and written too), x += alpha p and r -= alpha s
+// (VEC_CG_XR; VP_R_N: r only)
+hipError_t Batch::cg_update(int pid, int kind, int slot, int prev)
 {
     const double fb = sum_fb(lo, true), fb2 = sum_fb(px, true), n5 = sum_n5(true);
     if (kind == VEC_PUPD_RING) {
         abytes += 3 * fb;
         aflops += 48 * n5;
+    } else if (kind == VEC_PUPD_X) {
+        abytes += 3 * fb + 2 * fb2;
+        aflops += 96 * n5;
+    } else if (pid == VP_R_N) {
+        abytes += 3 * fb;
+        aflops += 96 * n5;
     } else {
-        abytes += a0 * fb + 2 * fb2;
-        aflops += 48.0 * a0 * n5;
+        abytes += 2 * fb2 + 4 * fb;
+        aflops += 144 * n5;
     }
     if (count_only) return hipSuccess;
-    return launch_ring_batch(kind, lo, px, vec_tab + (size_t)pid * nsys, nsys, max_n5, active, a0, a1,
-                             st);
+    return launch_cg_update(kind, lo, px, vec_tab + (size_t)pid * nsys, nsys, max_n5, active, restart, slot,
+                            prev, st);
+}
+
+// x += sum_{i < n} alpha_i p[i]: reads n directions and x, writes x
+hipError_t Batch::xring(int n)
+{
+    const double fb = sum_fb(lo, true), fb2 = sum_fb(px, true);
+    abytes += n * fb + 2 * fb2;
+    aflops += 48.0 * n * sum_n5(true);
+    if (count_only) return hipSuccess;
+    return launch_xring(lo, px, vec_tab + (size_t)VP_XRING * nsys, nsys, max_n5, active, n, st);
+}
+
+hipError_t Batch::first_level(int pid)
+{
+    if (!two_level || count_only) return hipSuccess;
+    return launch_reduce_parts(vec_tab + (size_t)pid * nsys, nsys, active, part2, st);
 }
 
 hipError_t Batch::reduce(int pid, double *out, int64_t stride, bool all)
@@ -695,27 +724,25 @@ hipError_t Batch::body(int q, int k)
     dirac += 4;
     if ((e = hop(HP_D1B)) != hipSuccess) return e;
     if ((e = hop(HP_D1C)) != hipSuccess) return e;
-    if ((e = reduce(norm_red(), &sc[0].gamma_new, SC_STRIDE)) != hipSuccess) return e;
-    if (!count_only && (e = launch_cg_scalar_batch(sc, nsys, 1, active, restart, st)) != hipSuccess) return e;
+    if ((e = first_level(VP_CGRED)) != hipSuccess) return e;
     const int slot = ring > 1 ? q : -1;
     if (ring > 1) {
         cur_slot = slot;
         for (Group &g : groups) g.f[F_P] = g.pring + (int64_t)slot * g.fb[F_P] * g.nrhs;
-        if ((e = ring_vec(VP_PUPD_R, VEC_PUPD_RING, slot, q == 0 ? ring - 1 : q - 1)) != hipSuccess)
+        if ((e = cg_update(VP_PUPD_R, VEC_PUPD_RING, slot, q == 0 ? ring - 1 : q - 1)) != hipSuccess)
             return e;
-    } else if ((e = vec(VP_PUPD_X, VEC_PUPD_X, lo, px)) != hipSuccess) {
+    } else if ((e = cg_update(VP_PUPD_X, VEC_PUPD_X, -1, -1)) != hipSuccess) {
         return e;
     }
     if (form == FORM_RIGHT && (e = m5inv_all(lo, 0, F_P, F_U)) != hipSuccess) return e;  // v = I^-1 p
     if ((e = hop(HP_D0A)) != hipSuccess) return e;
     if ((e = hop(HP_D0B)) != hipSuccess) return e;
-    if ((e = reduce(norm_red(), &sc[0].qq, SC_STRIDE)) != hipSuccess) return e;
-    if (!count_only && (e = launch_cg_scalar_batch(sc, nsys, 0, active, restart, st, slot)) != hipSuccess)
-        return e;
-    if ((e = rupd()) != hipSuccess) return e;
+    if ((e = first_level(VP_CGRED)) != hipSuccess) return e;
+    if ((e = rupd(slot)) != hipSuccess) return e;
+    if (q < k - 1) return hipSuccess;
+    // the host looks at |r|^2 between chunks only
     if ((e = reduce(VP_RUPD, &sc[0].rr, SC_STRIDE)) != hipSuccess) return e;
-    if (ring > 1 && q == k - 1) return ring_vec(VP_XRING, VEC_XRING, k, 0);
-    return hipSuccess;
+    return ring > 1 ? xring(k) : hipSuccess;
 }
 
 // Normal equations, p = r + beta p;  q = D p (|q|^2 -> alpha);  s = D^+ q;
@@ -725,32 +752,30 @@ hipError_t Batch::body_normal(int q, int k)
 {
     hipError_t e;
     dirac += 4;
-    if (!count_only && (e = launch_cg_scalar_batch(sc, nsys, 1, active, restart, st)) != hipSuccess) return e;
     const int slot = ring > 1 ? q : -1;
     if (ring > 1) {
         cur_slot = slot;
         for (Group &g : groups) g.f[F_P] = g.pring + (int64_t)slot * g.fb[F_P] * g.nrhs;
-        if ((e = ring_vec(VP_PUPD_RN, VEC_PUPD_RING, slot, q == 0 ? ring - 1 : q - 1)) != hipSuccess)
-            return e;
-    } else if ((e = vec(VP_PUPD_N, VEC_AXPBY, lo, lo)) != hipSuccess) {
-        return e;
     }
+    // beta from the |r|^2 partials that the last r update, the reliable update
+    // or the source's norm left
+    if ((e = first_level(VP_BLASRED)) != hipSuccess) return e;
+    if ((e = cg_update(VP_PUPD_RN, VEC_PUPD_RING, ring > 1 ? q : 0,
+                       ring > 1 ? (q == 0 ? ring - 1 : q - 1) : 0)) != hipSuccess)
+        return e;
     if ((e = hop(HP_D0A)) != hipSuccess) return e;
     if ((e = hop(HP_D0B)) != hipSuccess) return e;
-    if ((e = reduce(norm_red(), &sc[0].qq, SC_STRIDE)) != hipSuccess) return e;
-    if (!count_only && (e = launch_cg_scalar_batch(sc, nsys, 0, active, restart, st, slot)) != hipSuccess)
-        return e;
     if ((e = m5inv_dag_all(lo, F_Q, F_U)) != hipSuccess) return e;
     if ((e = hop(HP_D1B)) != hipSuccess) return e;
     if ((e = hop(HP_D1Q)) != hipSuccess) return e;
-    if ((e = vec(ring > 1 ? VP_R_N : VP_XR_N, VEC_CG_XR, lo, px)) != hipSuccess) return e;
+    if ((e = first_level(VP_CGRED)) != hipSuccess) return e;
+    if ((e = cg_update(ring > 1 ? VP_R_N : VP_XR_N, VEC_CG_XR, slot, -1)) != hipSuccess) return e;
+    if (q < k - 1) return hipSuccess;
     if ((e = reduce(VP_BLASRED, &sc[0].rr, SC_STRIDE)) != hipSuccess) return e;
-    if ((e = reduce(VP_BLASRED, &sc[0].gamma_new, SC_STRIDE)) != hipSuccess) return e;
-    if (ring > 1 && q == k - 1) return ring_vec(VP_XRING, VEC_XRING, k, 0);
-    return hipSuccess;
+    return ring > 1 ? xring(k) : hipSuccess;
 }
 
-hipError_t Batch::rupd()
+hipError_t Batch::rupd(int slot)
 {
     const double fb = sum_fb(lo, true), n5 = sum_n5(true);
     const int mode = rupd_mode();
@@ -758,7 +783,7 @@ hipError_t Batch::rupd()
     aflops += (48 + (mode == 2 ? 0 : 96) + (mode == 3 ? 48 : 0) + 48) * n5;
     if (count_only) return hipSuccess;
     return launch_rupd_m5inv_batch(lo, vec_tab + (size_t)VP_RUPD * nsys, nsys, max_site_blocks, active,
-                                   mode, st);
+                                   restart, slot, mode, st);
 }
 
 hipError_t Batch::reliable_update()
@@ -767,7 +792,7 @@ hipError_t Batch::reliable_update()
     dirac += normal ? 4 : 2;
     if (!normal && ring == 1) {  // the last alpha p of the iteration, then no pending update
         if ((e = vec(VP_XFLUSH, VEC_XFLUSH, lo, px)) != hipSuccess) return e;
-        if ((e = launch_cg_scalar_batch(sc, nsys, 2, active, restart, st)) != hipSuccess) return e;
+        if ((e = launch_clear_alpha(sc, nsys, active, st)) != hipSuccess) return e;
     }
     if ((e = vec(VP_ACC, VEC_ACCUMULATE, px, MOBIUS_F64)) != hipSuccess) return e;
     if (form == FORM_RIGHT && (e = m5inv_all(MOBIUS_F64, 0, F_XH, F_U64, true)) != hipSuccess) return e;
@@ -779,7 +804,6 @@ hipError_t Batch::reliable_update()
         if ((e = hop(HP_N64C)) != hipSuccess) return e;
         if ((e = vec(VP_RES_N, VEC_AXPBY_NORM, MOBIUS_F64, MOBIUS_F64)) != hipSuccess) return e;
         if ((e = reduce(VP_BLASRED, &extra[X_HR], NEXTRA)) != hipSuccess) return e;
-        if ((e = reduce(VP_BLASRED, &sc[0].gamma_new, SC_STRIDE)) != hipSuccess) return e;
     } else {
         if ((e = vec(VP_RES, VEC_AXPBY_NORM, MOBIUS_F64, MOBIUS_F64)) != hipSuccess) return e;
         if ((e = reduce(VP_BLASRED, &extra[X_HR], NEXTRA)) != hipSuccess) return e;
@@ -1028,18 +1052,18 @@ int run(mobius_ctx *const *ctxs, int ngroups, const void *const *src, void *cons
         // beta = 0 times p must be 0 (every slot of the ring)
         CK(launch_zero(g.pring, g.fb[F_P] * g.nrhs * B.ring, st));
     }
-    CK(B.vec(VP_NORM_B, VEC_NORM2, MOBIUS_F64, MOBIUS_F64));
-    CK(B.reduce(VP_BLASRED, &B.extra[X_BNORM2], NEXTRA, true));
-    if (B.normal) CK(B.reduce(VP_BLASRED, &B.sc[0].gamma_new, SC_STRIDE, true));
     CK(B.vec(VP_NORM_EE, VEC_NORM2, MOBIUS_F64, MOBIUS_F64));
     CK(B.reduce(VP_BLASRED, &B.extra[X_ETA_E2], NEXTRA, true));
     CK(B.vec(VP_NORM_EO, VEC_NORM2, MOBIUS_F64, MOBIUS_F64));
     CK(B.reduce(VP_BLASRED, &B.extra[X_ETA_O2], NEXTRA, true));
+    // (last: the normal equations' first direction reads these partials)
+    CK(B.vec(VP_NORM_B, VEC_NORM2, MOBIUS_F64, MOBIUS_F64));
+    CK(B.reduce(VP_BLASRED, &B.extra[X_BNORM2], NEXTRA, true));
     CK(B.vec(VP_CONV_B_RH, VEC_CONVERT, MOBIUS_F64, MOBIUS_F64));
     CK(B.vec(VP_CONV_RH_R, VEC_CONVERT, MOBIUS_F64, B.lo));
     if (!B.normal) {  // the iteration starts from the solve of r (left: u = I^-+ r) and no pending x update
         CK(B.next_u(false));
-        CK(launch_cg_scalar_batch(B.sc, nsys, 2, nullptr, nullptr, st));
+        CK(launch_clear_alpha(B.sc, nsys, nullptr, st));
     }
     std::vector<double> bnorm2, eta_e2, eta_o2;
     if (int rc = B.fetch(bnorm2, X_BNORM2)) return rc;
