@@ -131,11 +131,13 @@ struct HopParams {
     int64_t Vh, N5;
     int64_t fstride, pstride, nblocks;
     int Ls, spw, nrhs;
+    int split;              // workgroups that share the right-hand sides of one site block (1: one
+                            // takes them all, nrhs: one each)
     int remap;              // XCD-contiguous block order
     int stage_links;        // copy the block's links to LDS first
     int m5_off;             // byte offset in dynamic LDS of the I^-1 epilogue's buffer: 0 (it
                             // reuses the staged links' space once the direction loop is done)
-                            // or past the links (nrhs > 1: the links serve every system)
+                            // or past the links (split < nrhs: the links serve several systems)
     int nt;                 // non-temporal loads of the links
     int pf;                 // prefetch depth of the direction loop (0, 1, 2); 3: FP16 matrix-core
                             // colour multiply (requires stage_links and Ls % 4 == 0)

@@ -58,8 +58,10 @@ __device__ constexpr int HOP_DIR[8] = {7, 4, 0, 5, 1, 6, 2, 3};
 // are loaded in segment d; 1: the neighbour spinor of direction d+1 is loaded
 // while direction d computes; 2: its link as well.  The eight neighbour
 // indices are always loaded up front.
+// The block takes the right-hand sides r0, r0 + rstep, ... (one staging of the
+// links for all of them).
 template <int P, bool DAG, int EPI, int PF>
-__device__ __forceinline__ void hop_block(const HopParams &hp, int64_t lb)
+__device__ __forceinline__ void hop_block(const HopParams &hp, int64_t lb, int r0, int rstep)
 {
     using S = Spin<P>;
     using T = typename S::T;
@@ -75,7 +77,7 @@ __device__ __forceinline__ void hop_block(const HopParams &hp, int64_t lb)
 
     if (hp.active) {  // a system group whose systems have all converged: nothing to stage
         bool any = false;
-        for (int r = 0; r < hp.nrhs; ++r) any = any || hp.active[r];
+        for (int r = r0; r < hp.nrhs; r += rstep) any = any || hp.active[r];
         if (!any) return;
     }
 
@@ -136,7 +138,7 @@ __device__ __forceinline__ void hop_block(const HopParams &hp, int64_t lb)
 
     if (hp.stage_links) __syncthreads();
 
-    for (int r = 0; r < hp.nrhs; ++r) {
+    for (int r = r0; r < hp.nrhs; r += rstep) {
     if (hp.active && !hp.active[r]) continue;
     const Buf bin(hp.in + r * hp.fstride, fbytes), bout(hp.out + r * hp.fstride, fbytes);
     const char *xr = hp.x ? hp.x + r * hp.fstride : nullptr;
@@ -364,12 +366,13 @@ template <int P, bool DAG, int EPI, int PF>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(P == MOBIUS_F16 && PF == 3 ? 4 : 1)))
 void hop_kernel(HopParams hp)
 {
-    hop_block<P, DAG, EPI, PF>(hp, logical_block(hp.remap));
+    hop_block<P, DAG, EPI, PF>(hp, logical_block(hp.remap), blockIdx.y, gridDim.y);
 }
 
 // Persistent launch over a batch of lattices of uneven size: a fixed grid
 // walks the concatenated block lists of all groups (group j owns work items
-// [prefix[j], prefix[j+1])); every workgroup exits after its last item.
+// [prefix[j], prefix[j+1]), its site blocks once per split right-hand side); every
+// workgroup exits after its last item.
 template <int P, bool DAG, int EPI, int PF>
 __global__ __launch_bounds__(BLOCK) void hop_batch_kernel(const HopParams *groups, int ngroups,
                                                           const int64_t *prefix)
@@ -385,7 +388,9 @@ __global__ __launch_bounds__(BLOCK) void hop_batch_kernel(const HopParams *group
     const int64_t q = n / NUM_XCD, rem = n % NUM_XCD, x = b % NUM_XCD;
     for (int64_t w = x * q + (x < rem ? x : rem) + b / NUM_XCD; w < total; w += n) {
         while (w >= prefix[j + 1]) ++j;
-        hop_block<P, DAG, EPI, PF>(groups[j], w - prefix[j]);
+        const HopParams &hp = groups[j];
+        const int64_t i = w - prefix[j], r0 = i / hp.nblocks;
+        hop_block<P, DAG, EPI, PF>(hp, i - r0 * hp.nblocks, (int)r0, hp.split);
         __syncthreads();  // LDS of this item is dead before the next item stages
     }
 }
@@ -405,12 +410,13 @@ void hop_launch(const HopParams &hp0, hipStream_t st)
 {
     HopParams hp = hp0;
     const size_t links = hp.stage_links ? link_lds_bytes<P>(hp.spw, hp.pf == 3) : 0;
+    const int split = std::min(hp.split, MAX_GRID_Y);
     size_t dyn = links;
     if constexpr ((EPI & EPI_M5INV) != 0) {
-        hp.m5_off = hp.nrhs > 1 ? (int)links : 0;
+        hp.m5_off = split < hp.nrhs ? (int)links : 0;
         dyn = std::max(links, (size_t)hp.m5_off + sizeof(M5Lds<typename Spin<P>::T>));
     }
-    const dim3 grid((unsigned)hp.nblocks), blk(BLOCK);
+    const dim3 grid((unsigned)hp.nblocks, (unsigned)split), blk(BLOCK);
     switch (hp.pf) {
     case 0: hipLaunchKernelGGL((hop_kernel<P, DAG, EPI, 0>), grid, blk, dyn, st, hp); break;
     case 1: hipLaunchKernelGGL((hop_kernel<P, DAG, EPI, 1>), grid, blk, dyn, st, hp); break;
@@ -1494,6 +1500,14 @@ HopParams make_hop_params(const Geometry &g, const OpCoeffs &c, const void *link
     hp.Ls = g.Ls;
     hp.spw = sites_per_wave(g.Ls);
     hp.nrhs = a.nrhs;
+    // Right-hand sides run side by side, each workgroup staging its links for one
+    // of them, where the links of a parity fit half the 256 MB Infinity Cache;
+    // beyond, a workgroup takes all of them in turn on links staged once.  D_pre,
+    // shared against split: 8^3 x 16, Ls = 8, 12 right-hand sides (128 site
+    // blocks on 256 CUs) FP64 248 / 144 us, FP16 119 / 45 us; 16^3 x 32, Ls = 16,
+    // 12: FP64 4592 / 4241 us, FP16 1266 / 1241 us; 24^3 x 64, Ls = 12, 3: FP64
+    // 5600 / 5801 us, FP16 1610 / 1665 us.
+    hp.split = 8 * g.Vh * link_record_bytes(a.prec) <= (int64_t)128 << 20 ? a.nrhs : 1;
     const HopTuning &t = a.tune ? *a.tune : hop_tuning();
     hp.remap = t.xcd_remap;
     hp.stage_links = t.stage_links && hop_link_lds_bytes(a.prec, g.Ls, false) <= 64 * 1024;

@@ -365,7 +365,7 @@ int Batch::setup(mobius_ctx *const *ctxs, int n, const void *const *src, void *c
                                                 hop_args_for(g, hp[pid]));
             h_hop[(size_t)pid * ng + j] = h;
             h_prefix[(size_t)pid * (ng + 1) + j] = acc;
-            acc += h.nblocks;
+            acc += h.nblocks * h.split;
             if (h.stage_links) hop_lds[pid] = 1;  // sized below, once the loop variant is known
         }
         h_prefix[(size_t)pid * (ng + 1) + ng] = acc;
@@ -393,9 +393,9 @@ int Batch::setup(mobius_ctx *const *ctxs, int n, const void *const *src, void *c
         for (int j = 0; j < ng; ++j) {
             if (h_hop[(size_t)pid * ng + j].stage_links)
                 hop_lds[pid] = std::max(hop_lds[pid], hop_link_lds_bytes(hp[pid].prec, groups[j].ctx->g.Ls, rows));
-            multi = multi || h_hop[(size_t)pid * ng + j].nrhs > 1;
+            multi = multi || h_hop[(size_t)pid * ng + j].split < h_hop[(size_t)pid * ng + j].nrhs;
         }
-        // the I^-1 epilogue's buffer: over the links (one system per group)
+        // the I^-1 epilogue's buffer: over the links (one system per workgroup)
         // or past them
         if (hp[pid].epi & EPI_M5INV) {
             const size_t off = multi ? hop_lds[pid] : 0;
