@@ -982,6 +982,7 @@ extern "C" int mobius_set_tuning(mobius_ctx *ctx, const mobius_tune_result *t)
     h.xcd_remap = t->xcd_remap;
     h.nt_links = t->nt_links;
     h.mfma = t->mfma;
+    h.split_dirs = 0;  // the loop variant asked for
     ctx->tune[t->prec] = h;
     ctx->tuned_us[t->prec] = 0;
     return MOBIUS_OK;

@@ -12,7 +12,7 @@
 namespace mobius {
 namespace {
 
-constexpr int WAVES = 4;
+constexpr int WAVES = HOP_WAVES;
 constexpr int BLOCK = 64 * WAVES;
 
 // ---------------------------------------------------------------------------
@@ -717,15 +717,28 @@ __device__ __forceinline__ void half_spinor_h2(const half2v o[12], const half2v 
     }
 }
 
-// The colour multiply on the matrix cores (operand layout at LinkRows),
-// then the same FP32 reconstruction as link_accumulate_h2.
+// acc += s (1 + sigma g_mu) (M h) from the colour products w = M h of the two
+// spin rows (FP16 loops)
 template <int MU, int SIGMA>
-__device__ __forceinline__ void link_accumulate_mfma(const half2v h[6], float s, const LinkRows &x,
-                                                     cx<float> acc[12])
+__device__ __forceinline__ void spin_accumulate_f16(const cx<float> w[2][3], float s, cx<float> acc[12])
+{
+    const float sg = (float)SIGMA * s;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        acc[a] = acc[a] + s * w[0][a];
+        acc[3 + a] = acc[3 + a] + s * w[1][a];
+        cx<float> o0, o1;
+        Adag_apply<float, MU>(w[0][a], w[1][a], o0, o1);
+        acc[6 + a] = acc[6 + a] + sg * o0;
+        acc[9 + a] = acc[9 + a] + sg * o1;
+    }
+}
+
+// The colour multiply on the matrix cores (operand layout at LinkRows)
+__device__ __forceinline__ void link_mult_mfma(const half2v h[6], const LinkRows &x, cx<float> w[2][3])
 {
     const float4v z = {0.f, 0.f, 0.f, 0.f};
     const _Float16 h0 = (_Float16)0;
-    cx<float> w[2][3];
 #pragma unroll
     for (int sp = 0; sp < 2; ++sp) {
         const half2v *hs = h + 3 * sp;
@@ -739,87 +752,73 @@ __device__ __forceinline__ void link_accumulate_mfma(const half2v h[6], float s,
         w[sp][1] = {lo[2], lo[3]};
         w[sp][2] = {hi[0], hi[1]};
     }
-    const float sg = (float)SIGMA * s;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        acc[a] = acc[a] + s * w[0][a];
-        acc[3 + a] = acc[3 + a] + s * w[1][a];
-        cx<float> o0, o1;
-        Adag_apply<float, MU>(w[0][a], w[1][a], o0, o1);
-        acc[6 + a] = acc[6 + a] + sg * o0;
-        acc[9 + a] = acc[9 + a] + sg * o1;
-    }
 }
 
-template <int MU, int SIGMA>
-__device__ __forceinline__ void link_accumulate_h2(const half2v h[6], float s, const LinkH2 &x,
-                                                   cx<float> acc[12])
+// The same with packed dot products
+__device__ __forceinline__ void link_mult_h2(const half2v h[6], const LinkH2 &x, cx<float> w[2][3])
 {
-    const float sg = (float)SIGMA * s;
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        float w0r = dot2_0(x.pr[a * 3], h[0]), w0i = dot2_0(x.pi[a * 3], h[0]);
-        float w1r = dot2_0(x.pr[a * 3], h[3]), w1i = dot2_0(x.pi[a * 3], h[3]);
+    for (int a = 0; a < 3; ++a)
 #pragma unroll
-        for (int b = 1; b < 3; ++b) {
-            w0r = dot2(x.pr[a * 3 + b], h[b], w0r);
-            w0i = dot2(x.pi[a * 3 + b], h[b], w0i);
-            w1r = dot2(x.pr[a * 3 + b], h[3 + b], w1r);
-            w1i = dot2(x.pi[a * 3 + b], h[3 + b], w1i);
+        for (int sp = 0; sp < 2; ++sp) {
+            float wr = dot2_0(x.pr[a * 3], h[3 * sp]), wi = dot2_0(x.pi[a * 3], h[3 * sp]);
+#pragma unroll
+            for (int b = 1; b < 3; ++b) {
+                wr = dot2(x.pr[a * 3 + b], h[3 * sp + b], wr);
+                wi = dot2(x.pi[a * 3 + b], h[3 * sp + b], wi);
+            }
+            w[sp][a] = {wr, wi};
         }
-        const cx<float> w0 = {w0r, w0i}, w1 = {w1r, w1i};
-        acc[a] = acc[a] + s * w0;
-        acc[3 + a] = acc[3 + a] + s * w1;
-        cx<float> o0, o1;
-        Adag_apply<float, MU>(w0, w1, o0, o1);
-        acc[6 + a] = acc[6 + a] + sg * o0;
-        acc[9 + a] = acc[9 + a] + sg * o1;
-    }
 }
 
-// Colour multiply and reconstruction of one direction: acc += (1 + sigma g_mu) M h
-// given the half spinor h = (h0; h1) = u + sigma A_mu l, with M = U (forward)
-// or U^+ (backward).  u: the link as stored (element a*3+b of U_mu(x) or of
-// U_mu(x-mu), whose adjoint the backward term applies).
-template <typename T, int MU, bool FWD, int SIGMA>
-__device__ __forceinline__ void link_accumulate(const cx<T> h0[3], const cx<T> h1[3],
-                                                const cx<T> u[9], cx<T> acc[12])
+// Colour multiply of one direction, w = M h for the half spinor h = (h0; h1) =
+// u + sigma A_mu l, with M = U (forward) or U^+ (backward).  u: the link as
+// stored (element a*3+b of U_mu(x) or of U_mu(x-mu), whose adjoint the backward
+// term applies).
+template <typename T, bool FWD>
+__device__ __forceinline__ void link_mult(const cx<T> h0[3], const cx<T> h1[3], const cx<T> u[9],
+                                          cx<T> w[2][3])
 {
-    const T sg = (T)SIGMA;
-    cx<T> w0[3], w1[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        w0[a] = {0, 0};
-        w1[a] = {0, 0};
+        w[0][a] = {0, 0};
+        w[1][a] = {0, 0};
     }
 #pragma unroll
     for (int a = 0; a < 3; ++a)
 #pragma unroll
         for (int b = 0; b < 3; ++b) {
             if constexpr (FWD) {
-                w0[a] = cmadd(w0[a], u[a * 3 + b], h0[b]);
-                w1[a] = cmadd(w1[a], u[a * 3 + b], h1[b]);
+                w[0][a] = cmadd(w[0][a], u[a * 3 + b], h0[b]);
+                w[1][a] = cmadd(w[1][a], u[a * 3 + b], h1[b]);
             } else {  // (U^+)_{ab} = conj(U_ba)
-                w0[a] = cjmadd(w0[a], u[b * 3 + a], h0[b]);
-                w1[a] = cjmadd(w1[a], u[b * 3 + a], h1[b]);
+                w[0][a] = cjmadd(w[0][a], u[b * 3 + a], h0[b]);
+                w[1][a] = cjmadd(w[1][a], u[b * 3 + a], h1[b]);
             }
         }
+}
+
+// Reconstruction: acc += (1 + sigma g_mu) w
+template <typename T, int MU, int SIGMA>
+__device__ __forceinline__ void spin_accumulate(const cx<T> w[2][3], cx<T> acc[12])
+{
+    const T sg = (T)SIGMA;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        acc[a] = acc[a] + w0[a];
-        acc[3 + a] = acc[3 + a] + w1[a];
+        acc[a] = acc[a] + w[0][a];
+        acc[3 + a] = acc[3 + a] + w[1][a];
         cx<T> o0, o1;
-        Adag_apply<T, MU>(w0[a], w1[a], o0, o1);
+        Adag_apply<T, MU>(w[0][a], w[1][a], o0, o1);
         acc[6 + a] = acc[6 + a] + sg * o0;
         acc[9 + a] = acc[9 + a] + sg * o1;
     }
 }
 
-// One direction from a full (already b5/c5-mixed) spinor chi.
+// Colour products of one direction from a full (already b5/c5-mixed) spinor chi
 template <int P, int MU, bool FWD, int SIGMA>
-__device__ __forceinline__ void hop_dir(const cx<typename Spin<P>::T> chi[12],
-                                        const cx<typename Spin<P>::T> u[9],
-                                        cx<typename Spin<P>::T> acc[12])
+__device__ __forceinline__ void hop_dir_w(const cx<typename Spin<P>::T> chi[12],
+                                          const cx<typename Spin<P>::T> u[9],
+                                          cx<typename Spin<P>::T> w[2][3])
 {
     using T = typename Spin<P>::T;
     const T sg = (T)SIGMA;
@@ -831,7 +830,18 @@ __device__ __forceinline__ void hop_dir(const cx<typename Spin<P>::T> chi[12],
         h0[a] = chi[a] + sg * o0;
         h1[a] = chi[3 + a] + sg * o1;
     }
-    link_accumulate<T, MU, FWD, SIGMA>(h0, h1, u, acc);
+    link_mult<T, FWD>(h0, h1, u, w);
+}
+
+// One direction: acc += (1 + sigma g_mu) M chi
+template <int P, int MU, bool FWD, int SIGMA>
+__device__ __forceinline__ void hop_dir(const cx<typename Spin<P>::T> chi[12],
+                                        const cx<typename Spin<P>::T> u[9],
+                                        cx<typename Spin<P>::T> acc[12])
+{
+    cx<typename Spin<P>::T> w[2][3];
+    hop_dir_w<P, MU, FWD, SIGMA>(chi, u, w);
+    spin_accumulate<typename Spin<P>::T, MU, SIGMA>(w, acc);
 }
 
 // ---------------------------------------------------------------------------
@@ -876,6 +886,37 @@ struct SiteMap {
     int lm, lp;  // lanes holding s-1 and s+1 of the same site (cyclic)
 };
 
+// Half spinor hh of one direction from the stored words, to be multiplied by the
+// returned scale.  MIX: wa, wu and wl are this lane's weights of its own slice
+// and of the P+ and P- halves of slices s-1 and s+1 (site norms not included).
+template <int MU, int SIGMA, bool MIX>
+__device__ __forceinline__ float half_spinor_f16(const RawH &o, float wa, float wu, float wl,
+                                                 const SiteMap &m, half2v hh[6])
+{
+    half2v um[6], lp[6];
+    float al, bu = 0.f, bl = 0.f;
+    if constexpr (MIX) {
+#pragma unroll
+        for (int c = 0; c < 6; ++c) {
+            um[c] = shfl_h2(o.c[c], m.lm);
+            lp[c] = shfl_h2(o.c[6 + c], m.lp);
+        }
+        al = wa * o.n;
+        bu = wu * __shfl(o.n, m.lm, 64);
+        bl = wl * __shfl(o.n, m.lp, 64);
+    } else {
+        al = o.n;
+    }
+    // weights divided by the largest of them (the binary16 step keeps every term
+    // O(1)); the scale is restored in FP32
+    const float sc = fmaxf(fabsf(al), fmaxf(fabsf(bu), fabsf(bl)));
+    // (hardware reciprocal: its last-bit error scales both the binary16 terms
+    // and their restoration, so it cancels)
+    const float inv = sc > 0.f ? __builtin_amdgcn_rcpf(sc) : 0.f;
+    half_spinor_h2<MU, SIGMA, MIX>(o.c, um, lp, splat_h2(al * inv), splat_h2(bu * inv), splat_h2(bl * inv), hh);
+    return sc;
+}
+
 // Workgroups are dispatched round-robin over the 8 XCDs (block b runs on XCD
 // b mod 8), each with its own L2.  With remap on, the blocks an XCD receives
 // cover one contiguous range of sites, so the neighbours a block reads were
@@ -892,14 +933,15 @@ __device__ __forceinline__ int64_t logical_block(int remap)
     return x * q + (x < r ? x : r) + c;
 }
 
-__device__ __forceinline__ SiteMap site_map_lb(int Ls, int spw, int64_t Vh, int64_t lb)
+// the map of a wavefront whose sites start at packed site `first`
+__device__ __forceinline__ SiteMap site_map_first(int Ls, int spw, int64_t Vh, int64_t first)
 {
     SiteMap m;
     m.lane = threadIdx.x & 63;
     m.wave = threadIdx.x >> 6;
     m.g = m.lane / Ls;
     m.s = m.lane - m.g * Ls;
-    const int64_t first = (lb * WAVES + m.wave) * spw, i = first + m.g;
+    const int64_t i = first + m.g;
     m.site_ok = (m.g < spw) && (i < Vh);
     // lanes without a site repeat their wavefront's first site, whose data the
     // wavefront reads anyway (packed site 0 for all of them is a far cache line
@@ -910,6 +952,11 @@ __device__ __forceinline__ SiteMap site_map_lb(int Ls, int spw, int64_t Vh, int6
     m.lm = base + (m.s == 0 ? Ls - 1 : m.s - 1);
     m.lp = base + (m.s == Ls - 1 ? 0 : m.s + 1);
     return m;
+}
+
+__device__ __forceinline__ SiteMap site_map_lb(int Ls, int spw, int64_t Vh, int64_t lb)
+{
+    return site_map_first(Ls, spw, Vh, (lb * WAVES + (threadIdx.x >> 6)) * spw);
 }
 
 __device__ __forceinline__ SiteMap site_map(int Ls, int spw, int64_t Vh, int remap = 0)
@@ -1023,7 +1070,21 @@ struct M5Lds {
     cx<T> buf[WAVES][64 * STRIDE];
 };
 
-template <typename T>
+// Order LDS accesses across the workgroup, or (WAVE_ONLY: one wavefront runs
+// the step by itself) across the lanes of this wavefront.
+template <bool WAVE_ONLY>
+__device__ __forceinline__ void lds_sync()
+{
+    if constexpr (WAVE_ONLY) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    } else {
+        __syncthreads();
+    }
+}
+
+template <bool WAVE_ONLY = false, typename T>
 __device__ __forceinline__ void m5inv_lanes(cx<T> r[12], const Coef<T> &k, const SiteMap &m, int Ls,
                                             bool dag, M5Lds<T> &lds)
 {
@@ -1038,7 +1099,7 @@ __device__ __forceinline__ void m5inv_lanes(cx<T> r[12], const Coef<T> &k, const
     constexpr int ST = M5Lds<T>::STRIDE;
 #pragma unroll
     for (int c = 0; c < 12; ++c) w[lane * ST + c] = r[c];
-    __syncthreads();
+    lds_sync<WAVE_ONLY>();
     if (k.ls && g * Ls + Ls <= 64) {
         // s-dependent coefficients: the cyclic bidiagonal form of each
         // chirality (P-: M-(t) at (t, t+1) and -m M-(Ls) at (Ls, 1); P+: M-(t)
@@ -1136,17 +1197,24 @@ __device__ __forceinline__ void m5inv_lanes(cx<T> r[12], const Coef<T> &k, const
             }
         }
     }
-    __syncthreads();
+    lds_sync<WAVE_ONLY>();
 #pragma unroll
     for (int c = 0; c < 12; ++c) r[c] = w[lane * ST + c];
+}
+
+// the sum over the lanes of a wavefront, in every lane
+__device__ __forceinline__ double wave_sum(double v)
+{
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
 }
 
 // FP64 block reduction of one value per thread -> partials[slot]
 __device__ __forceinline__ void block_sum_store(double v, double *partials, int64_t slot)
 {
     __shared__ double red[WAVES];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    v = wave_sum(v);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (lane == 0) red[wave] = v;
     __syncthreads();

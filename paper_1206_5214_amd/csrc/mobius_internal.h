@@ -115,6 +115,7 @@ struct HopArgs {
     int64_t fstride = 0;  // bytes between rhs fields (0: one field)
     int64_t pstride = 0;  // partial slots per rhs (0: the number of blocks)
     const struct HopTuning *tune = nullptr;  // launch parameters (null: process defaults)
+    bool allow_split = true;  // the directions may be split over wavefronts (not in a batched launch)
 };
 
 // Kernel arguments of one hop launch over one lattice and nrhs fields (rhs r
@@ -139,8 +140,10 @@ struct HopParams {
                             // reuses the staged links' space once the direction loop is done)
                             // or past the links (split < nrhs: the links serve several systems)
     int nt;                 // non-temporal loads of the links
+    int split_mfma;         // split directions: FP16 colour multiply on the matrix cores
     int pf;                 // prefetch depth of the direction loop (0, 1, 2); 3: FP16 matrix-core
-                            // colour multiply (requires stage_links and Ls % 4 == 0)
+                            // colour multiply (requires stage_links and Ls % 4 == 0); 4: the
+                            // directions split over the wavefronts (hop_split)
     OpCoeffs c;
 };
 
@@ -156,7 +159,20 @@ struct HopTuning {
     int stage_links = 1;   // copy each block's links to LDS once
     int nt_links = 0;      // non-temporal link loads
     int mfma = 1;          // FP16: colour multiply on the matrix cores where the lane map allows
+    int split_dirs = -1;   // directions split over the wavefronts of a workgroup: 0, 1, or -1: by
+                           // the lattice (hop_splits_dirs); the loop parameters above are then unused
 };
+// Site blocks times right-hand sides up to which a hop splits its directions:
+// the split form's workgroups then run in about one round, and its chain of two
+// directions instead of eight is what the launch lasts.  D_pre, unsplit against
+// split (us): FP64 4^4 25.8 / 13.8 (4 blocks), 8^3 x 16 31.5 / 20.7 (128), 12^4
+// 47.2 / 45.9, its adjoint form 41.6 / 45.1 (324); FP32 20.1 / 15.1 (128), 26.8 /
+// 24.4 and 24.4 / 23.2 (324), 39.4 / 38.7 and 31.7 / 36.2 (692); FP16 14.6 / 11.8
+// (4), 15.4 / 13.7 (128), 16.9 / 16.2 and 15.9 / 17.3 (210).
+constexpr int64_t SPLIT_BLOCKS[3] = {160, 400, 160};  // FP64, FP32, FP16
+bool hop_splits_dirs(const Geometry &g, int prec, int nrhs, const HopTuning &t);
+// workgroups, and so |out|^2 partials per right-hand side, of a single-lattice hop
+int64_t hop_partials(const Geometry &g, bool split_dirs);
 // prefetch depth used for a precision (measured at 24^3x64, Ls=12: the FP64
 // hop needs more than 256 VGPRs once a neighbour is prefetched, which halves
 // its occupancy -- 967 us at depth 0 against 1262 us at depth 1; FP32 and FP16
@@ -170,6 +186,7 @@ inline int prefetch_depth(const HopTuning &t, int prec)
 void choose_brick(const int L[4], int Ls, int brick[3]);
 HopTuning &hop_tuning();
 
+constexpr int HOP_WAVES = 4;  // wavefronts of a site kernel's workgroup
 // Reduction workspace sizing: number of blocks a site kernel launches.
 int64_t site_kernel_blocks(const Geometry &g);
 
@@ -290,6 +307,7 @@ struct VecSys {
     int64_t nparts;        // number of valid partial slots (for the reduction)
     const double *red;     // partial sums of the norm that gives beta (p update) or alpha (r
     int64_t nred;          // update), and their number; never the slots the kernel writes
+    int32_t group, redgroup;  // consecutive slots of partials and of red that make one summand (1 or WAVES)
     CgScalars *cg;         // this system's scalars
     int64_t N5;
     int32_t flag;          // index into the active flags (-1: always active)

@@ -54,6 +54,90 @@ size_t link_lds_bytes(int spw, bool rows)
 // 16^3 x 32, Ls = 16: 160 to 147 us (the reverse order: 166 us).
 __device__ constexpr int HOP_DIR[8] = {7, 4, 0, 5, 1, 6, 2, 3};
 
+// What follows the hopping sum r = -1/2 H (B in) at one lane (Epilogue): the
+// s-direction operators, x - r, the norm and the store.  WAVE_ONLY: this
+// wavefront runs it by itself (its I^-1 buffer is the first of the workgroup's).
+// lds_shared: the I^-1 buffer overlays LDS that the other wavefronts may still
+// read.
+template <int P, bool DAG, int EPI, bool WAVE_ONLY>
+__device__ __forceinline__ void hop_epilogue(const HopParams &hp, const SiteMap &m,
+                                             cx<typename Spin<P>::T> acc[12], int r, int64_t lb, int m5_off,
+                                             bool lds_shared)
+{
+    using S = Spin<P>;
+    using T = typename S::T;
+    extern __shared__ u32x4 dyn_lds[];
+    const int Ls = hp.Ls;
+    const uint32_t N5 = (uint32_t)hp.N5, k5 = (uint32_t)m.i * (uint32_t)Ls + (uint32_t)m.s;
+    const int64_t fbytes = S::bytes(hp.N5);
+    const Buf bout(hp.out + r * hp.fstride, fbytes);
+    const char *xr = hp.x ? hp.x + r * hp.fstride : nullptr;
+    const char *yr = hp.y ? hp.y + r * hp.fstride : nullptr;
+    // coefficients of the epilogue, converted here so that none of them is
+    // held in a register across the direction loop
+    const Coef<T> k = make_coef<T>(hp.c);
+    if constexpr (DAG && (EPI & EPI_NOBOUT) == 0) {  // B^+ on the output
+        if (!k.ls)
+            mix_s(acc, k.b5, k.c5, k.mf, m, Ls, true);
+        else
+            mix_s(acc, mix_w(k, false, m, Ls, true), k.mf, m, Ls, true);
+    }
+    if constexpr ((EPI & EPI_M5ADD) != 0) {
+        cx<T> yv[12];
+        S::load(Buf(yr, fbytes), N5, k5, yv);
+        mix_s(yv, mix_w(k, true, m, Ls, DAG), k.mf, m, Ls, DAG);  // I y = M+ y + M- C5 y
+        // (I y rounded before the sum in every variant, which contracting the
+        // products into it would leave to the compiler)
+#pragma unroll
+        for (int c = 0; c < 12; ++c) pin(yv[c]);
+#pragma unroll
+        for (int c = 0; c < 12; ++c) acc[c] = acc[c] + yv[c];
+    }
+    if constexpr ((EPI & EPI_M5SUB) != 0) {
+        cx<T> yv[12];
+        S::load(Buf(yr, fbytes), N5, k5, yv);
+        mix_s(yv, mix_w(k, true, m, Ls, DAG), k.mf, m, Ls, DAG);  // I y (I^+ y)
+#pragma unroll
+        for (int c = 0; c < 12; ++c) pin(yv[c]);
+#pragma unroll
+        for (int c = 0; c < 12; ++c) acc[c] = yv[c] - acc[c];
+    }
+    if constexpr ((EPI & EPI_PRESUB) != 0) {
+        cx<T> xv[12];
+        S::load(Buf(xr, fbytes), N5, k5, xv);
+#pragma unroll
+        for (int c = 0; c < 12; ++c) acc[c] = xv[c] - acc[c];
+    }
+    if constexpr ((EPI & EPI_M5INV) != 0) {
+        // the buffer lives in the dynamic LDS; where it overlays the staged
+        // links, every wave of the block must be past its direction loop
+        if (!WAVE_ONLY && lds_shared) __syncthreads();
+        M5Lds<T> &lds = *reinterpret_cast<M5Lds<T> *>(reinterpret_cast<char *>(dyn_lds) + m5_off);
+        m5inv_lanes<WAVE_ONLY>(acc, k, m, Ls, DAG, lds);
+    }
+    if constexpr ((EPI & EPI_BMIX) != 0)  // B r (B^+ r in the adjoint hop)
+        mix_s(acc, mix_w(k, false, m, Ls, DAG), k.mf, m, Ls, DAG);
+    if constexpr ((EPI & EPI_POSTSUB) != 0) {
+        cx<T> xv[12];
+        S::load(Buf(xr, fbytes), N5, k5, xv);
+#pragma unroll
+        for (int c = 0; c < 12; ++c) acc[c] = xv[c] - acc[c];
+    }
+    if constexpr ((EPI & EPI_NORM) != 0) {
+        // |stored value|^2, from the encoded registers
+        double n = 0;
+        if (m.site_ok) n = S::store_norm2(bout, N5, k5, acc);
+        if constexpr (WAVE_ONLY) {
+            n = wave_sum(n);
+            if (m.lane == 0) hp.partials[r * hp.pstride + lb] = n;
+        } else {
+            block_sum_store(n, hp.partials + r * hp.pstride, lb);
+        }
+    } else {
+        if (m.site_ok) S::store(bout, N5, k5, acc);
+    }
+}
+
 // PF: software pipelining of the direction loop.  0: operands of direction d
 // are loaded in segment d; 1: the neighbour spinor of direction d+1 is loaded
 // while direction d computes; 2: its link as well.  The eight neighbour
@@ -70,7 +154,6 @@ __device__ __forceinline__ void hop_block(const HopParams &hp, int64_t lb, int r
     const int Ls = hp.Ls;
     const uint32_t Vh = (uint32_t)hp.Vh, N5 = (uint32_t)hp.N5;
     const uint32_t i = (uint32_t)m.i;
-    const uint32_t k5 = i * (uint32_t)Ls + (uint32_t)m.s;
     const int64_t fbytes = S::bytes(hp.N5);
     const Buf blink(hp.links, (int64_t)8 * hp.Vh * Link<P>::REC);
     const Buf bnbr(hp.nbr, 8 * hp.Vh * 4);
@@ -140,9 +223,7 @@ __device__ __forceinline__ void hop_block(const HopParams &hp, int64_t lb, int r
 
     for (int r = r0; r < hp.nrhs; r += rstep) {
     if (hp.active && !hp.active[r]) continue;
-    const Buf bin(hp.in + r * hp.fstride, fbytes), bout(hp.out + r * hp.fstride, fbytes);
-    const char *xr = hp.x ? hp.x + r * hp.fstride : nullptr;
-    const char *yr = hp.y ? hp.y + r * hp.fstride : nullptr;
+    const Buf bin(hp.in + r * hp.fstride, fbytes);
 
     cx<T> acc[12];
 #pragma unroll
@@ -201,48 +282,29 @@ __device__ __forceinline__ void hop_block(const HopParams &hp, int64_t lb, int r
                     ls.template get_h2<false>(d, u);
             }
             constexpr int SF = DAG ? +1 : -1;
-            const int sig = d < 4 ? SF : -SF;
-            half2v um[6], lp[6];
-            float al, bu = 0.f, bl = 0.f;
-            if constexpr (MIXIN) {
-#pragma unroll
-                for (int c = 0; c < 6; ++c) {
-                    um[c] = shfl_h2(o.c[c], m.lm);
-                    lp[c] = shfl_h2(o.c[6 + c], m.lp);
-                }
-                al = (float)wB.a * o.n;
-                bu = wu * __shfl(o.n, m.lm, 64);
-                bl = wl * __shfl(o.n, m.lp, 64);
-            } else {
-                al = o.n;
-            }
-            (void)sig;
-            // weights divided by the largest of them (the binary16 step keeps
-            // every term O(1)); the scale is restored in FP32
-            const float sc = fmaxf(fabsf(al), fmaxf(fabsf(bu), fabsf(bl)));
-            // (hardware reciprocal: its last-bit error scales both the
-            // binary16 terms and their restoration, so it cancels)
-            const float inv = sc > 0.f ? __builtin_amdgcn_rcpf(sc) : 0.f;
-            const half2v al2 = splat_h2(al * inv), bu2 = splat_h2(bu * inv), bl2 = splat_h2(bl * inv);
             half2v hh[6];
-#define MOBIUS_HS(MU, SG) half_spinor_h2<MU, SG, MIXIN>(o.c, um, lp, al2, bu2, bl2, hh)
-#define MOBIUS_LA(MU, SG)                                                                          \
-    if constexpr (MF)                                                                              \
-        link_accumulate_mfma<MU, SG>(hh, -0.5f * sc, ur, acc);                                     \
-    else                                                                                           \
-        link_accumulate_h2<MU, SG>(hh, -0.5f * sc, u, acc)
+#define MOBIUS_DIR(MU, SG)                                                                         \
+    {                                                                                              \
+        const float sc = half_spinor_f16<MU, SG, MIXIN>(o, (float)wB.a, wu, wl, m, hh);            \
+        cx<float> w[2][3];                                                                         \
+        if constexpr (MF)                                                                          \
+            link_mult_mfma(hh, ur, w);                                                             \
+        else                                                                                       \
+            link_mult_h2(hh, u, w);                                                                \
+        spin_accumulate_f16<MU, SG>(w, -0.5f * sc, acc);                                           \
+    }                                                                                              \
+    break
             switch (d) {
-            case 0: MOBIUS_HS(0, SF); MOBIUS_LA(0, SF); break;
-            case 1: MOBIUS_HS(1, SF); MOBIUS_LA(1, SF); break;
-            case 2: MOBIUS_HS(2, SF); MOBIUS_LA(2, SF); break;
-            case 3: MOBIUS_HS(3, SF); MOBIUS_LA(3, SF); break;
-            case 4: MOBIUS_HS(0, -SF); MOBIUS_LA(0, -SF); break;
-            case 5: MOBIUS_HS(1, -SF); MOBIUS_LA(1, -SF); break;
-            case 6: MOBIUS_HS(2, -SF); MOBIUS_LA(2, -SF); break;
-            default: MOBIUS_HS(3, -SF); MOBIUS_LA(3, -SF); break;
+            case 0: MOBIUS_DIR(0, SF);
+            case 1: MOBIUS_DIR(1, SF);
+            case 2: MOBIUS_DIR(2, SF);
+            case 3: MOBIUS_DIR(3, SF);
+            case 4: MOBIUS_DIR(0, -SF);
+            case 5: MOBIUS_DIR(1, -SF);
+            case 6: MOBIUS_DIR(2, -SF);
+            default: MOBIUS_DIR(3, -SF);
             }
-#undef MOBIUS_LA
-#undef MOBIUS_HS
+#undef MOBIUS_DIR
 #pragma unroll
             for (int c = 0; c < 12; ++c) pin(acc[c]);
             __builtin_amdgcn_sched_barrier(0);
@@ -300,61 +362,173 @@ __device__ __forceinline__ void hop_block(const HopParams &hp, int64_t lb, int r
         for (int c = 0; c < 12; ++c) acc[c] = mhalf * acc[c];
     }
 
-    {
-    // coefficients of the epilogue, converted here so that none of them is
-    // held in a register across the direction loop
-    const Coef<T> k = make_coef<T>(hp.c);
-    if constexpr (DAG && (EPI & EPI_NOBOUT) == 0) {  // B^+ on the output
-        if (!k.ls)
-            mix_s(acc, k.b5, k.c5, k.mf, m, Ls, true);
-        else
-            mix_s(acc, mix_w(k, false, m, Ls, true), k.mf, m, Ls, true);
-    }
-    if constexpr ((EPI & EPI_M5ADD) != 0) {
-        cx<T> yv[12];
-        S::load(Buf(yr, fbytes), N5, k5, yv);
-        mix_s(yv, mix_w(k, true, m, Ls, DAG), k.mf, m, Ls, DAG);  // I y = M+ y + M- C5 y
-#pragma unroll
-        for (int c = 0; c < 12; ++c) acc[c] = acc[c] + yv[c];
-    }
-    if constexpr ((EPI & EPI_M5SUB) != 0) {
-        cx<T> yv[12];
-        S::load(Buf(yr, fbytes), N5, k5, yv);
-        mix_s(yv, mix_w(k, true, m, Ls, DAG), k.mf, m, Ls, DAG);  // I y (I^+ y)
-#pragma unroll
-        for (int c = 0; c < 12; ++c) acc[c] = yv[c] - acc[c];
-    }
-    if constexpr ((EPI & EPI_PRESUB) != 0) {
-        cx<T> xv[12];
-        S::load(Buf(xr, fbytes), N5, k5, xv);
-#pragma unroll
-        for (int c = 0; c < 12; ++c) acc[c] = xv[c] - acc[c];
-    }
-    if constexpr ((EPI & EPI_M5INV) != 0) {
-        // the buffer lives in the dynamic LDS; where it overlays the staged
-        // links, every wave of the block must be past its direction loop
-        if (hp.m5_off == 0 && hp.stage_links) __syncthreads();
-        M5Lds<T> &lds = *reinterpret_cast<M5Lds<T> *>(reinterpret_cast<char *>(dyn_lds) + hp.m5_off);
-        m5inv_lanes(acc, k, m, Ls, DAG, lds);
-    }
-    if constexpr ((EPI & EPI_BMIX) != 0)  // B r (B^+ r in the adjoint hop)
-        mix_s(acc, mix_w(k, false, m, Ls, DAG), k.mf, m, Ls, DAG);
-    if constexpr ((EPI & EPI_POSTSUB) != 0) {
-        cx<T> xv[12];
-        S::load(Buf(xr, fbytes), N5, k5, xv);
-#pragma unroll
-        for (int c = 0; c < 12; ++c) acc[c] = xv[c] - acc[c];
-    }
-    if constexpr ((EPI & EPI_NORM) != 0) {
-        // |stored value|^2, from the encoded registers
-        double n = 0;
-        if (m.site_ok) n = S::store_norm2(bout, N5, k5, acc);
-        block_sum_store(n, hp.partials + r * hp.pstride, lb);
-    } else {
-        if (m.site_ok) S::store(bout, N5, k5, acc);
-    }
-    }
+    hop_epilogue<P, DAG, EPI, false>(hp, m, acc, r, lb, hp.m5_off, hp.m5_off == 0 && hp.stage_links);
     }  // rhs
+}
+
+// The hop with its directions split over the four wavefronts of a workgroup
+// (PF 4): small lattices, where a hop lasts as long as one wavefront's chain
+// of eight directions.  Every wavefront of block lb covers the same 64 / Ls
+// sites; wavefront w forms the colour products of directions HOP_DIR[2w] and
+// [2w + 1] (both neighbours and links loaded before either is used), hands them
+// over in LDS, and the first one adds all eight in the order of the unsplit
+// loop -- the same bits -- and runs the epilogue.
+
+// LDS of one wavefront: first its staged FP16 link rows, then its products
+template <int P>
+constexpr int split_lds_wave(int spw)
+{
+    // 12 products and (FP16) two scales per lane; 2 spw link records
+    const int prod = 64 * (12 * (int)sizeof(cx<typename Spin<P>::T>) + (P == MOBIUS_F16 ? 8 : 0));
+    const int rows = P == MOBIUS_F16 ? 2 * spw * LINKROW_REC : 0;
+    return prod > rows ? prod : rows;
+}
+
+// colour products w and scales sc (FP16) of directions HOP_DIR[2 PART] and [2 PART + 1]
+template <int P, bool DAG, int EPI, int PART>
+__device__ __forceinline__ void hop_two_dirs(const HopParams &hp, const SiteMap &m, int r, char *lds,
+                                             cx<typename Spin<P>::T> w[2][2][3], float sc[2])
+{
+    using S = Spin<P>;
+    using T = typename S::T;
+    constexpr int D0 = HOP_DIR[2 * PART], D1 = HOP_DIR[2 * PART + 1];
+    constexpr int SF = DAG ? +1 : -1;  // forward projector (1 -+ g_mu)
+    constexpr int S0 = D0 < 4 ? SF : -SF, S1 = D1 < 4 ? SF : -SF;
+    constexpr bool MIXIN = !DAG && (EPI & EPI_PREMIXED) == 0;
+    const int Ls = hp.Ls;
+    const uint32_t Vh = (uint32_t)hp.Vh, N5 = (uint32_t)hp.N5, i = (uint32_t)m.i;
+    const Buf bnbr(hp.nbr, 8 * hp.Vh * 4), blink(hp.links, (int64_t)8 * hp.Vh * Link<P>::REC);
+    const Buf bin(hp.in + r * hp.fstride, S::bytes(hp.N5));
+    const uint32_t j0 = bnbr.ld4(i * 32u + 4u * D0, 0u) * (uint32_t)Ls + (uint32_t)m.s;
+    const uint32_t j1 = bnbr.ld4(i * 32u + 4u * D1, 0u) * (uint32_t)Ls + (uint32_t)m.s;
+    const Coef<T> k = make_coef<T>(hp.c);
+    const MixW<T> wB = mix_w(k, false, m, Ls, false);
+    if constexpr (P == MOBIUS_F16) {
+        // the unsplit loop's choice: matrix cores where whole 4-lane groups share a site
+        const bool mf = hp.split_mfma;
+        constexpr uint32_t REC = Link<P>::REC;
+        LinkH2 u0, u1;
+        if (mf) {  // one lane per link record
+            const uint32_t spw = (uint32_t)hp.spw, i0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)i);
+            const uint32_t lane = (uint32_t)m.lane, dd = lane / spw, j = lane - dd * spw;
+            if (dd < 2 && i0 + j < Vh) {
+                half2v u[9];
+                u32x4 *dst = reinterpret_cast<u32x4 *>(lds + lane * LINKROW_REC);
+                Link<P>::raw_load(blink, (i0 + j) * REC + (dd ? D1 : D0) * Vh * REC, 0u, u);
+                if (dd == 0)
+                    stage_link_f16<(D0 < 4), true>(u, dst);
+                else
+                    stage_link_f16<(D1 < 4), true>(u, dst);
+            }
+        } else {
+            const LinkSource<P> ls{&blink, nullptr, Vh, i, 0u, 0u};
+            ls.template get_h2<(D0 < 4)>(D0, u0);
+            ls.template get_h2<(D1 < 4)>(D1, u1);
+        }
+        RawH o0, o1;
+        load_raw_f16(bin, N5, j0, o0);
+        load_raw_f16(bin, N5, j1, o1);
+        const float wu = MIXIN ? (float)wB.bu * (m.s == 0 ? -(float)k.mf : 1.f) : 0.f;
+        const float wl = MIXIN ? (float)wB.bl * (m.s == Ls - 1 ? -(float)k.mf : 1.f) : 0.f;
+        half2v h0[6], h1[6];
+        sc[0] = half_spinor_f16<(D0 & 3), S0, MIXIN>(o0, (float)wB.a, wu, wl, m, h0);
+        sc[1] = half_spinor_f16<(D1 & 3), S1, MIXIN>(o1, (float)wB.a, wu, wl, m, h1);
+        if (mf) {
+            lds_sync<true>();
+            LinkSource<P> ls{&blink, lds, Vh, i, m.site_ok ? (uint32_t)m.g : 0u, (uint32_t)hp.spw};
+            LinkRows x;
+            ls.get_rows(0, m.lane & 3, x);
+            link_mult_mfma(h0, x, w[0]);
+            ls.get_rows(1, m.lane & 3, x);
+            link_mult_mfma(h1, x, w[1]);
+            lds_sync<true>();  // (the products take the rows' place)
+        } else {
+            link_mult_h2(h0, u0, w[0]);
+            link_mult_h2(h1, u1, w[1]);
+        }
+    } else {
+        cx<T> c0[12], c1[12], u0[9], u1[9];
+        load_link<P>(blink, Vh, D0, i, u0);
+        load_link<P>(blink, Vh, D1, i, u1);
+        S::load(bin, N5, j0, c0);
+        S::load(bin, N5, j1, c1);
+        if constexpr (MIXIN) mix_s(c0, wB, k.mf, m, Ls, false);
+        hop_dir_w<P, (D0 & 3), (D0 < 4), S0>(c0, u0, w[0]);
+        if constexpr (MIXIN) mix_s(c1, wB, k.mf, m, Ls, false);
+        hop_dir_w<P, (D1 & 3), (D1 < 4), S1>(c1, u1, w[1]);
+    }
+}
+
+// acc += the products of direction D
+template <int P, bool DAG, int D>
+__device__ __forceinline__ void split_accumulate(const cx<typename Spin<P>::T> w[2][3], float sc,
+                                                 cx<typename Spin<P>::T> acc[12])
+{
+    constexpr int SF = DAG ? +1 : -1, SG = D < 4 ? SF : -SF;
+    if constexpr (P == MOBIUS_F16)
+        spin_accumulate_f16<(D & 3), SG>(w, -0.5f * sc, acc);
+    else
+        spin_accumulate<typename Spin<P>::T, (D & 3), SG>(w, acc);
+}
+
+template <int P, bool DAG, int EPI>
+__device__ __forceinline__ void hop_split(const HopParams &hp, int64_t lb, int r)
+{
+    using T = typename Spin<P>::T;
+    if (hp.active && !hp.active[r]) return;
+    const SiteMap m = site_map_first(hp.Ls, hp.spw, hp.Vh, lb * hp.spw);
+    extern __shared__ u32x4 dyn_lds[];
+    const int stride = split_lds_wave<P>(hp.spw);
+    const int wv = __builtin_amdgcn_readfirstlane(m.wave);
+    char *mine = reinterpret_cast<char *>(dyn_lds) + wv * stride;
+    cx<T> w[2][2][3];
+    float sc[2] = {0.f, 0.f};
+    switch (wv) {
+    case 0: hop_two_dirs<P, DAG, EPI, 0>(hp, m, r, mine, w, sc); break;
+    case 1: hop_two_dirs<P, DAG, EPI, 1>(hp, m, r, mine, w, sc); break;
+    case 2: hop_two_dirs<P, DAG, EPI, 2>(hp, m, r, mine, w, sc); break;
+    default: hop_two_dirs<P, DAG, EPI, 3>(hp, m, r, mine, w, sc); break;
+    }
+    if (wv > 0) {
+        cx<T> *p = reinterpret_cast<cx<T> *>(mine);
+#pragma unroll
+        for (int e = 0; e < 12; ++e) p[e * 64 + m.lane] = w[e / 6][(e / 3) % 2][e % 3];
+        if constexpr (P == MOBIUS_F16) {
+            float *q = reinterpret_cast<float *>(p + 12 * 64);
+            q[m.lane] = sc[0];
+            q[64 + m.lane] = sc[1];
+        }
+    }
+    __syncthreads();
+    if (wv > 0) return;
+    cx<T> acc[12];
+#pragma unroll
+    for (int c = 0; c < 12; ++c) acc[c] = {0, 0};
+    split_accumulate<P, DAG, HOP_DIR[0]>(w[0], sc[0], acc);
+    split_accumulate<P, DAG, HOP_DIR[1]>(w[1], sc[1], acc);
+#define MOBIUS_PART(Q)                                                                             \
+    {                                                                                              \
+        const cx<T> *p = reinterpret_cast<const cx<T> *>(reinterpret_cast<const char *>(dyn_lds) + (Q) * stride); \
+        _Pragma("unroll") for (int e = 0; e < 12; ++e) w[e / 6][(e / 3) % 2][e % 3] = p[e * 64 + m.lane]; \
+        if constexpr (P == MOBIUS_F16) {                                                           \
+            const float *q = reinterpret_cast<const float *>(p + 12 * 64);                         \
+            sc[0] = q[m.lane];                                                                     \
+            sc[1] = q[64 + m.lane];                                                                \
+        }                                                                                          \
+        split_accumulate<P, DAG, HOP_DIR[2 * (Q)]>(w[0], sc[0], acc);                              \
+        split_accumulate<P, DAG, HOP_DIR[2 * (Q) + 1]>(w[1], sc[1], acc);                          \
+    }
+    MOBIUS_PART(1)
+    MOBIUS_PART(2)
+    MOBIUS_PART(3)
+#undef MOBIUS_PART
+    if constexpr (P != MOBIUS_F16) {
+        const T mhalf = (T)-0.5;
+#pragma unroll
+        for (int c = 0; c < 12; ++c) acc[c] = mhalf * acc[c];
+    }
+    lds_sync<true>();
+    hop_epilogue<P, DAG, EPI, true>(hp, m, acc, r, lb, 0, false);
 }
 
 // The binary16 matrix-core loop is held to 128 VGPRs (four waves per SIMD):
@@ -366,7 +540,14 @@ template <int P, bool DAG, int EPI, int PF>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(P == MOBIUS_F16 && PF == 3 ? 4 : 1)))
 void hop_kernel(HopParams hp)
 {
-    hop_block<P, DAG, EPI, PF>(hp, logical_block(hp.remap), blockIdx.y, gridDim.y);
+    if constexpr (PF == 4) {
+        for (int r = blockIdx.y; r < hp.nrhs; r += gridDim.y) {
+            hop_split<P, DAG, EPI>(hp, logical_block(hp.remap), r);
+            if (r + (int)gridDim.y < hp.nrhs) __syncthreads();  // (more right-hand sides than grid rows)
+        }
+    } else {
+        hop_block<P, DAG, EPI, PF>(hp, logical_block(hp.remap), blockIdx.y, gridDim.y);
+    }
 }
 
 // Persistent launch over a batch of lattices of uneven size: a fixed grid
@@ -416,10 +597,13 @@ void hop_launch(const HopParams &hp0, hipStream_t st)
         hp.m5_off = split < hp.nrhs ? (int)links : 0;
         dyn = std::max(links, (size_t)hp.m5_off + sizeof(M5Lds<typename Spin<P>::T>));
     }
+    // split directions: each wavefront's products; the one I^-1 buffer in use goes over them
+    if (hp.pf == 4) dyn = (size_t)WAVES * split_lds_wave<P>(hp.spw);
     const dim3 grid((unsigned)hp.nblocks, (unsigned)split), blk(BLOCK);
     switch (hp.pf) {
     case 0: hipLaunchKernelGGL((hop_kernel<P, DAG, EPI, 0>), grid, blk, dyn, st, hp); break;
     case 1: hipLaunchKernelGGL((hop_kernel<P, DAG, EPI, 1>), grid, blk, dyn, st, hp); break;
+    case 4: hipLaunchKernelGGL((hop_kernel<P, DAG, EPI, 4>), grid, blk, dyn, st, hp); break;
     case 3:
         if constexpr (P == MOBIUS_F16) {
             hipLaunchKernelGGL((hop_kernel<P, DAG, EPI, 3>), grid, blk, dyn, st, hp);
@@ -911,14 +1095,26 @@ __device__ __forceinline__ bool sys_inactive(const VecSys &v, const int32_t *act
 // and the restart flag, which alpha's writes; alpha's reads gamma_new, which
 // beta's writes), so no workgroup waits for another.
 
+// the k-th summand of a sum of partials: `group` consecutive slots, added in
+// the order in which a workgroup adds its wavefronts (the split hop leaves one
+// slot per wavefront of sites), so that the sum does not depend on the split
+__device__ __forceinline__ double summand(const double *part, int64_t k, int group, int64_t n)
+{
+    if (group == 1) return part[k];
+    double t = 0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) t += k * WAVES + w < n ? part[k * WAVES + w] : 0.0;
+    return t;
+}
+
 // sum of n partial sums by the whole workgroup (BLAS_BLOCK threads), in every thread
 static_assert(BLOCK == BLAS_BLOCK, "the r update runs in the site kernels' workgroups");
-__device__ __forceinline__ double block_total(const double *part, int64_t n)
+__device__ __forceinline__ double block_total(const double *part, int64_t n, int group)
 {
     __shared__ double red[BLAS_BLOCK / 64];
     double t = 0;
 #pragma unroll 4
-    for (int64_t k = threadIdx.x; k < n; k += BLAS_BLOCK) t += part[k];
+    for (int64_t k = threadIdx.x; k * group < n; k += BLAS_BLOCK) t += summand(part, k, group, n);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = t;
@@ -936,7 +1132,7 @@ __device__ __forceinline__ double cg_beta(const VecSys &v, const int32_t *restar
     CgScalars &s = *v.cg;
     const double gamma = s.gamma;
     const bool rs = restart[v.flag] != 0;
-    const double g = block_total(v.red, v.nred);
+    const double g = block_total(v.red, v.nred, v.redgroup);
     const double beta = (!rs && gamma > 0) ? g / gamma : 0.0;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         s.gamma_new = g;
@@ -951,7 +1147,7 @@ __device__ __forceinline__ double cg_alpha(const VecSys &v, int32_t *restart, in
 {
     CgScalars &s = *v.cg;
     const double g = s.gamma_new;
-    const double qq = block_total(v.red, v.nred);
+    const double qq = block_total(v.red, v.nred, v.redgroup);
     const double alpha = qq > 0 ? g / qq : 0.0;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         s.qq = qq;
@@ -1276,7 +1472,7 @@ __global__ __launch_bounds__(1024) void reduce_batch(const VecSys *sys, const in
     __shared__ double sm[1024];
     const int64_t n = count_override > 0 ? count_override : v.nparts;
     double t = 0;
-    for (int64_t k = threadIdx.x; k < n; k += 1024) t += v.partials[k];
+    for (int64_t k = threadIdx.x; k * v.group < n; k += 1024) t += summand(v.partials, k, v.group, n);
     sm[threadIdx.x] = t;
     __syncthreads();
     for (int w = 512; w > 0; w >>= 1) {
@@ -1292,9 +1488,11 @@ __global__ __launch_bounds__(BLAS_BLOCK) void reduce_parts_batch(const VecSys *s
                                                                  double *out)
 {
     const VecSys v = sys[blockIdx.y];
-    if (sys_inactive(v, active) || v.nparts <= RED_DIRECT) return;
-    const int64_t n = v.nparts, a = n * blockIdx.x / RED_PARTS, b = n * (blockIdx.x + 1) / RED_PARTS;
-    const double t = block_total(v.partials + a, b - a);
+    if (sys_inactive(v, active) || v.nparts <= RED_DIRECT * v.group) return;
+    // in whole summands
+    const int64_t n = (v.nparts + v.group - 1) / v.group;
+    const int64_t a = n * blockIdx.x / RED_PARTS * v.group, b = n * (blockIdx.x + 1) / RED_PARTS * v.group;
+    const double t = block_total(v.partials + a, (b < v.nparts ? b : v.nparts) - a, v.group);
     if (threadIdx.x == 0) out[(int64_t)blockIdx.y * RED_PARTS + blockIdx.x] = t;
 }
 
@@ -1344,10 +1542,16 @@ HopTuning &hop_tuning()
 {
     static HopTuning t = [] {
         HopTuning d;
-        if (const char *e = std::getenv("MOBIUS_XCD_REMAP")) d.xcd_remap = std::atoi(e);
-        if (const char *e = std::getenv("MOBIUS_PREFETCH")) d.prefetch = std::atoi(e);
-        if (const char *e = std::getenv("MOBIUS_STAGE_LINKS")) d.stage_links = std::atoi(e);
-        if (const char *e = std::getenv("MOBIUS_NT_LINKS")) d.nt_links = std::atoi(e);
+        const auto given = [&d](const char *name, int &v) {
+            if (const char *e = std::getenv(name)) {
+                v = std::atoi(e);
+                d.split_dirs = 0;  // a loop variant was asked for
+            }
+        };
+        given("MOBIUS_XCD_REMAP", d.xcd_remap);
+        given("MOBIUS_PREFETCH", d.prefetch);
+        given("MOBIUS_STAGE_LINKS", d.stage_links);
+        given("MOBIUS_NT_LINKS", d.nt_links);
         return d;
     }();
     return t;
@@ -1361,6 +1565,18 @@ int64_t site_kernel_blocks(const Geometry &g)
     const int spw = sites_per_wave(g.Ls);
     const int64_t per_block = (int64_t)spw * WAVES;
     return (g.Vh + per_block - 1) / per_block;
+}
+
+bool hop_splits_dirs(const Geometry &g, int prec, int nrhs, const HopTuning &t)
+{
+    if (t.split_dirs >= 0) return t.split_dirs != 0;
+    return site_kernel_blocks(g) * nrhs <= SPLIT_BLOCKS[prec];
+}
+
+int64_t hop_partials(const Geometry &g, bool split_dirs)
+{
+    const int spw = sites_per_wave(g.Ls);
+    return split_dirs ? (g.Vh + spw - 1) / spw : site_kernel_blocks(g);
 }
 
 int64_t blas_blocks(const Geometry &g) { return (g.N5 + BLAS_BLOCK - 1) / BLAS_BLOCK; }
@@ -1495,7 +1711,9 @@ HopParams make_hop_params(const Geometry &g, const OpCoeffs &c, const void *link
     hp.Vh = g.Vh;
     hp.N5 = g.N5;
     hp.fstride = a.fstride > 0 ? a.fstride : field_bytes(g, a.prec);
-    hp.nblocks = site_kernel_blocks(g);
+    const HopTuning &t = a.tune ? *a.tune : hop_tuning();
+    const bool split_dirs = a.allow_split && hop_splits_dirs(g, a.prec, a.nrhs, t);
+    hp.nblocks = hop_partials(g, split_dirs);
     hp.pstride = a.pstride > 0 ? a.pstride : hp.nblocks;
     hp.Ls = g.Ls;
     hp.spw = sites_per_wave(g.Ls);
@@ -1508,7 +1726,6 @@ HopParams make_hop_params(const Geometry &g, const OpCoeffs &c, const void *link
     // 12: FP64 4592 / 4241 us, FP16 1266 / 1241 us; 24^3 x 64, Ls = 12, 3: FP64
     // 5600 / 5801 us, FP16 1610 / 1665 us.
     hp.split = 8 * g.Vh * link_record_bytes(a.prec) <= (int64_t)128 << 20 ? a.nrhs : 1;
-    const HopTuning &t = a.tune ? *a.tune : hop_tuning();
     hp.remap = t.xcd_remap;
     hp.stage_links = t.stage_links && hop_link_lds_bytes(a.prec, g.Ls, false) <= 64 * 1024;
     hp.nt = t.nt_links;
@@ -1518,6 +1735,12 @@ HopParams make_hop_params(const Geometry &g, const OpCoeffs &c, const void *link
     if (a.prec == MOBIUS_F16 && t.mfma && hp.stage_links && g.Ls % 4 == 0 &&
         hop_link_lds_bytes(a.prec, g.Ls, true) <= 64 * 1024)
         hp.pf = 3;
+    if (split_dirs) {
+        hp.split_mfma = hp.pf == 3;
+        hp.pf = 4;
+        hp.stage_links = 0;
+        hp.split = a.nrhs;
+    }
     hp.c = c;
     return hp;
 }

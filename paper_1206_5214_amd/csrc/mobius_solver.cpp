@@ -68,7 +68,9 @@ struct Group {
     int64_t fb[NFIELDS];      // bytes of one field of each kind
     char *f[NFIELDS];         // (f[F_P]: the ring slot of the current iteration)
     char *pring;              // slot 0 of the ring of directions
-    int64_t hop_blocks, blas_blocks;
+    int split, split64;                // hops split their directions: in the inner precision, in FP64
+    int64_t hop_blocks, hop_blocks64;  // partials of such a hop
+    int64_t site_blocks, blas_blocks;  // of the site kernels and of the vector kernels
 };
 
 // extra per-system doubles
@@ -252,10 +254,14 @@ int Batch::setup(mobius_ctx *const *ctxs, int n, const void *const *src, void *c
             w += g.fb[k] * nrhs * slots(k);
         }
         g.pring = g.f[F_P];
-        g.hop_blocks = site_kernel_blocks(G);
-        max_site_blocks = std::max(max_site_blocks, g.hop_blocks);
+        g.split = n == 1 && hop_splits_dirs(G, lo, nrhs, g.ctx->tune[lo]);
+        g.split64 = n == 1 && hop_splits_dirs(G, MOBIUS_F64, nrhs, g.ctx->tune[MOBIUS_F64]);
+        g.hop_blocks = hop_partials(G, g.split);
+        g.hop_blocks64 = hop_partials(G, g.split64);
+        g.site_blocks = site_kernel_blocks(G);
+        max_site_blocks = std::max(max_site_blocks, g.site_blocks);
         g.blas_blocks = blas_blocks(G);
-        pstride = std::max(pstride, std::max(g.hop_blocks, g.blas_blocks));
+        pstride = std::max({pstride, g.hop_blocks, g.hop_blocks64, g.site_blocks, g.blas_blocks});
         max_n5 = std::max(max_n5, G.N5);
     }
     // |out|^2 partial sums fused into the hop epilogue for every system (the
@@ -415,14 +421,18 @@ int Batch::setup(mobius_ctx *const *ctxs, int n, const void *const *src, void *c
             v.coef = coef + (&g - groups.data());
             v.partials = part_v + (int64_t)j * pstride;
             v.nparts = g.blas_blocks;
+            v.group = v.redgroup = 1;
             v.cg = &sc[j];
             // beta and alpha come from the |out|^2 partials of the hops (or of the
             // separate norm pass) -- in the normal equations beta from those of r
             VecSys h = v;
             h.partials = part + (int64_t)j * pstride;
             h.nparts = fused_norm ? g.hop_blocks : g.blas_blocks;
+            h.group = fused_norm && g.split ? HOP_WAVES : 1;
             auto reads = [&](VecSys &w, const VecSys &from) {
-                const bool two = from.nparts > RED_DIRECT;  // (by the system alone: a batch sums as its solo solves)
+                // (by the system alone: a batch sums as its solo solves)
+                const bool two = from.nparts > RED_DIRECT * from.group;
+                w.redgroup = two ? 1 : from.group;
                 w.red = two ? part2 + (int64_t)j * RED_PARTS : from.partials;
                 w.nred = two ? RED_PARTS : from.nparts;
             };
@@ -433,7 +443,7 @@ int Batch::setup(mobius_ctx *const *ctxs, int n, const void *const *src, void *c
             h_vec[(size_t)VP_ACC * nsys + j] = t;
             t = v; t.a = F(F_B); t.b = F(F_Q64); t.s1 = &extra[j * NEXTRA + X_MINUS1]; t.d = F(F_RH);
             h_vec[(size_t)VP_RES * nsys + j] = t;
-            t = h; t.nparts = g.hop_blocks;
+            t = h; t.nparts = g.hop_blocks64; t.group = g.split64 ? HOP_WAVES : 1;
             h_vec[(size_t)VP_HOPRED * nsys + j] = t;
             h_vec[(size_t)VP_CGRED * nsys + j] = h;
             h_vec[(size_t)VP_BLASRED * nsys + j] = v;
@@ -468,7 +478,7 @@ int Batch::setup(mobius_ctx *const *ctxs, int n, const void *const *src, void *c
             h_vec[(size_t)VP_PUPD_RN * nsys + j] = t;
             t = v; t.c = F(F_R); t.d = F(F_S); reads(t, h);
             h_vec[(size_t)VP_R_N * nsys + j] = t;
-            t = v; t.a = F(F_R); t.b = F(F_Q); t.c = F(F_U); t.nparts = g.hop_blocks; reads(t, h);
+            t = v; t.a = F(F_R); t.b = F(F_Q); t.c = F(F_U); t.nparts = g.site_blocks; reads(t, h);
             h_vec[(size_t)VP_RUPD * nsys + j] = t;
             t = h; t.a = F(F_Q);
             h_vec[(size_t)VP_NORM_Q * nsys + j] = t;
@@ -542,6 +552,7 @@ HopArgs Batch::hop_args_for(const Group &g, const HopPattern &p) const
     a.fstride = g.fb[p.in];
     a.pstride = pstride;
     a.tune = &g.ctx->tune[p.prec];
+    a.allow_split = ngroups() == 1;
     return a;
 }
 

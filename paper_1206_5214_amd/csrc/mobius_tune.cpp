@@ -8,7 +8,9 @@
 //   non-temporal link loads                {off, on}
 //   FP16 colour multiply on the matrix cores {off, on} (with staging, Ls % 4 == 0)
 // and keeps the fastest in the context; every later operator application,
-// solve and force evaluation of the context launches with it.  Results can be
+// solve and force evaluation of the context launches with it.  Where the
+// library would split the directions over wavefronts by itself (a small
+// lattice), that form, which has no such parameters, is timed against them too.  Results can be
 // cached in a text file (one line per lattice, Ls, precision and device)
 // named by MOBIUS_TUNE_CACHE, so that a run re-uses the measurement of an
 // earlier one.
@@ -51,6 +53,9 @@ bool cache_lookup(const std::string &path, const std::string &key, HopTuning &t,
         HopTuning c;
         double u;
         if (v >> c.prefetch >> c.stage_links >> c.xcd_remap >> c.nt_links >> c.mfma >> u) {
+            // 1: the split form was faster than all of them; absent or 0: it was not tried or was not
+            if (!(v >> c.split_dirs) || c.split_dirs != 1) c.split_dirs = 0;
+            if (c.split_dirs) c.split_dirs = -1;
             t = c;
             us = u;
             found = true;
@@ -64,7 +69,7 @@ void cache_store(const std::string &path, const std::string &key, const HopTunin
     std::ofstream f(path, std::ios::app);
     f.precision(17);  // the time reads back exactly
     f << key << " | " << t.prefetch << ' ' << t.stage_links << ' ' << t.xcd_remap << ' '
-      << t.nt_links << ' ' << t.mfma << ' ' << us << '\n';
+      << t.nt_links << ' ' << t.mfma << ' ' << us << ' ' << (t.split_dirs ? 1 : 0) << '\n';
 }
 
 }  // namespace
@@ -97,6 +102,35 @@ int tune(mobius_ctx *ctx, int prec, int reps, mobius_tune_result *out, hipStream
         best_us = 1e300;
         int rc = MOBIUS_OK;
         const int nmf = prec == MOBIUS_F16 && g.Ls % 4 == 0 ? 2 : 1;
+        // one candidate on the metered hop; its time per hop
+        auto time_one = [&](const HopTuning &c, double &us) -> int {
+            HopArgs a;
+            a.prec = prec;
+            a.dag = 0;
+            a.epi = 0;
+            a.in = in;
+            a.out = outf;
+            a.nrhs = 1;
+            a.tune = &c;
+            auto run = [&](int n) {
+                for (int r = 0; r < n; ++r)
+                    for (int par = 0; par < 2; ++par) {
+                        a.out_parity = par;
+                        hipError_t x = launch_hop(g, ctx->c, hop_links(ctx, prec, a.dag),
+                                                  static_cast<const int32_t *>(ctx->nbr.p), a, st);
+                        if (x != hipSuccess) return x;
+                    }
+                return hipSuccess;
+            };
+            float ms = 0;
+            if ((e = run(2)) != hipSuccess || (e = hipEventRecord(e0, st)) != hipSuccess ||
+                (e = run(nrep)) != hipSuccess || (e = hipEventRecord(e1, st)) != hipSuccess ||
+                (e = hipEventSynchronize(e1)) != hipSuccess ||
+                (e = hipEventElapsedTime(&ms, e0, e1)) != hipSuccess)
+                return set_error(MOBIUS_EHIP, hipGetErrorString(e));
+            us = 1e3 * ms / (2.0 * nrep);
+            return MOBIUS_OK;
+        };
         for (int mf = 0; mf < nmf && rc == MOBIUS_OK; ++mf)
         for (int pf = 0; pf < 3 && rc == MOBIUS_OK; ++pf)
             for (int stage = 0; stage < 2 && rc == MOBIUS_OK; ++stage)
@@ -110,38 +144,21 @@ int tune(mobius_ctx *ctx, int prec, int reps, mobius_tune_result *out, hipStream
                         c.xcd_remap = remap;
                         c.nt_links = nt;
                         c.mfma = mf;
-                        HopArgs a;
-                        a.prec = prec;
-                        a.dag = 0;
-                        a.epi = 0;
-                        a.in = in;
-                        a.out = outf;
-                        a.nrhs = 1;
-                        a.tune = &c;
-                        auto run = [&](int n) {
-                            for (int r = 0; r < n; ++r)
-                                for (int par = 0; par < 2; ++par) {
-                                    a.out_parity = par;
-                                    hipError_t x = launch_hop(g, ctx->c, hop_links(ctx, prec, a.dag),
-                                                              static_cast<const int32_t *>(ctx->nbr.p), a, st);
-                                    if (x != hipSuccess) return x;
-                                }
-                            return hipSuccess;
-                        };
-                        float ms = 0;
-                        if ((e = run(2)) != hipSuccess || (e = hipEventRecord(e0, st)) != hipSuccess ||
-                            (e = run(nrep)) != hipSuccess || (e = hipEventRecord(e1, st)) != hipSuccess ||
-                            (e = hipEventSynchronize(e1)) != hipSuccess ||
-                            (e = hipEventElapsedTime(&ms, e0, e1)) != hipSuccess) {
-                            rc = set_error(MOBIUS_EHIP, hipGetErrorString(e));
-                            break;
-                        }
-                        const double us = 1e3 * ms / (2.0 * nrep);
+                        c.split_dirs = 0;
+                        double us = 0;
+                        if ((rc = time_one(c, us)) != MOBIUS_OK) break;
                         if (us < best_us) {
                             best_us = us;
                             best = c;
                         }
                     }
+        if (HopTuning c; rc == MOBIUS_OK && hop_splits_dirs(g, prec, 1, c)) {
+            double us = 0;
+            if ((rc = time_one(c, us)) == MOBIUS_OK && us < best_us) {
+                best_us = us;
+                best.split_dirs = -1;  // (the loop parameters serve the launches that do not split)
+            }
+        }
         (void)hipEventDestroy(e0);
         (void)hipEventDestroy(e1);
         if (rc != MOBIUS_OK) return rc;

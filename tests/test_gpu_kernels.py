@@ -52,3 +52,38 @@ def test_pack_unpack_exact(torch_cuda, dims, Ls, nrhs):
                 assert torch.equal(e1, even[r * fb:(r + 1) * fb])
                 assert torch.equal(o1, odd[r * fb:(r + 1) * fb])
     op.close()
+
+
+# a hop with its directions split over wavefronts (the small lattices' default)
+# against the loop variants that set_tuning asks for: fewer sites than one
+# wavefront's, partial last wavefronts, odd Ls, one site per wavefront, matrix-core
+# and dot-product colour multiply (Ls divisible by 4 or not)
+@pytest.mark.parametrize("dims,Ls,nrhs", [((2, 2, 2, 2), 2, 1), ((4, 2, 2, 6), 5, 3), ((6, 4, 2, 4), 33, 2),
+                                          ((4, 4, 4, 6), 12, 1), ((4, 4, 6, 6), 7, 2), ((8, 8, 8, 16), 8, 1)])
+def test_split_hop_same_bits(torch_cuda, dims, Ls, nrhs):
+    """The split form adds the eight directions in the order of the loop: every
+    operator block has the same bits, and a solve the same iterates."""
+    torch = torch_cuda
+    mobius, op, eta = _setup(torch, dims, Ls, nrhs)
+    fields = {}
+    for prec in (mobius.F64, mobius.F32, mobius.F16):
+        even, odd = op.pack(eta, prec, nrhs)
+        fields[prec] = {p: torch.cat([even, odd]) if p == mobius.OP_FULL else odd for p in range(8)}
+
+    def blocks():
+        return {(prec, o, dag): op.dslash(fields[prec][o], 1, prec, op=o, dag=dag, nrhs=nrhs)
+                for prec in fields for o in range(8) for dag in (False, True)}
+
+    def solves():
+        return [op.solve(eta, tol=1e-10, maxiter=20000, inner_prec=prec)[:2] for prec in fields]
+
+    split, ssol = blocks(), solves() if Ls == 8 else []
+    for prec in fields:
+        op.set_tuning(prec, 0 if prec == mobius.F64 else 2, 1, 1, 0, mfma=1)
+    loop, lsol = blocks(), solves() if Ls == 8 else []
+    for key in split:
+        assert torch.equal(split[key], loop[key]), key
+    for (a, ia), (b, ib) in zip(ssol, lsol):
+        assert torch.equal(a, b)
+        assert [i.iters for i in ia] == [i.iters for i in ib]
+    op.close()
