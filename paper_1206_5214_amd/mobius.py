@@ -231,6 +231,11 @@ class Operator:
         import torch
         return torch.zeros(self.field_bytes(prec) * nrhs, dtype=torch.uint8, device="cuda")
 
+    def _out_field(self, prec, nrhs=1):
+        """A packed field the library writes in full (every byte: no clearing)."""
+        import torch
+        return torch.empty(self.field_bytes(prec) * nrhs, dtype=torch.uint8, device="cuda")
+
     def _check_canon(self, t, nrhs, name):
         import torch
         _require_cuda(t, torch.complex128, name)
@@ -251,7 +256,7 @@ class Operator:
 
     def pack(self, canon, prec, nrhs=1):
         self._check_canon(canon, nrhs, "canonical field")
-        even, odd = self.new_field(prec, nrhs), self.new_field(prec, nrhs)
+        even, odd = self._out_field(prec, nrhs), self._out_field(prec, nrhs)
         _check(lib().mobius_pack(self._h, prec, _ptr(canon), _ptr(even), _ptr(odd), nrhs,
                                  _stream()))
         return even, odd
@@ -261,7 +266,7 @@ class Operator:
         followed by its nrhs odd halves (the operand form of OP_FULL)."""
         self._check_canon(canon, nrhs, "canonical field")
         fb = self.field_bytes(prec) * nrhs
-        buf = self.new_field(prec, 2 * nrhs)
+        buf = self._out_field(prec, 2 * nrhs)
         _check(lib().mobius_pack(self._h, prec, _ptr(canon), _ptr(buf), _ptr(buf[fb:]), nrhs,
                                  _stream()))
         return buf
@@ -288,7 +293,7 @@ class Operator:
         For op=OP_FULL, x and out hold both halves (see pack_full)."""
         nf = 2 * nrhs if op == OP_FULL else nrhs
         if out is None:
-            out = self.new_field(max(prec, 0) if prec in (F64, F32, F16) else F64, nf)
+            out = self._out_field(prec if prec in (F64, F32, F16) else F64, nf)
         self._check_packed(x, prec, nf, "input")
         self._check_packed(out, prec, nf, "output")
         f = lib().mobius_dslash_dag if dag else lib().mobius_dslash
@@ -308,7 +313,7 @@ class Operator:
 
     def m5inv(self, x, prec, dag=False, out=None, nrhs=1):
         if out is None:
-            out = self.new_field(prec, nrhs)
+            out = self._out_field(prec, nrhs)
         self._check_packed(x, prec, nrhs, "input")
         self._check_packed(out, prec, nrhs, "output")
         _check(lib().mobius_m5inv(self._h, prec, int(dag), _ptr(x), _ptr(out), nrhs, _stream()))
