@@ -154,7 +154,13 @@ __device__ __forceinline__ void pin(cx<T> &v)
 }
 
 // ---------------------------------------------------------------------------
-// storage policies for packed spinors: 16-byte chunks over site5
+// storage policies for packed spinors (layouts: see mobius_internal.h)
+
+struct Lay {
+    uint32_t Ls, N5;  // fifth-dimension extent, 5d sites of the field
+    // FP64 and FP32: one record per 4d site where its pieces are whole 64-byte sectors
+    __device__ bool records() const { return (Ls & 3u) == 0; }
+};
 
 template <int P>
 struct Spin;
@@ -163,28 +169,31 @@ template <>
 struct Spin<MOBIUS_F64> {
     using T = double;
     __host__ __device__ static int64_t bytes(int64_t N5) { return N5 * 192; }
-    __device__ static void load(const Buf &b, uint32_t N5, uint32_t k, cx<T> v[12])
+    // lane offset of slice s of packed site i, and uniform offset of chunk c
+    __device__ static uint32_t site_off(Lay L, uint32_t i, uint32_t s) { return i * (L.Ls * (L.records() ? 192u : 16u)) + s * 16u; }
+    __device__ static uint32_t chunk_off(Lay L, int c) { return (uint32_t)c * (L.records() ? L.Ls : L.N5) * 16u; }
+    __device__ static void load(const Buf &b, Lay L, uint32_t i, uint32_t s, cx<T> v[12])
     {
 #pragma unroll
         for (int c = 0; c < 12; ++c) {
-            double2 t = __builtin_bit_cast(double2, b.ld16(k * 16u, (uint32_t)c * N5 * 16u));
+            double2 t = __builtin_bit_cast(double2, b.ld16(site_off(L, i, s), chunk_off(L, c)));
             v[c] = {t.x, t.y};
         }
     }
-    __device__ static void store(const Buf &b, uint32_t N5, uint32_t k, const cx<T> v[12])
+    __device__ static void store(const Buf &b, Lay L, uint32_t i, uint32_t s, const cx<T> v[12])
     {
 #pragma unroll
         for (int c = 0; c < 12; ++c)
-            b.st16(__builtin_bit_cast(u32x4, make_double2(v[c].r, v[c].i)), k * 16u,
-                   (uint32_t)c * N5 * 16u);
+            b.st16(__builtin_bit_cast(u32x4, make_double2(v[c].r, v[c].i)), site_off(L, i, s),
+                   chunk_off(L, c));
     }
-    __device__ static double store_norm2_q(const Buf &b, uint32_t N5, uint32_t k, cx<T> v[12])
+    __device__ static double store_norm2_q(const Buf &b, Lay L, uint32_t i, uint32_t s, cx<T> v[12])
     {
-        return store_norm2(b, N5, k, v);
+        return store_norm2(b, L, i, s, v);
     }
-    __device__ static double store_norm2(const Buf &b, uint32_t N5, uint32_t k, const cx<T> v[12])
+    __device__ static double store_norm2(const Buf &b, Lay L, uint32_t i, uint32_t s, const cx<T> v[12])
     {
-        store(b, N5, k, v);
+        store(b, L, i, s, v);
         double n = 0;
 #pragma unroll
         for (int c = 0; c < 12; ++c) n += (double)v[c].r * v[c].r + (double)v[c].i * v[c].i;
@@ -196,30 +205,33 @@ template <>
 struct Spin<MOBIUS_F32> {
     using T = float;
     __host__ __device__ static int64_t bytes(int64_t N5) { return N5 * 96; }
-    __device__ static void load(const Buf &b, uint32_t N5, uint32_t k, cx<T> v[12])
+    // lane offset of slice s of packed site i, and uniform offset of chunk c
+    __device__ static uint32_t site_off(Lay L, uint32_t i, uint32_t s) { return i * (L.Ls * (L.records() ? 96u : 16u)) + s * 16u; }
+    __device__ static uint32_t chunk_off(Lay L, int c) { return (uint32_t)c * (L.records() ? L.Ls : L.N5) * 16u; }
+    __device__ static void load(const Buf &b, Lay L, uint32_t i, uint32_t s, cx<T> v[12])
     {
 #pragma unroll
         for (int c = 0; c < 6; ++c) {
-            float4 t = __builtin_bit_cast(float4, b.ld16(k * 16u, (uint32_t)c * N5 * 16u));
+            float4 t = __builtin_bit_cast(float4, b.ld16(site_off(L, i, s), chunk_off(L, c)));
             v[2 * c] = {t.x, t.y};
             v[2 * c + 1] = {t.z, t.w};
         }
     }
-    __device__ static void store(const Buf &b, uint32_t N5, uint32_t k, const cx<T> v[12])
+    __device__ static void store(const Buf &b, Lay L, uint32_t i, uint32_t s, const cx<T> v[12])
     {
 #pragma unroll
         for (int c = 0; c < 6; ++c)
             b.st16(__builtin_bit_cast(u32x4, make_float4(v[2 * c].r, v[2 * c].i, v[2 * c + 1].r,
                                                          v[2 * c + 1].i)),
-                   k * 16u, (uint32_t)c * N5 * 16u);
+                   site_off(L, i, s), chunk_off(L, c));
     }
-    __device__ static double store_norm2_q(const Buf &b, uint32_t N5, uint32_t k, cx<T> v[12])
+    __device__ static double store_norm2_q(const Buf &b, Lay L, uint32_t i, uint32_t s, cx<T> v[12])
     {
-        return store_norm2(b, N5, k, v);
+        return store_norm2(b, L, i, s, v);
     }
-    __device__ static double store_norm2(const Buf &b, uint32_t N5, uint32_t k, const cx<T> v[12])
+    __device__ static double store_norm2(const Buf &b, Lay L, uint32_t i, uint32_t s, const cx<T> v[12])
     {
-        store(b, N5, k, v);
+        store(b, L, i, s, v);
         double n = 0;
 #pragma unroll
         for (int c = 0; c < 12; ++c) n += (double)v[c].r * v[c].r + (double)v[c].i * v[c].i;
@@ -231,12 +243,15 @@ template <>
 struct Spin<MOBIUS_F16> {
     using T = float;
     __host__ __device__ static int64_t bytes(int64_t N5) { return N5 * 52; }
-    __device__ static void load(const Buf &b, uint32_t N5, uint32_t k, cx<T> v[12])
+    __device__ static uint32_t site_off(Lay L, uint32_t i, uint32_t s) { return (i * L.Ls + s) * 16u; }
+    __device__ static uint32_t chunk_off(Lay L, int c) { return (uint32_t)c * L.N5 * 16u; }
+    __device__ static uint32_t norm_off(Lay L, uint32_t i, uint32_t s) { return (i * L.Ls + s) * 4u; }
+    __device__ static void load(const Buf &b, Lay L, uint32_t i, uint32_t s, cx<T> v[12])
     {
-        const float nrm = __builtin_bit_cast(float, b.ld4(k * 4u, 3u * N5 * 16u));
+        const float nrm = __builtin_bit_cast(float, b.ld4(norm_off(L, i, s), 3u * L.N5 * 16u));
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-            half8 t = __builtin_bit_cast(half8, b.ld16(k * 16u, (uint32_t)c * N5 * 16u));
+            half8 t = __builtin_bit_cast(half8, b.ld16(site_off(L, i, s), chunk_off(L, c)));
 #pragma unroll
             for (int j = 0; j < 4; ++j)
                 v[4 * c + j] = {nrm * (float)t[2 * j], nrm * (float)t[2 * j + 1]};
@@ -264,23 +279,23 @@ struct Spin<MOBIUS_F16> {
             }
         return m;
     }
-    __device__ static void store(const Buf &b, uint32_t N5, uint32_t k, const cx<T> v[12])
+    __device__ static void store(const Buf &b, Lay L, uint32_t i, uint32_t s, const cx<T> v[12])
     {
         half8 h[3];
         const float m = encode(v, h);
 #pragma unroll
-        for (int c = 0; c < 3; ++c) b.st16(__builtin_bit_cast(u32x4, h[c]), k * 16u, (uint32_t)c * N5 * 16u);
-        b.st4(__builtin_bit_cast(uint32_t, m), k * 4u, 3u * N5 * 16u);
+        for (int c = 0; c < 3; ++c) b.st16(__builtin_bit_cast(u32x4, h[c]), site_off(L, i, s), chunk_off(L, c));
+        b.st4(__builtin_bit_cast(uint32_t, m), norm_off(L, i, s), 3u * L.N5 * 16u);
     }
     // store, return |stored value|^2 and replace v by the stored value (what a
     // later load returns), all from the encoded registers
-    __device__ static double store_norm2_q(const Buf &b, uint32_t N5, uint32_t k, cx<T> v[12])
+    __device__ static double store_norm2_q(const Buf &b, Lay L, uint32_t i, uint32_t s, cx<T> v[12])
     {
         half8 h[3];
         const float m = encode(v, h);
 #pragma unroll
-        for (int c = 0; c < 3; ++c) b.st16(__builtin_bit_cast(u32x4, h[c]), k * 16u, (uint32_t)c * N5 * 16u);
-        b.st4(__builtin_bit_cast(uint32_t, m), k * 4u, 3u * N5 * 16u);
+        for (int c = 0; c < 3; ++c) b.st16(__builtin_bit_cast(u32x4, h[c]), site_off(L, i, s), chunk_off(L, c));
+        b.st4(__builtin_bit_cast(uint32_t, m), norm_off(L, i, s), 3u * L.N5 * 16u);
         double n = 0;
 #pragma unroll
         for (int c = 0; c < 3; ++c)
@@ -292,27 +307,27 @@ struct Spin<MOBIUS_F16> {
         return n;
     }
     // store, and return |stored value|^2 computed from the encoded registers
-    __device__ static double store_norm2(const Buf &b, uint32_t N5, uint32_t k, const cx<T> v[12])
+    __device__ static double store_norm2(const Buf &b, Lay L, uint32_t i, uint32_t s, const cx<T> v[12])
     {
         half8 h[3];
         const float m = encode(v, h);
 #pragma unroll
-        for (int c = 0; c < 3; ++c) b.st16(__builtin_bit_cast(u32x4, h[c]), k * 16u, (uint32_t)c * N5 * 16u);
-        b.st4(__builtin_bit_cast(uint32_t, m), k * 4u, 3u * N5 * 16u);
+        for (int c = 0; c < 3; ++c) b.st16(__builtin_bit_cast(u32x4, h[c]), site_off(L, i, s), chunk_off(L, c));
+        b.st4(__builtin_bit_cast(uint32_t, m), norm_off(L, i, s), 3u * L.N5 * 16u);
         // m^2 sum h^2: the binary16 squares are exact in FP32 and the 24 of
         // them (each <= 1) are summed by packed dot products with an FP32
         // accumulator (relative rounding below 24 ulp of FP32), then scaled
         // by m^2 in FP64
-        float s = 0.f;
+        float sum = 0.f;
 #pragma unroll
         for (int c = 0; c < 3; ++c)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const half2v p = {h[c][2 * j], h[c][2 * j + 1]};
-                s = __builtin_amdgcn_fdot2(p, p, s, false);
+                sum = __builtin_amdgcn_fdot2(p, p, sum, false);
             }
         const double md = (double)m;
-        return md * md * (double)s;
+        return md * md * (double)sum;
     }
 };
 
@@ -858,12 +873,12 @@ struct RawH {
     float n;       // per-site norm
 };
 
-__device__ __forceinline__ void load_raw_f16(const Buf &b, uint32_t N5, uint32_t k, RawH &r)
+__device__ __forceinline__ void load_raw_f16(const Buf &b, Lay L, uint32_t i, uint32_t s, RawH &r)
 {
-    r.n = __builtin_bit_cast(float, b.ld4(k * 4u, 3u * N5 * 16u));
+    r.n = __builtin_bit_cast(float, b.ld4(Spin<MOBIUS_F16>::norm_off(L, i, s), 3u * L.N5 * 16u));
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
-        const half8 t = __builtin_bit_cast(half8, b.ld16(k * 16u, (uint32_t)q * N5 * 16u));
+        const half8 t = __builtin_bit_cast(half8, b.ld16(Spin<MOBIUS_F16>::site_off(L, i, s), Spin<MOBIUS_F16>::chunk_off(L, q)));
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             half2v h;

@@ -62,11 +62,10 @@ __device__ __forceinline__ void force_dir(const ForceParams &fp, const SiteMap &
                                           uint32_t jn, ForceLds &lds)
 {
     using S = Spin<MOBIUS_F64>;
-    const uint32_t N5 = (uint32_t)fp.N5;
     const int64_t fb = S::bytes(fp.N5);
     cx<double> Ln[12], Rn[12];
-    S::load(Buf(fp.Ln, fb), N5, jn, Ln);
-    S::load(Buf(fp.Rn, fb), N5, jn, Rn);
+    S::load(Buf(fp.Ln, fb), Lay{(uint32_t)fp.Ls, (uint32_t)fp.N5}, jn, (uint32_t)m.s, Ln);
+    S::load(Buf(fp.Rn, fb), Lay{(uint32_t)fp.Ls, (uint32_t)fp.N5}, jn, (uint32_t)m.s, Rn);
     mix_s(Rn, mix_w(k, false, m, fp.Ls, false), k.mf, m, fp.Ls, false);  // B R_{1-p}(y + mu)
 
     cx<double> hL[6], hR[6], c[9];
@@ -126,19 +125,17 @@ __global__ __launch_bounds__(BLOCK) void force_kernel(ForceParams fp)
     using S = Spin<MOBIUS_F64>;
     const SiteMap m = site_map(fp.Ls, fp.spw, fp.Vh);
     const Coef<double> k = make_coef<double>(fp.c);
-    const uint32_t N5 = (uint32_t)fp.N5;
     const int64_t fb = S::bytes(fp.N5);
-    const uint32_t k5 = (uint32_t)m.i * (uint32_t)fp.Ls + (uint32_t)m.s;
     cx<double> Lo[12], BRo[12];
-    S::load(Buf(fp.Lp, fb), N5, k5, Lo);
-    S::load(Buf(fp.Rp, fb), N5, k5, BRo);
+    S::load(Buf(fp.Lp, fb), Lay{(uint32_t)fp.Ls, (uint32_t)fp.N5}, (uint32_t)m.i, (uint32_t)m.s, Lo);
+    S::load(Buf(fp.Rp, fb), Lay{(uint32_t)fp.Ls, (uint32_t)fp.N5}, (uint32_t)m.i, (uint32_t)m.s, BRo);
     mix_s(BRo, mix_w(k, false, m, fp.Ls, false), k.mf, m, fp.Ls, false);  // B R_p(y)
     const int32_t *nb = fp.nbr + m.i * 8;
     __shared__ ForceLds lds;
-    force_dir<0>(fp, m, k, Lo, BRo, (uint32_t)nb[0] * (uint32_t)fp.Ls + (uint32_t)m.s, lds);
-    force_dir<1>(fp, m, k, Lo, BRo, (uint32_t)nb[1] * (uint32_t)fp.Ls + (uint32_t)m.s, lds);
-    force_dir<2>(fp, m, k, Lo, BRo, (uint32_t)nb[2] * (uint32_t)fp.Ls + (uint32_t)m.s, lds);
-    force_dir<3>(fp, m, k, Lo, BRo, (uint32_t)nb[3] * (uint32_t)fp.Ls + (uint32_t)m.s, lds);
+    force_dir<0>(fp, m, k, Lo, BRo, (uint32_t)nb[0], lds);
+    force_dir<1>(fp, m, k, Lo, BRo, (uint32_t)nb[1], lds);
+    force_dir<2>(fp, m, k, Lo, BRo, (uint32_t)nb[2], lds);
+    force_dir<3>(fp, m, k, Lo, BRo, (uint32_t)nb[3], lds);
 }
 
 // Lie-algebra force per link: F = TA(U G^+), TA(M) = (M - M^+)/2 - tr(M - M^+)/6,

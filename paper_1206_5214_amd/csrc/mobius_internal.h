@@ -24,14 +24,26 @@ namespace mobius {
 // canon_of[p][i] is the canonical 4d index (x fastest, then y, z, t) of packed
 // site i of parity p.  5d sites are Ls-inner: site5 = i * Ls + s.
 //
-// Spinor field of one parity, storage precision P, is a structure of arrays
-// of 16-byte chunks over site5:
+// Spinor field of one parity, storage precision P, 16-byte chunks of the 12
+// components (spin * 3 + colour) of a 5d site:
 //   F64: 12 chunks (one complex each)            -> 192 B / site5
 //   F32:  6 chunks (two complex each)            ->  96 B / site5
 //   F16:  3 chunks (four complex each, binary16) + one FP32 norm per site5
 //                                                ->  52 B / site5
-// chunk c of site5 k lives at base + (c * N5 + k) * 16; the F16 norms follow
-// the chunks at base + CH * N5 * 16.  Component order is spin * 3 + colour.
+// F64 and F32 with Ls divisible by 4: one record per 4d site i, a structure of
+// arrays over its slices; chunk c of slice s lives at base + i * (Ls * W) +
+// (c * Ls + s) * 16, W the bytes per site5.  A neighbour's slices are then one
+// stretch of memory (24^3 x 64, Ls = 12, FP64: eighteen whole cache lines) instead
+// of twelve pieces of a line and a half each, N5 * 16 bytes apart: hops 5 to 11 %
+// (FP64) and 3 to 6 % (FP32) faster there (FP64 adjoint hop 791 to 711 us, D_pre
+// 1956 to 1846 us).
+// F16, and the others where a piece of Ls * 16 bytes is no whole number of 64-byte
+// sectors: one structure of arrays over all 5d sites; chunk c of site5 k = i * Ls + s
+// at base + (c * N5 + k) * 16, the F16 norms behind the chunks at base + 3 * N5 * 16.
+// (In records such pieces share sectors, which costs the stores more than the loads
+// gain: 24^3 x 32, FP64 D_pre^+ at Ls = 5 566 to 674 us, Ls = 7 754 to 808 us, Ls = 10
+// 951 to 942 us; FP32 265 to 314, 349 to 393, 450 to 464 us; FP16, whose records of
+// 52 Ls bytes are never aligned, D_pre at 24^3 x 64, Ls = 12 565 to 592 us.)
 //
 // Links: for output parity p, 8 directions d: d < 4 is U_d(x), d >= 4 is
 // U_{d-4}(x - d^) (undaggered; the kernel applies the dagger), x the packed

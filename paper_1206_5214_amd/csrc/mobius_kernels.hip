@@ -68,7 +68,8 @@ __device__ __forceinline__ void hop_epilogue(const HopParams &hp, const SiteMap 
     using T = typename S::T;
     extern __shared__ u32x4 dyn_lds[];
     const int Ls = hp.Ls;
-    const uint32_t N5 = (uint32_t)hp.N5, k5 = (uint32_t)m.i * (uint32_t)Ls + (uint32_t)m.s;
+    const uint32_t i5 = (uint32_t)m.i, s5 = (uint32_t)m.s;
+    const Lay lay{(uint32_t)Ls, (uint32_t)hp.N5};
     const int64_t fbytes = S::bytes(hp.N5);
     const Buf bout(hp.out + r * hp.fstride, fbytes);
     const char *xr = hp.x ? hp.x + r * hp.fstride : nullptr;
@@ -84,7 +85,7 @@ __device__ __forceinline__ void hop_epilogue(const HopParams &hp, const SiteMap 
     }
     if constexpr ((EPI & EPI_M5ADD) != 0) {
         cx<T> yv[12];
-        S::load(Buf(yr, fbytes), N5, k5, yv);
+        S::load(Buf(yr, fbytes), lay, i5, s5, yv);
         mix_s(yv, mix_w(k, true, m, Ls, DAG), k.mf, m, Ls, DAG);  // I y = M+ y + M- C5 y
         // (I y rounded before the sum in every variant, which contracting the
         // products into it would leave to the compiler)
@@ -95,7 +96,7 @@ __device__ __forceinline__ void hop_epilogue(const HopParams &hp, const SiteMap 
     }
     if constexpr ((EPI & EPI_M5SUB) != 0) {
         cx<T> yv[12];
-        S::load(Buf(yr, fbytes), N5, k5, yv);
+        S::load(Buf(yr, fbytes), lay, i5, s5, yv);
         mix_s(yv, mix_w(k, true, m, Ls, DAG), k.mf, m, Ls, DAG);  // I y (I^+ y)
 #pragma unroll
         for (int c = 0; c < 12; ++c) pin(yv[c]);
@@ -104,7 +105,7 @@ __device__ __forceinline__ void hop_epilogue(const HopParams &hp, const SiteMap 
     }
     if constexpr ((EPI & EPI_PRESUB) != 0) {
         cx<T> xv[12];
-        S::load(Buf(xr, fbytes), N5, k5, xv);
+        S::load(Buf(xr, fbytes), lay, i5, s5, xv);
 #pragma unroll
         for (int c = 0; c < 12; ++c) acc[c] = xv[c] - acc[c];
     }
@@ -119,14 +120,14 @@ __device__ __forceinline__ void hop_epilogue(const HopParams &hp, const SiteMap 
         mix_s(acc, mix_w(k, false, m, Ls, DAG), k.mf, m, Ls, DAG);
     if constexpr ((EPI & EPI_POSTSUB) != 0) {
         cx<T> xv[12];
-        S::load(Buf(xr, fbytes), N5, k5, xv);
+        S::load(Buf(xr, fbytes), lay, i5, s5, xv);
 #pragma unroll
         for (int c = 0; c < 12; ++c) acc[c] = xv[c] - acc[c];
     }
     if constexpr ((EPI & EPI_NORM) != 0) {
         // |stored value|^2, from the encoded registers
         double n = 0;
-        if (m.site_ok) n = S::store_norm2(bout, N5, k5, acc);
+        if (m.site_ok) n = S::store_norm2(bout, lay, i5, s5, acc);
         if constexpr (WAVE_ONLY) {
             n = wave_sum(n);
             if (m.lane == 0) hp.partials[r * hp.pstride + lb] = n;
@@ -134,7 +135,7 @@ __device__ __forceinline__ void hop_epilogue(const HopParams &hp, const SiteMap 
             block_sum_store(n, hp.partials + r * hp.pstride, lb);
         }
     } else {
-        if (m.site_ok) S::store(bout, N5, k5, acc);
+        if (m.site_ok) S::store(bout, lay, i5, s5, acc);
     }
 }
 
@@ -152,8 +153,9 @@ __device__ __forceinline__ void hop_block(const HopParams &hp, int64_t lb, int r
     const SiteMap m = site_map_lb(hp.Ls, hp.spw, hp.Vh, lb);
     const Coef<T> k = make_coef<T>(hp.c);
     const int Ls = hp.Ls;
-    const uint32_t Vh = (uint32_t)hp.Vh, N5 = (uint32_t)hp.N5;
-    const uint32_t i = (uint32_t)m.i;
+    const uint32_t Vh = (uint32_t)hp.Vh;
+    const uint32_t i = (uint32_t)m.i, s5 = (uint32_t)m.s;
+    const Lay lay{(uint32_t)Ls, (uint32_t)hp.N5};
     const int64_t fbytes = S::bytes(hp.N5);
     const Buf blink(hp.links, (int64_t)8 * hp.Vh * Link<P>::REC);
     const Buf bnbr(hp.nbr, 8 * hp.Vh * 4);
@@ -214,8 +216,8 @@ __device__ __forceinline__ void hop_block(const HopParams &hp, int64_t lb, int r
         const u32x4 n0 = bnbr.ld16(i * 32u, 0u), n1 = bnbr.ld16(i * 32u + 16u, 0u);
 #pragma unroll
         for (int d = 0; d < 4; ++d) {
-            jn[d] = n0[d] * (uint32_t)Ls + (uint32_t)m.s;
-            jn[4 + d] = n1[d] * (uint32_t)Ls + (uint32_t)m.s;
+            jn[d] = n0[d];
+            jn[4 + d] = n1[d];
         }
     }
 
@@ -247,9 +249,9 @@ __device__ __forceinline__ void hop_block(const HopParams &hp, int64_t lb, int r
         RawH nx, nx2;
         LinkH2 unx;
         LinkRows rnx;
-        load_raw_f16(bin, N5, jn[HOP_DIR[0]], nx);
+        load_raw_f16(bin, lay, jn[HOP_DIR[0]], s5, nx);
         if constexpr (MF) {
-            load_raw_f16(bin, N5, jn[HOP_DIR[1]], nx2);
+            load_raw_f16(bin, lay, jn[HOP_DIR[1]], s5, nx2);
             ls.get_rows(HOP_DIR[0], quad, rnx);
         } else if constexpr (PF >= 2) {
             ls.template get_h2<(HOP_DIR[0] < 4)>(HOP_DIR[0], unx);
@@ -260,9 +262,9 @@ __device__ __forceinline__ void hop_block(const HopParams &hp, int64_t lb, int r
             const RawH o = nx;
             if constexpr (MF) {
                 nx = nx2;
-                if (q < 6) load_raw_f16(bin, N5, jn[d2], nx2);
+                if (q < 6) load_raw_f16(bin, lay, jn[d2], s5, nx2);
             } else {
-                if (q < 7) load_raw_f16(bin, N5, jn[d1], nx);
+                if (q < 7) load_raw_f16(bin, lay, jn[d1], s5, nx);
             }
             LinkH2 u;
             LinkRows ur;
@@ -311,7 +313,7 @@ __device__ __forceinline__ void hop_block(const HopParams &hp, int64_t lb, int r
         }
     } else {
     cx<T> nxt[12], unx[9];
-    if constexpr (PF >= 1) S::load(bin, N5, jn[HOP_DIR[0]], nxt);
+    if constexpr (PF >= 1) S::load(bin, lay, jn[HOP_DIR[0]], s5, nxt);
     if constexpr (PF >= 2) ls.get(HOP_DIR[0], unx);
 
 #pragma unroll
@@ -321,9 +323,9 @@ __device__ __forceinline__ void hop_block(const HopParams &hp, int64_t lb, int r
         if constexpr (PF >= 1) {
 #pragma unroll
             for (int c = 0; c < 12; ++c) chi[c] = nxt[c];
-            if (q < 7) S::load(bin, N5, jn[d1], nxt);
+            if (q < 7) S::load(bin, lay, jn[d1], s5, nxt);
         } else {
-            S::load(bin, N5, jn[d], chi);
+            S::load(bin, lay, jn[d], s5, chi);
         }
         if constexpr (PF >= 2) {
 #pragma unroll
@@ -396,11 +398,12 @@ __device__ __forceinline__ void hop_two_dirs(const HopParams &hp, const SiteMap 
     constexpr int S0 = D0 < 4 ? SF : -SF, S1 = D1 < 4 ? SF : -SF;
     constexpr bool MIXIN = !DAG && (EPI & EPI_PREMIXED) == 0;
     const int Ls = hp.Ls;
-    const uint32_t Vh = (uint32_t)hp.Vh, N5 = (uint32_t)hp.N5, i = (uint32_t)m.i;
+    const uint32_t Vh = (uint32_t)hp.Vh, i = (uint32_t)m.i, s5 = (uint32_t)m.s;
+    const Lay lay{(uint32_t)Ls, (uint32_t)hp.N5};
     const Buf bnbr(hp.nbr, 8 * hp.Vh * 4), blink(hp.links, (int64_t)8 * hp.Vh * Link<P>::REC);
     const Buf bin(hp.in + r * hp.fstride, S::bytes(hp.N5));
-    const uint32_t j0 = bnbr.ld4(i * 32u + 4u * D0, 0u) * (uint32_t)Ls + (uint32_t)m.s;
-    const uint32_t j1 = bnbr.ld4(i * 32u + 4u * D1, 0u) * (uint32_t)Ls + (uint32_t)m.s;
+    const uint32_t j0 = bnbr.ld4(i * 32u + 4u * D0, 0u);
+    const uint32_t j1 = bnbr.ld4(i * 32u + 4u * D1, 0u);
     const Coef<T> k = make_coef<T>(hp.c);
     const MixW<T> wB = mix_w(k, false, m, Ls, false);
     if constexpr (P == MOBIUS_F16) {
@@ -426,8 +429,8 @@ __device__ __forceinline__ void hop_two_dirs(const HopParams &hp, const SiteMap 
             ls.template get_h2<(D1 < 4)>(D1, u1);
         }
         RawH o0, o1;
-        load_raw_f16(bin, N5, j0, o0);
-        load_raw_f16(bin, N5, j1, o1);
+        load_raw_f16(bin, lay, j0, s5, o0);
+        load_raw_f16(bin, lay, j1, s5, o1);
         const float wu = MIXIN ? (float)wB.bu * (m.s == 0 ? -(float)k.mf : 1.f) : 0.f;
         const float wl = MIXIN ? (float)wB.bl * (m.s == Ls - 1 ? -(float)k.mf : 1.f) : 0.f;
         half2v h0[6], h1[6];
@@ -450,8 +453,8 @@ __device__ __forceinline__ void hop_two_dirs(const HopParams &hp, const SiteMap 
         cx<T> c0[12], c1[12], u0[9], u1[9];
         load_link<P>(blink, Vh, D0, i, u0);
         load_link<P>(blink, Vh, D1, i, u1);
-        S::load(bin, N5, j0, c0);
-        S::load(bin, N5, j1, c1);
+        S::load(bin, lay, j0, s5, c0);
+        S::load(bin, lay, j1, s5, c1);
         if constexpr (MIXIN) mix_s(c0, wB, k.mf, m, Ls, false);
         hop_dir_w<P, (D0 & 3), (D0 < 4), S0>(c0, u0, w[0]);
         if constexpr (MIXIN) mix_s(c1, wB, k.mf, m, Ls, false);
@@ -757,17 +760,16 @@ __global__ __launch_bounds__(BLOCK) void m5_kernel(const char *in, char *out, in
     using T = typename S::T;
     const SiteMap m = site_map(Ls, spw, Vh);
     const Coef<T> k = make_coef<T>(c);
-    const uint32_t k5 = (uint32_t)m.i * (uint32_t)Ls + (uint32_t)m.s;
     const int64_t fbytes = S::bytes(N5);
     cx<T> v[12];
-    S::load(Buf(in, fbytes), (uint32_t)N5, k5, v);
+    S::load(Buf(in, fbytes), Lay{(uint32_t)Ls, (uint32_t)N5}, (uint32_t)m.i, (uint32_t)m.s, v);
     if constexpr (KIND == 0) {
         mix_s(v, mix_w(k, true, m, Ls, DAG), k.mf, m, Ls, DAG);
     } else {
         __shared__ M5Lds<T> lds;
         m5inv_lanes(v, k, m, Ls, DAG, lds);
     }
-    if (m.site_ok) S::store(Buf(out, fbytes), (uint32_t)N5, k5, v);
+    if (m.site_ok) S::store(Buf(out, fbytes), Lay{(uint32_t)Ls, (uint32_t)N5}, (uint32_t)m.i, (uint32_t)m.s, v);
 }
 
 // ---------------------------------------------------------------------------
@@ -937,7 +939,7 @@ struct PackLds {
 
 struct PackMap {
     int p;
-    int64_t k5;  // packed 5d site of this lane
+    uint32_t i, s;  // packed 4d site and slice of this lane
     bool ok;
 };
 
@@ -947,13 +949,11 @@ __device__ __forceinline__ PackMap pack_map(int64_t Vh, int Ls, const int32_t *c
     const int64_t lb = logical_block(1);
     PackMap m;
     m.p = (int)(lb & 1);
-    m.k5 = (lb >> 1) * PACK_BLOCK + threadIdx.x;
-    m.ok = m.k5 < Vh * Ls;
-    int64_t rec = -1;
-    if (m.ok) {
-        const uint32_t i = (uint32_t)m.k5 / (uint32_t)Ls, s = (uint32_t)m.k5 - i * (uint32_t)Ls;
-        rec = (int64_t)s * 2 * Vh + canon_of[m.p * Vh + i];
-    }
+    const int64_t k5 = (lb >> 1) * PACK_BLOCK + threadIdx.x;
+    m.ok = k5 < Vh * Ls;
+    m.i = (uint32_t)k5 / (uint32_t)Ls;
+    m.s = (uint32_t)k5 - m.i * (uint32_t)Ls;
+    const int64_t rec = m.ok ? (int64_t)m.s * 2 * Vh + canon_of[m.p * Vh + m.i] : -1;
     lds.rec[threadIdx.x] = rec;
     return m;
 }
@@ -988,8 +988,7 @@ __global__ __launch_bounds__(PACK_BLOCK) void pack_spinor_kernel(int64_t Vh, int
     cx<T> v[12];
 #pragma unroll
     for (int c = 0; c < 12; ++c) v[c] = lds.v[threadIdx.x * PackLds<T>::STRIDE + c];
-    S::store(Buf((m.p == 0 ? even : odd) + blockIdx.y * S::bytes(N5), S::bytes(N5)), (uint32_t)N5,
-             (uint32_t)m.k5, v);
+    S::store(Buf((m.p == 0 ? even : odd) + blockIdx.y * S::bytes(N5), S::bytes(N5)), Lay{(uint32_t)Ls, (uint32_t)N5}, m.i, m.s, v);
 }
 
 template <int P>
@@ -1006,8 +1005,7 @@ __global__ __launch_bounds__(PACK_BLOCK) void unpack_spinor_kernel(int64_t Vh, i
     canon += (int64_t)blockIdx.y * 2 * N5 * 12;
     if (m.ok) {
         cx<T> v[12];
-        S::load(Buf((m.p == 0 ? even : odd) + blockIdx.y * S::bytes(N5), S::bytes(N5)), (uint32_t)N5,
-                (uint32_t)m.k5, v);
+        S::load(Buf((m.p == 0 ? even : odd) + blockIdx.y * S::bytes(N5), S::bytes(N5)), Lay{(uint32_t)Ls, (uint32_t)N5}, m.i, m.s, v);
 #pragma unroll
         for (int c = 0; c < 12; ++c) lds.v[threadIdx.x * PackLds<T>::STRIDE + c] = v[c];
     }
@@ -1086,6 +1084,17 @@ __device__ __forceinline__ bool sys_inactive(const VecSys &v, const int32_t *act
 {
     return v.flag >= 0 && active && active[v.flag] == 0;
 }
+
+// 5d site k of a system in the order of the packed records: slice s of site i
+struct Slice5 {
+    Lay lay;
+    uint32_t i, s;
+    __device__ __forceinline__ Slice5(const VecSys &v, int64_t k) : lay{(uint32_t)v.Ls, (uint32_t)v.N5}
+    {
+        i = (uint32_t)k / lay.Ls;
+        s = (uint32_t)k - i * lay.Ls;
+    }
+};
 
 // The CG scalars.  The kernel that needs beta or alpha sums the norm it depends
 // on itself, every workgroup the same partial sums in the same order, and its
@@ -1176,11 +1185,11 @@ __global__ __launch_bounds__(BLAS_BLOCK) void cg_xr_batch(const VecSys *sys, con
     if ((int64_t)blockIdx.x * BLAS_BLOCK >= v.N5) return;
     const bool ok = k < v.N5;
     const int64_t fb = S::bytes(v.N5);
-    const uint32_t n5 = (uint32_t)v.N5, kk = (uint32_t)(ok ? k : v.N5 - 1);
+    const Slice5 z(v, ok ? k : v.N5 - 1);
     const Buf bx(v.a, SX::bytes(v.N5)), bp(v.b, fb), br(v.c, fb), bq(v.d, fb);
     cx<T> rv[12], qv[12];
-    S::load(br, n5, kk, rv);
-    S::load(bq, n5, kk, qv);
+    S::load(br, z.lay, z.i, z.s, rv);
+    S::load(bq, z.lay, z.i, z.s, qv);
     const double alpha = cg_alpha(v, restart, slot);
     double n = 0;
     if (ok) {
@@ -1189,15 +1198,15 @@ __global__ __launch_bounds__(BLAS_BLOCK) void cg_xr_batch(const VecSys *sys, con
             const TX alx = (TX)alpha;
             cx<TX> xv[12];
             cx<T> pv[12];
-            SX::load(bx, n5, kk, xv);
-            S::load(bp, n5, kk, pv);
+            SX::load(bx, z.lay, z.i, z.s, xv);
+            S::load(bp, z.lay, z.i, z.s, pv);
 #pragma unroll
             for (int c = 0; c < 12; ++c) xv[c] = xv[c] + alx * cx<TX>{(TX)pv[c].r, (TX)pv[c].i};
-            SX::store(bx, n5, kk, xv);
+            SX::store(bx, z.lay, z.i, z.s, xv);
         }
 #pragma unroll
         for (int c = 0; c < 12; ++c) rv[c] = rv[c] - al * qv[c];
-        n = S::store_norm2(br, n5, kk, rv);
+        n = S::store_norm2(br, z.lay, z.i, z.s, rv);
     }
     block_sum_store(n, v.partials, blockIdx.x);
 }
@@ -1216,16 +1225,16 @@ __global__ __launch_bounds__(BLAS_BLOCK) void axpby_batch(const VecSys *sys, con
     if (k < v.N5) {
         const T av = v.s0 ? (T)*v.s0 : (T)1, bv = v.s1 ? (T)*v.s1 : (T)1;
         const int64_t fb = S::bytes(v.N5);
-        const uint32_t n5 = (uint32_t)v.N5, kk = (uint32_t)k;
+        const Slice5 z(v, k);
         cx<T> xv[12], yv[12];
-        S::load(Buf(v.a, fb), n5, kk, xv);
-        S::load(Buf(v.b, fb), n5, kk, yv);
+        S::load(Buf(v.a, fb), z.lay, z.i, z.s, xv);
+        S::load(Buf(v.b, fb), z.lay, z.i, z.s, yv);
 #pragma unroll
         for (int c = 0; c < 12; ++c) xv[c] = av * xv[c] + bv * yv[c];
         if constexpr (NORM)
-            n = S::store_norm2(Buf(v.d, fb), n5, kk, xv);
+            n = S::store_norm2(Buf(v.d, fb), z.lay, z.i, z.s, xv);
         else
-            S::store(Buf(v.d, fb), n5, kk, xv);
+            S::store(Buf(v.d, fb), z.lay, z.i, z.s, xv);
     }
     if constexpr (NORM) block_sum_store(n, v.partials, blockIdx.x);
 }
@@ -1242,8 +1251,9 @@ __global__ __launch_bounds__(BLAS_BLOCK) void norm2_batch(const VecSys *sys, con
     const int64_t k = (int64_t)blockIdx.x * BLAS_BLOCK + threadIdx.x;
     double n = 0;
     if (k < v.N5) {
+        const Slice5 z(v, k);
         cx<T> x[12];
-        S::load(Buf(v.a, S::bytes(v.N5)), (uint32_t)v.N5, (uint32_t)k, x);
+        S::load(Buf(v.a, S::bytes(v.N5)), z.lay, z.i, z.s, x);
         n = site_norm2(x);
     }
     block_sum_store(n, v.partials, blockIdx.x);
@@ -1257,12 +1267,13 @@ __global__ __launch_bounds__(BLAS_BLOCK) void convert_batch(const VecSys *sys, c
     if (sys_inactive(v, active)) return;
     const int64_t k = (int64_t)blockIdx.x * BLAS_BLOCK + threadIdx.x;
     if (k >= v.N5) return;
+    const Slice5 z(v, k);
     cx<typename Spin<PI>::T> x[12];
-    Spin<PI>::load(Buf(v.a, Spin<PI>::bytes(v.N5)), (uint32_t)v.N5, (uint32_t)k, x);
+    Spin<PI>::load(Buf(v.a, Spin<PI>::bytes(v.N5)), z.lay, z.i, z.s, x);
     cx<typename Spin<PO>::T> w[12];
 #pragma unroll
     for (int c = 0; c < 12; ++c) w[c] = {(typename Spin<PO>::T)x[c].r, (typename Spin<PO>::T)x[c].i};
-    Spin<PO>::store(Buf(v.b, Spin<PO>::bytes(v.N5)), (uint32_t)v.N5, (uint32_t)k, w);
+    Spin<PO>::store(Buf(v.b, Spin<PO>::bytes(v.N5)), z.lay, z.i, z.s, w);
 }
 
 template <int PI>
@@ -1272,19 +1283,20 @@ __global__ __launch_bounds__(BLAS_BLOCK) void accumulate_batch(const VecSys *sys
     if (sys_inactive(v, active)) return;
     const int64_t k = (int64_t)blockIdx.x * BLAS_BLOCK + threadIdx.x;
     if (k >= v.N5) return;
+    const Slice5 z(v, k);
     cx<typename Spin<PI>::T> x[12];
-    Spin<PI>::load(Buf(v.a, Spin<PI>::bytes(v.N5)), (uint32_t)v.N5, (uint32_t)k, x);
+    Spin<PI>::load(Buf(v.a, Spin<PI>::bytes(v.N5)), z.lay, z.i, z.s, x);
     cx<double> h[12];
     const Buf bh(v.d, Spin<MOBIUS_F64>::bytes(v.N5));
-    Spin<MOBIUS_F64>::load(bh, (uint32_t)v.N5, (uint32_t)k, h);
+    Spin<MOBIUS_F64>::load(bh, z.lay, z.i, z.s, h);
 #pragma unroll
     for (int c = 0; c < 12; ++c) h[c] = {h[c].r + (double)x[c].r, h[c].i + (double)x[c].i};
-    Spin<MOBIUS_F64>::store(bh, (uint32_t)v.N5, (uint32_t)k, h);
+    Spin<MOBIUS_F64>::store(bh, z.lay, z.i, z.s, h);
     // the low-precision correction is consumed: clear it
-    cx<typename Spin<PI>::T> z[12];
+    cx<typename Spin<PI>::T> zero[12];
 #pragma unroll
-    for (int c = 0; c < 12; ++c) z[c] = {0, 0};
-    Spin<PI>::store(Buf(v.a, Spin<PI>::bytes(v.N5)), (uint32_t)v.N5, (uint32_t)k, z);
+    for (int c = 0; c < 12; ++c) zero[c] = {0, 0};
+    Spin<PI>::store(Buf(v.a, Spin<PI>::bytes(v.N5)), z.lay, z.i, z.s, zero);
 }
 
 // x (PX) += alpha p_old;  p = s + beta p_old.  a = s, b = p, c = x, s0 = alpha.
@@ -1302,22 +1314,22 @@ __global__ __launch_bounds__(BLAS_BLOCK) void pupd_x_batch(const VecSys *sys, co
     const int64_t k = (int64_t)blockIdx.x * BLAS_BLOCK + threadIdx.x;
     if ((int64_t)blockIdx.x * BLAS_BLOCK >= v.N5) return;
     const int64_t fb = S::bytes(v.N5);
-    const uint32_t n5 = (uint32_t)v.N5, kk = (uint32_t)(k < v.N5 ? k : v.N5 - 1);
+    const Slice5 z(v, k < v.N5 ? k : v.N5 - 1);
     const Buf bs(v.a, fb), bp(v.b, fb), bx(v.c, SX::bytes(v.N5));
     cx<T> sv[12], pv[12];
     cx<TX> xv[12];
-    S::load(bp, n5, kk, pv);
-    SX::load(bx, n5, kk, xv);
-    S::load(bs, n5, kk, sv);
+    S::load(bp, z.lay, z.i, z.s, pv);
+    SX::load(bx, z.lay, z.i, z.s, xv);
+    S::load(bs, z.lay, z.i, z.s, sv);
     const TX al = (TX)*v.s0;
     const T be = (T)cg_beta(v, restart);
     if (k >= v.N5) return;
 #pragma unroll
     for (int c = 0; c < 12; ++c) xv[c] = xv[c] + al * cx<TX>{(TX)pv[c].r, (TX)pv[c].i};
-    SX::store(bx, n5, kk, xv);
+    SX::store(bx, z.lay, z.i, z.s, xv);
 #pragma unroll
     for (int c = 0; c < 12; ++c) pv[c] = sv[c] + be * pv[c];
-    S::store(bp, n5, kk, pv);
+    S::store(bp, z.lay, z.i, z.s, pv);
 }
 
 // x (PX) += alpha p.  a = p, c = x, s0 = alpha.
@@ -1332,15 +1344,15 @@ __global__ __launch_bounds__(BLAS_BLOCK) void xflush_batch(const VecSys *sys, co
     const int64_t k = (int64_t)blockIdx.x * BLAS_BLOCK + threadIdx.x;
     if (k >= v.N5) return;
     const TX al = (TX)*v.s0;
-    const uint32_t n5 = (uint32_t)v.N5, kk = (uint32_t)k;
+    const Slice5 z(v, k);
     const Buf bx(v.c, SX::bytes(v.N5));
     cx<typename S::T> pv[12];
     cx<TX> xv[12];
-    S::load(Buf(v.a, S::bytes(v.N5)), n5, kk, pv);
-    SX::load(bx, n5, kk, xv);
+    S::load(Buf(v.a, S::bytes(v.N5)), z.lay, z.i, z.s, pv);
+    SX::load(bx, z.lay, z.i, z.s, xv);
 #pragma unroll
     for (int c = 0; c < 12; ++c) xv[c] = xv[c] + al * cx<TX>{(TX)pv[c].r, (TX)pv[c].i};
-    SX::store(bx, n5, kk, xv);
+    SX::store(bx, z.lay, z.i, z.s, xv);
 }
 
 // p[slot] = s + beta p[prev] in a ring of directions (the deferred x update
@@ -1358,15 +1370,15 @@ __global__ __launch_bounds__(BLAS_BLOCK) void pupd_ring_batch(const VecSys *sys,
     const int64_t k = (int64_t)blockIdx.x * BLAS_BLOCK + threadIdx.x;
     if ((int64_t)blockIdx.x * BLAS_BLOCK >= v.N5) return;
     const int64_t fb = S::bytes(v.N5);
-    const uint32_t n5 = (uint32_t)v.N5, kk = (uint32_t)(k < v.N5 ? k : v.N5 - 1);
+    const Slice5 z(v, k < v.N5 ? k : v.N5 - 1);
     cx<T> sv[12], pv[12];  // (in flight while beta is summed)
-    S::load(Buf(v.b + prev * v.sstride, fb), n5, kk, pv);
-    S::load(Buf(v.a, fb), n5, kk, sv);
+    S::load(Buf(v.b + prev * v.sstride, fb), z.lay, z.i, z.s, pv);
+    S::load(Buf(v.a, fb), z.lay, z.i, z.s, sv);
     const T be = (T)cg_beta(v, restart);
     if (k >= v.N5) return;
 #pragma unroll
     for (int c = 0; c < 12; ++c) pv[c] = sv[c] + be * pv[c];
-    S::store(Buf(v.b + slot * v.sstride, fb), n5, kk, pv);
+    S::store(Buf(v.b + slot * v.sstride, fb), z.lay, z.i, z.s, pv);
 }
 
 // x (PX) += sum_{i < n} alpha_i p[i]: the x update of a chunk in one pass.
@@ -1382,7 +1394,7 @@ __global__ __launch_bounds__(BLAS_BLOCK) void xring_batch(const VecSys *sys, con
     const int64_t k = (int64_t)blockIdx.x * BLAS_BLOCK + threadIdx.x;
     if (k >= v.N5) return;
     const int64_t fb = S::bytes(v.N5);
-    const uint32_t n5 = (uint32_t)v.N5, kk = (uint32_t)k;
+    const Slice5 z(v, k);
     cx<TX> acc[12];
 #pragma unroll
     for (int c = 0; c < 12; ++c) acc[c] = cx<TX>{0, 0};
@@ -1390,16 +1402,16 @@ __global__ __launch_bounds__(BLAS_BLOCK) void xring_batch(const VecSys *sys, con
     for (int i = 0; i < n; ++i) {
         const TX al = (TX)v.s0[i];
         cx<typename S::T> pv[12];
-        S::load(Buf(v.b + i * v.sstride, fb), n5, kk, pv);
+        S::load(Buf(v.b + i * v.sstride, fb), z.lay, z.i, z.s, pv);
 #pragma unroll
         for (int c = 0; c < 12; ++c) acc[c] = acc[c] + al * cx<TX>{(TX)pv[c].r, (TX)pv[c].i};
     }
     const Buf bx(v.c, SX::bytes(v.N5));
     cx<TX> xv[12];
-    SX::load(bx, n5, kk, xv);
+    SX::load(bx, z.lay, z.i, z.s, xv);
 #pragma unroll
     for (int c = 0; c < 12; ++c) xv[c] = xv[c] + acc[c];
-    SX::store(bx, n5, kk, xv);
+    SX::store(bx, z.lay, z.i, z.s, xv);
 }
 
 // r -= alpha q, |r|^2 per site block, and u = I^-+ r of the stored r, in the
@@ -1419,24 +1431,25 @@ __global__ __launch_bounds__(BLOCK) void rupd_m5inv_batch(const VecSys *sys, con
     using T = typename S::T;
     const SiteMap m = site_map_lb(Ls, spw, Vh, blockIdx.x);
     const Coef<T> k = make_coef<T>(*v.coef);
-    const uint32_t n5 = (uint32_t)v.N5, k5 = (uint32_t)m.i * (uint32_t)Ls + (uint32_t)m.s;
+    const uint32_t i5 = (uint32_t)m.i, s5 = (uint32_t)m.s;
+    const Lay lay{(uint32_t)Ls, (uint32_t)v.N5};
     const int64_t fb = S::bytes(v.N5);
     const Buf br(v.a, fb);
     cx<T> rv[12], qv[12];
-    S::load(br, n5, k5, rv);
-    S::load(Buf(v.b, fb), n5, k5, qv);
+    S::load(br, lay, i5, s5, rv);
+    S::load(Buf(v.b, fb), lay, i5, s5, qv);
     const T al = (T)cg_alpha(v, restart, slot);
 #pragma unroll
     for (int c = 0; c < 12; ++c) rv[c] = rv[c] - al * qv[c];
     double n = 0;
-    if (m.site_ok) n = S::store_norm2_q(br, n5, k5, rv);
+    if (m.site_ok) n = S::store_norm2_q(br, lay, i5, s5, rv);
     vmem_drain();
     block_sum_store(n, v.partials, blockIdx.x);
     if (mode == 2) return;  // uniform: no solve of the updated residual
     __shared__ M5Lds<T> lds;
     m5inv_lanes(rv, k, m, Ls, mode != 1, lds);
     if (mode == 3) mix_s(rv, k.b5, k.c5, k.mf, m, Ls, true);  // B^+ I^-+ r (left form)
-    if (m.site_ok) S::store(Buf(v.c, fb), n5, k5, rv);
+    if (m.site_ok) S::store(Buf(v.c, fb), lay, i5, s5, rv);
 }
 
 // partials of Re <a, b>
@@ -1452,9 +1465,10 @@ __global__ __launch_bounds__(BLAS_BLOCK) void dot_batch(const VecSys *sys, const
     double n = 0;
     if (k < v.N5) {
         const int64_t fb = S::bytes(v.N5);
+        const Slice5 z(v, k);
         cx<T> x[12], y[12];
-        S::load(Buf(v.a, fb), (uint32_t)v.N5, (uint32_t)k, x);
-        S::load(Buf(v.b, fb), (uint32_t)v.N5, (uint32_t)k, y);
+        S::load(Buf(v.a, fb), z.lay, z.i, z.s, x);
+        S::load(Buf(v.b, fb), z.lay, z.i, z.s, y);
 #pragma unroll
         for (int c = 0; c < 12; ++c) n += (double)x[c].r * y[c].r + (double)x[c].i * y[c].i;
     }
