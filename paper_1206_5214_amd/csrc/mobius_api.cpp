@@ -291,7 +291,6 @@ extern "C" int mobius_create(mobius_ctx **out, const mobius_params *p, const voi
     if (e != hipSuccess) return cleanup(fail(MOBIUS_EHIP, hipGetErrorString(e)));
     for (int prec = 0; prec < 3; ++prec) {
         ctx->tune[prec] = hop_tuning();
-        ctx->tune[prec].prefetch = prefetch_depth(hop_tuning(), prec);
         // a chemical potential enters the time-like records: e^{+mu} forward,
         // e^{-mu} backward, and the opposite in the adjoint's own records
         const double ef = std::exp(p->mu), eb = std::exp(-p->mu);

@@ -167,9 +167,9 @@ struct HopParams {
 // mobius_tune replaces by the fastest measured candidate.
 struct HopTuning {
     int xcd_remap = 1;
-    int prefetch = -1;     // 0, 1 (next neighbour spinor), 2 (and its link); -1: per precision
+    int prefetch = -1;     // 0, 1 (next neighbour spinor), 2 (and its link); -1: by precision and kernel
     int stage_links = 1;   // copy each block's links to LDS once
-    int nt_links = 0;      // non-temporal link loads
+    int nt_links = -1;     // non-temporal link loads; -1: by precision and size
     int mfma = 1;          // FP16: colour multiply on the matrix cores where the lane map allows
     int split_dirs = -1;   // directions split over the wavefronts of a workgroup: 0, 1, or -1: by
                            // the lattice (hop_splits_dirs); the loop parameters above are then unused
@@ -185,14 +185,28 @@ constexpr int64_t SPLIT_BLOCKS[3] = {160, 400, 160};  // FP64, FP32, FP16
 bool hop_splits_dirs(const Geometry &g, int prec, int nrhs, const HopTuning &t);
 // workgroups, and so |out|^2 partials per right-hand side, of a single-lattice hop
 int64_t hop_partials(const Geometry &g, bool split_dirs);
-// prefetch depth used for a precision (measured at 24^3x64, Ls=12: the FP64
-// hop needs more than 256 VGPRs once a neighbour is prefetched, which halves
-// its occupancy -- 967 us at depth 0 against 1262 us at depth 1; FP32 and FP16
-// gain a few percent from depth 2)
-inline int prefetch_depth(const HopTuning &t, int prec)
+// Default depth.  FP64: a prefetched neighbour takes the hop that mixes its
+// input in s past 256 VGPRs, which halves its occupancy (24^3 x 64, Ls = 12: 820 us
+// at depth 0, 1101 us at depth 1), and gains the others nothing (711 and 724 us).
+// FP32: the mixing hops run four waves per SIMD at depth 0 and two or three
+// deeper (D_pre, most of whose extra time was its mixing hop: 877 us against 954 us
+// at depth 2), the others gain from depth 2 where the fields stay in the Infinity
+// Cache (16^3 x 32, Ls = 16, adjoint hop 53 against 57 us).  FP16: depth 2.
+inline int prefetch_depth(const HopTuning &t, int prec, bool mixes_input)
 {
     if (t.prefetch >= 0) return t.prefetch;
-    return prec == MOBIUS_F64 ? 0 : 2;
+    return prec == MOBIUS_F64 || (prec == MOBIUS_F32 && mixes_input) ? 0 : 2;
+}
+// Default link loads: past the caches for FP64 fields that do not stay in the
+// 256 MB Infinity Cache anyway (16^3 x 32, Ls = 16: adjoint hop 135 to 126 us;
+// 24^3 x 64, Ls = 12: 711 to 693 us).  FP32 and FP16 gain nothing there (FP32 373
+// and 373 us, FP16 241 and 245 us) and lose where the links are still cached from the
+// last hop (16^3 x 32: FP32 52 to 66 us).
+inline int nt_link_loads(const HopTuning &t, const Geometry &g, int prec)
+{
+    if (t.nt_links >= 0) return t.nt_links;
+    return prec == MOBIUS_F64 &&
+           2 * field_bytes(g, prec) + 8 * g.Vh * link_record_bytes(prec) > (int64_t)256 << 20;
 }
 // Brick of the site order for a lattice: MOBIUS_BRICK="bx,by,bz" overrides.
 void choose_brick(const int L[4], int Ls, int brick[3]);

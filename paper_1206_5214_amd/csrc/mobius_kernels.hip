@@ -534,13 +534,20 @@ __device__ __forceinline__ void hop_split(const HopParams &hp, int64_t lb, int r
     hop_epilogue<P, DAG, EPI, true>(hp, m, acc, r, lb, 0, false);
 }
 
-// The binary16 matrix-core loop is held to 128 VGPRs (four waves per SIMD):
-// its adjoint hop with the I^-+ epilogue needs 130 on its own and then runs
-// three waves (the cap costs it one spilled dword pair; the FP16 solve runs
-// about 1 % faster).  The FP64 hop spills heavily under a three-wave cap and
-// keeps two.
+// Wavefronts per SIMD a hop kernel is held to.  The binary16 matrix-core loop
+// to four (128 VGPRs): its adjoint hop with the I^-+ epilogue needs 130 on its
+// own and then runs three (the cap costs it one spilled dword pair; the FP16
+// solve runs about 1 % faster).  FP32: four without a prefetched neighbour
+// (D_pre at 24^3 x 64, Ls = 12: 900 to 877 us), three with one (its mixing hops
+// with an epilogue need 172 and would run two: 955 to 905 us, 20 spilled bytes).
+// The FP64 hop spills under a three-wave cap and keeps two (821 against 923 us).
+constexpr int hop_waves(int P, int PF)
+{
+    return P == MOBIUS_F16 && PF == 3 ? 4 : P == MOBIUS_F32 && PF < 3 ? (PF == 0 ? 4 : 3) : 1;
+}
+
 template <int P, bool DAG, int EPI, int PF>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(P == MOBIUS_F16 && PF == 3 ? 4 : 1)))
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(hop_waves(P, PF))))
 void hop_kernel(HopParams hp)
 {
     if constexpr (PF == 4) {
@@ -1742,8 +1749,8 @@ HopParams make_hop_params(const Geometry &g, const OpCoeffs &c, const void *link
     hp.split = 8 * g.Vh * link_record_bytes(a.prec) <= (int64_t)128 << 20 ? a.nrhs : 1;
     hp.remap = t.xcd_remap;
     hp.stage_links = t.stage_links && hop_link_lds_bytes(a.prec, g.Ls, false) <= 64 * 1024;
-    hp.nt = t.nt_links;
-    hp.pf = prefetch_depth(t, a.prec);
+    hp.nt = nt_link_loads(t, g, a.prec);
+    hp.pf = prefetch_depth(t, a.prec, !a.dag && !(a.epi & EPI_PREMIXED));
     // matrix-core colour multiply: FP16 with staged links and whole 4-lane
     // groups of one site (Ls divisible by 4)
     if (a.prec == MOBIUS_F16 && t.mfma && hp.stage_links && g.Ls % 4 == 0 &&
