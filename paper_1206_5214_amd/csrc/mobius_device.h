@@ -136,13 +136,6 @@ struct Buf {
     }
 };
 
-// Wait until every memory instruction this wavefront has issued has completed
-// (stores included).
-__device__ __forceinline__ void vmem_drain()
-{
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-}
-
 // Materialise a value in VGPRs at this program point (an empty asm with a
 // read-write register operand; no instruction is emitted).  Used to stop the
 // compiler from sinking the per-direction arithmetic of the hop below the
@@ -1217,12 +1210,33 @@ __device__ __forceinline__ void m5inv_lanes(cx<T> r[12], const Coef<T> &k, const
     for (int c = 0; c < 12; ++c) r[c] = w[lane * ST + c];
 }
 
-// the sum over the lanes of a wavefront, in every lane
+// the value of the lane that the DPP control CTRL names (within a row of 16 lanes)
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v)
+{
+    const u32x2 b = __builtin_bit_cast(u32x2, v);
+    return __builtin_bit_cast(double, u32x2{(uint32_t)__builtin_amdgcn_mov_dpp((int)b.x, CTRL, 0xf, 0xf, true),
+                                            (uint32_t)__builtin_amdgcn_mov_dpp((int)b.y, CTRL, 0xf, 0xf, true)});
+}
+
+__device__ __forceinline__ double lane_value(double v, int lane)
+{
+    const u32x2 b = __builtin_bit_cast(u32x2, v);
+    return __builtin_bit_cast(double, u32x2{(uint32_t)__builtin_amdgcn_readlane((int)b.x, lane),
+                                            (uint32_t)__builtin_amdgcn_readlane((int)b.y, lane)});
+}
+
+// The sum over the 64 lanes of a wavefront, in every lane (all must be active):
+// rows of 16 by moves within the row, then the four row sums.  A sum is a chain
+// of dependent steps; six LDS shuffles of 64 bits took about 0.3 us of each of
+// the small kernels of a CG iteration.
 __device__ __forceinline__ double wave_sum(double v)
 {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+    v += dpp<0xB1>(v);   // lanes 1 0 3 2 of each four
+    v += dpp<0x4E>(v);   // lanes 2 3 0 1
+    v += dpp<0x141>(v);  // mirrored within eight
+    v += dpp<0x140>(v);  // mirrored within the row
+    return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
 }
 
 // FP64 block reduction of one value per thread -> partials[slot]

@@ -1124,15 +1124,23 @@ __device__ __forceinline__ double summand(const double *part, int64_t k, int gro
 }
 
 // sum of n partial sums by the whole workgroup (BLAS_BLOCK threads), in every thread
+// (with the row sums of wave_sum instead of LDS shuffles, no barrier for up to
+// 64 partials, and the r update no longer waiting for its stores: FP16 solve on
+// 16^3 x 32, Ls = 16, 536 to 529 ms, 12 columns on 8^3 x 16 367 to 362, FP64 on
+// 8^3 x 16 64.1 to 63.2; the same for up to 128 or 256 partials, where every
+// wavefront loads them all, is slower again by 0.5 %)
 static_assert(BLOCK == BLAS_BLOCK, "the r update runs in the site kernels' workgroups");
 __device__ __forceinline__ double block_total(const double *part, int64_t n, int group)
 {
     __shared__ double red[BLAS_BLOCK / 64];
     double t = 0;
+    if (n <= 64 && group == 1) {  // each wavefront by itself: none waits for another
+        const int64_t k = threadIdx.x & 63;
+        return wave_sum(k < n ? part[k] : 0.0);
+    }
 #pragma unroll 4
     for (int64_t k = threadIdx.x; k * group < n; k += BLAS_BLOCK) t += summand(part, k, group, n);
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
+    t = wave_sum(t);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = t;
     __syncthreads();
     t = 0;
@@ -1450,7 +1458,6 @@ __global__ __launch_bounds__(BLOCK) void rupd_m5inv_batch(const VecSys *sys, con
     for (int c = 0; c < 12; ++c) rv[c] = rv[c] - al * qv[c];
     double n = 0;
     if (m.site_ok) n = S::store_norm2_q(br, lay, i5, s5, rv);
-    vmem_drain();
     block_sum_store(n, v.partials, blockIdx.x);
     if (mode == 2) return;  // uniform: no solve of the updated residual
     __shared__ M5Lds<T> lds;
