@@ -48,11 +48,12 @@ size_t link_lds_bytes(int spw, bool rows)
 // together, while the line is still in the XCD's L2 (at 24^3 x 64, Ls = 12 the
 // L2 turns over about every 5 us and a wavefront lives 10 to 19 us): the FP64
 // hop reads 3.04 GB from memory instead of 4.48.  The pairs -mu, +mu in between
-// are adjacent because the two reads of one wavefront overlap in the L1.
+// are close because the two reads of one wavefront overlap in the L1.
 // Against x+ y+ z+ t+ x- y- z- t-, D_pre and D_pre^+ there: FP64 2090 and 2265
 // to 2010 and 2215 us, FP16 600 and 650 to 565 and 607 us; FP64 hop at
-// 16^3 x 32, Ls = 16: 160 to 147 us (the reverse order: 166 us).
-__device__ constexpr int HOP_DIR[8] = {7, 4, 0, 5, 1, 6, 2, 3};
+// 16^3 x 32, Ls = 16: 160 to 147 us (the reverse order: 166 us).  The order in
+// between (y- y+ z- z+ or z- z+ y- y+ in pairs, or as here) is within 0.5 %.
+__device__ constexpr int HOP_DIR[8] = {7, 4, 0, 5, 6, 1, 2, 3};
 
 // What follows the hopping sum r = -1/2 H (B in) at one lane (Epilogue): the
 // s-direction operators, x - r, the norm and the store.  WAVE_ONLY: this
