@@ -376,7 +376,10 @@ typedef struct {
  * (MOBIUS_F64/F32/F16): every combination of the launch parameters above is
  * timed on `reps` applications of each parity (<= 0 selects 10), the fastest
  * is kept in the context and used by every later call on it (operator blocks,
- * solves, batches, force).  If the environment variable MOBIUS_TUNE_CACHE
+ * solves, batches, force).  On small lattices the form that splits the directions
+ * over a workgroup's wavefronts is timed too; chosen, it is used with the same
+ * bits wherever one lattice runs by itself, and the parameters above serve the
+ * other launches.  If the environment variable MOBIUS_TUNE_CACHE
  * names a file, an entry for the same lattice, Ls, site order, precision and
  * device is used without timing, and a new measurement is appended to it.
  * The tuner uses context scratch memory only; caller fields are untouched.
