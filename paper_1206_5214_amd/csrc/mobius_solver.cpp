@@ -1097,8 +1097,7 @@ int run(mobius_ctx *const *ctxs, int ngroups, const void *const *src, void *cons
     auto sync_flags = [&]() -> int {
         CK(hipMemcpyAsync(B.active, B.h_active.data(), sizeof(int32_t) * nsys, hipMemcpyHostToDevice, st));
         CK(hipMemcpyAsync(B.restart, B.h_restart.data(), sizeof(int32_t) * nsys, hipMemcpyHostToDevice, st));
-        CK(hipStreamSynchronize(st));  // host copies are pageable; the device clears restart flags
-        std::fill(B.h_restart.begin(), B.h_restart.end(), 0);
+        CK(hipStreamSynchronize(st));  // host copies are pageable
         return MOBIUS_OK;
     };
     if (int rc = sync_flags()) return rc;
@@ -1169,6 +1168,10 @@ int run(mobius_ctx *const *ctxs, int ngroups, const void *const *src, void *cons
             for (int q = 0; q < k; ++q) CK(B.normal ? B.body_normal(q, k) : B.body(q, k));
         }
         it += k;
+        // the chunk's first iteration took the restart flags and cleared them on
+        // the device; until then each upload repeats them (a system that restarts
+        // in the update in which another one ends is uploaded twice)
+        std::fill(B.h_restart.begin(), B.h_restart.end(), 0);
         for (int j = 0; j < nsys; ++j)
             if (B.h_active[j]) iters[j] += k;
 

@@ -296,3 +296,31 @@ def test_uneven_batch_deferred_x_update(torch_cuda, monkeypatch, inner):
             assert diff <= 1e-8 and cdiff <= 1e-5
     for op in ops:
         op.close()
+
+
+@pytest.mark.parametrize("inner", [1, 2], ids=["mixed_f32", "mixed_f16"])
+def test_restart_survives_another_system_finishing(torch_cuda, inner):
+    """A system that a reliable update sends back to its residual (beta = 0) does
+    so also when another system reaches its target in that same update: with a
+    threshold near 1 the ill-conditioned lattice restarts after every chunk, the
+    heavy free one is done after a few of them, and the former runs bit for bit as
+    by itself."""
+    from paper_1206_5214_amd import inputs, mobius
+    torch = torch_cuda
+    dims, Ls = (4, 4, 4, 4), 8
+    rng = np.random.default_rng(5)
+    ops = [mobius.Operator(dims, Ls, 1.8, mf, 1.5, 0.5, torch.from_numpy(U).cuda())
+           for mf, U in ((1.0, inputs.unit_links(dims)), (0.01, inputs.random_links(dims, 0.5, rng)))]
+    eta = torch.from_numpy(inputs.gaussian_spinor(dims, Ls, rng, 2)).cuda()
+    opts = dict(tol=1e-5, maxiter=120, inner_prec=inner, reliable_delta=0.95, check_every=4)
+    (_, both), info, _ = mobius.batch_solve(ops, [eta[0], eta[1]], **opts)
+    alone, info1, _ = ops[1].solve(eta[1], **opts)
+    free, slow = info[0][0], info[1][0]
+    _flush(f"restart beside a finished system, inner {inner}: iters {free.iters} and {slow.iters}, alone "
+           f"{info1[0].iters}; updates {free.reliable_updates} and {slow.reliable_updates}, alone "
+           f"{info1[0].reliable_updates}")
+    assert free.status == mobius.OK and free.iters < slow.iters
+    assert (slow.iters, slow.reliable_updates) == (info1[0].iters, info1[0].reliable_updates)
+    assert torch.equal(both, alone)
+    for op in ops:
+        op.close()
