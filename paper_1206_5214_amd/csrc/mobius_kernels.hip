@@ -759,8 +759,79 @@ bool run_hop<MOBIUS_HOP_PREC>(int dag, int epi, const HopParams &hp, hipStream_t
 
 namespace {
 
-// per-site s-direction operators: kind 0 -> I (or I^+), kind 1 -> I^-1 (or I^-+)
-template <int P, bool DAG, int KIND>
+// A wavefront's whole sites of a field in records (one stretch of memory) to and
+// from the chunks of each lane's 5d site, through the wavefront's own LDS.  The
+// s-direction operators only stream their field: where a site's chunk of Ls * 16
+// bytes is no whole number of 128-byte lines (Ls = 4, 12, 20, 28), one access per
+// chunk touches half lines, and the stores, which go past the caches, pay for them.
+// Moved as one stretch, every access covers whole lines.  24^3 x 64, Ls = 12, I and
+// I^-1: FP32 198 to 172 and 200 to 177 us, FP64 383 to 365 and 400 to 367 us;
+// 24^3 x 32, Ls = 4: FP64 63.4 to 50.3 and 65.2 to 55.1 us.  With one site to a
+// wavefront (Ls = 36) the pass through LDS costs I^-1 more than it gains (167 to
+// 210 us): such sites, and whole lines, are read and written directly.
+template <int P>
+struct RecordTile {
+    using T = typename Spin<P>::T;
+    static constexpr int CH = 12 * (int)sizeof(cx<T>) / 16;  // 16-byte chunks of a 5d site
+    static constexpr int PER = 12 / CH;                      // components of a chunk
+    struct Chunk { cx<T> v[PER]; };
+    u32x4 *lds;                                              // 64 * CH of them
+    uint32_t base, n;                                        // byte offset in the field, chunks
+    __device__ __forceinline__ RecordTile(void *buf, const SiteMap &m, int Ls, int spw, int64_t Vh, int64_t lb)
+        : lds(static_cast<u32x4 *>(buf))
+    {
+        const int64_t first = (lb * WAVES + m.wave) * spw, left = Vh - first;
+        base = left > 0 ? (uint32_t)(first * Ls) * (CH * 16u) : 0u;
+        n = left > 0 ? (uint32_t)((left < spw ? left : spw) * Ls * CH) : 0u;
+    }
+    // chunk c of this lane (a lane without a site reads the first site's)
+    __device__ __forceinline__ uint32_t slot(const SiteMap &m, int Ls, int c) const
+    {
+        return (uint32_t)(((m.site_ok ? m.g : 0) * CH + c) * Ls + m.s);
+    }
+    __device__ __forceinline__ void load(const Buf &b, const SiteMap &m, int Ls, cx<T> v[12])
+    {
+        u32x4 t[CH];
+#pragma unroll
+        for (int j = 0; j < CH; ++j) {
+            const uint32_t u = (uint32_t)j * 64u + (uint32_t)m.lane;
+            t[j] = b.ld16(u < n ? base + u * 16u : base, 0u);
+        }
+#pragma unroll
+        for (int j = 0; j < CH; ++j) lds[j * 64 + m.lane] = t[j];
+        lds_sync<true>();
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            const Chunk q = __builtin_bit_cast(Chunk, lds[slot(m, Ls, c)]);
+#pragma unroll
+            for (int e = 0; e < PER; ++e) v[c * PER + e] = q.v[e];
+        }
+        lds_sync<true>();
+    }
+    __device__ __forceinline__ void store(const Buf &b, const SiteMap &m, int Ls, const cx<T> v[12])
+    {
+        lds_sync<true>();
+        if (m.site_ok) {
+#pragma unroll
+            for (int c = 0; c < CH; ++c) {
+                Chunk q;
+#pragma unroll
+                for (int e = 0; e < PER; ++e) q.v[e] = v[c * PER + e];
+                lds[slot(m, Ls, c)] = __builtin_bit_cast(u32x4, q);
+            }
+        }
+        lds_sync<true>();
+#pragma unroll
+        for (int j = 0; j < CH; ++j) {
+            const uint32_t u = (uint32_t)j * 64u + (uint32_t)m.lane;
+            if (u < n) b.st16(lds[u], base + u * 16u, 0u);
+        }
+    }
+};
+
+// per-site s-direction operators: kind 0 -> I (or I^+), kind 1 -> I^-1 (or I^-+).
+// LINEAR: the field moves through RecordTile.
+template <int P, bool DAG, int KIND, bool LINEAR>
 __global__ __launch_bounds__(BLOCK) void m5_kernel(const char *in, char *out, int64_t Vh,
                                                    int64_t N5, int Ls, int spw, OpCoeffs c)
 {
@@ -769,15 +840,23 @@ __global__ __launch_bounds__(BLOCK) void m5_kernel(const char *in, char *out, in
     const SiteMap m = site_map(Ls, spw, Vh);
     const Coef<T> k = make_coef<T>(c);
     const int64_t fbytes = S::bytes(N5);
+    const Lay lay{(uint32_t)Ls, (uint32_t)N5};
+    __shared__ M5Lds<T> lds;
     cx<T> v[12];
-    S::load(Buf(in, fbytes), Lay{(uint32_t)Ls, (uint32_t)N5}, (uint32_t)m.i, (uint32_t)m.s, v);
-    if constexpr (KIND == 0) {
+    if constexpr (LINEAR)
+        RecordTile<P>(lds.buf[m.wave], m, Ls, spw, Vh, logical_block(0))
+            .load(Buf(in, fbytes), m, Ls, v);
+    else
+        S::load(Buf(in, fbytes), lay, (uint32_t)m.i, (uint32_t)m.s, v);
+    if constexpr (KIND == 0)
         mix_s(v, mix_w(k, true, m, Ls, DAG), k.mf, m, Ls, DAG);
-    } else {
-        __shared__ M5Lds<T> lds;
+    else
         m5inv_lanes(v, k, m, Ls, DAG, lds);
-    }
-    if (m.site_ok) S::store(Buf(out, fbytes), Lay{(uint32_t)Ls, (uint32_t)N5}, (uint32_t)m.i, (uint32_t)m.s, v);
+    if constexpr (LINEAR)
+        RecordTile<P>(lds.buf[m.wave], m, Ls, spw, Vh, logical_block(0))
+            .store(Buf(out, fbytes), m, Ls, v);
+    else if (m.site_ok)
+        S::store(Buf(out, fbytes), lay, (uint32_t)m.i, (uint32_t)m.s, v);
 }
 
 // ---------------------------------------------------------------------------
@@ -1808,11 +1887,18 @@ void m5_launch(int kind, int dag, const char *in, char *out, const Geometry &g, 
                int64_t blocks, hipStream_t st)
 {
     const int spw = sites_per_wave(g.Ls);
-    dim3 grid((unsigned)blocks), blk(BLOCK);
-    if (kind == 0 && !dag) hipLaunchKernelGGL((m5_kernel<P, false, 0>), grid, blk, 0, st, in, out, g.Vh, g.N5, g.Ls, spw, c);
-    if (kind == 0 && dag) hipLaunchKernelGGL((m5_kernel<P, true, 0>), grid, blk, 0, st, in, out, g.Vh, g.N5, g.Ls, spw, c);
-    if (kind == 1 && !dag) hipLaunchKernelGGL((m5_kernel<P, false, 1>), grid, blk, 0, st, in, out, g.Vh, g.N5, g.Ls, spw, c);
-    if (kind == 1 && dag) hipLaunchKernelGGL((m5_kernel<P, true, 1>), grid, blk, 0, st, in, out, g.Vh, g.N5, g.Ls, spw, c);
+    const bool linear = P != MOBIUS_F16 && g.Ls % 8 == 4 && spw > 1;  // (see RecordTile)
+    const dim3 grid((unsigned)blocks), blk(BLOCK);
+#define MOBIUS_M5(D, K)                                                                             \
+    if (linear)                                                                                    \
+        hipLaunchKernelGGL((m5_kernel<P, D, K, P != MOBIUS_F16>), grid, blk, 0, st, in, out, g.Vh, g.N5, g.Ls, spw, c); \
+    else                                                                                           \
+        hipLaunchKernelGGL((m5_kernel<P, D, K, false>), grid, blk, 0, st, in, out, g.Vh, g.N5, g.Ls, spw, c)
+    if (kind == 0 && !dag) { MOBIUS_M5(false, 0); }
+    if (kind == 0 && dag) { MOBIUS_M5(true, 0); }
+    if (kind == 1 && !dag) { MOBIUS_M5(false, 1); }
+    if (kind == 1 && dag) { MOBIUS_M5(true, 1); }
+#undef MOBIUS_M5
 }
 }  // namespace
 

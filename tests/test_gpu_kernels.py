@@ -54,6 +54,32 @@ def test_pack_unpack_exact(torch_cuda, dims, Ls, nrhs):
     op.close()
 
 
+# the s-direction operators on fields in records: fewer sites than one wavefront's,
+# partial last wavefronts and workgroups, moved as one stretch (Ls = 4, 12, 20, 28)
+# and read directly (Ls = 8, and 36 with one site per wavefront)
+@pytest.mark.parametrize("dims,Ls", [((2, 2, 2, 2), 4), ((4, 4, 4, 6), 4), ((4, 2, 2, 6), 12), ((6, 4, 2, 4), 20),
+                                     ((2, 2, 2, 6), 28), ((2, 2, 2, 6), 8), ((4, 4, 2, 2), 36)])
+@pytest.mark.parametrize("prec,tol", [(0, 1e-12), (1, 2e-5)], ids=["f64", "f32"])
+def test_s_direction_operators_vs_oracle(torch_cuda, orc, dims, Ls, prec, tol):
+    """I, I^+, I^-1 and I^-+ of two right-hand sides against the FP64 oracle (a
+    lane's sums have Ls terms of order one: the hop's tolerances hold)."""
+    from oracle import Params
+    from paper_1206_5214_amd import inputs
+    from parity import check
+    torch = torch_cuda
+    mobius, op, eta = _setup(torch, dims, Ls, 2)
+    p, psi, U = Params(dims, Ls, 1.8, 0.05, 1.5, 0.5), eta.cpu().numpy(), inputs.unit_links(dims)  # (no links enter)
+    even, odd = op.pack(eta, prec, 2)
+    for dag in (False, True):
+        m5 = [op.dslash(x, q, prec, op=mobius.OP_M5, dag=dag, nrhs=2) for q, x in enumerate((even, odd))]
+        inv = [op.m5inv(x, prec, dag=dag, nrhs=2) for x in (even, odd)]
+        for halves, ref in ((m5, lambda v: orc.m5(p, U, v, dag=dag)), (inv, lambda v: orc.m5inv(p, v, dag=dag))):
+            got = op.unpack(*halves, prec, 2).cpu().numpy()
+            for r in range(2):
+                check(got[r], ref(psi[r]), tol, (dims, Ls, dag, r))
+    op.close()
+
+
 # a hop with its directions split over wavefronts (the small lattices' default)
 # against the loop variants that set_tuning asks for: fewer sites than one
 # wavefront's, partial last wavefronts, odd Ls, one site per wavefront, matrix-core
