@@ -1803,6 +1803,55 @@ size_t hop_link_lds_bytes(int prec, int Ls, bool rows)
     }
 }
 
+namespace {
+
+// Whether the right-hand sides of a launch run side by side, each workgroup
+// staging its links for one of them, or take turns in workgroups that stage once.
+// Ratios: time taking turns / time side by side, D_{p,1-p} and its adjoint and left
+// forms unless D_pre is named.
+bool rhs_side_by_side(const Geometry &g, const HopArgs &a, const HopParams &hp)
+{
+    const int64_t n = a.nrhs, b = site_kernel_blocks(g), cus = 256;
+    const auto per_cu = [](int64_t blocks) { return (blocks + cus - 1) / cus; };
+    // links of a parity beyond half the 256 MB Infinity Cache come from memory
+    // each time (24^3 x 64, Ls = 12, 3 right-hand sides, D_pre: FP64 0.97, FP16 0.97)
+    if (8 * g.Vh * link_record_bytes(a.prec) > (int64_t)128 << 20) return false;
+    if (!hp.stage_links) return true;  // nothing is staged (FP64, Ls = 4, 16^4, 3: D_pre 1.1)
+    // CUs that the sites alone leave idle (128 blocks, 3 to 12: 1.0 to 2.3; 210
+    // blocks, 2: 1.0 to 1.2)
+    if (b <= 160 || b * n <= 2 * cus) return true;
+    // The I^-1 epilogue's buffer takes the links' place in LDS only if they are
+    // done with; beside them it may cost a resident workgroup (16^3 x 32, Ls = 8,
+    // 3 right-hand sides, D_pre: FP64 1.19, FP16 1.11; at Ls = 12, where FP64 loses
+    // none, 0.94).  FP32 and FP16 keep two on a CU, enough for up to 512 blocks
+    // (16^4, Ls = 4, 2 to 6, FP32: 0.9).
+    const bool inverse = (a.epi & EPI_M5INV) != 0, mixes = !a.dag && !(a.epi & EPI_PREMIXED);
+    if (inverse && (a.prec == MOBIUS_F64 || b > 2 * cus)) {
+        const int64_t lds = 160 * 1024, resident = a.prec == MOBIUS_F64 ? 2 : 4;
+        const int64_t both = hop_link_lds_bytes(a.prec, g.Ls, hp.pf == 3) + m5_epilogue_lds_bytes(a.prec);
+        if (lds / both < resident) return true;
+    }
+    // FP32 and FP16: the sites fill the chip from about 400 blocks (324: 1.0 to 1.3;
+    // 432: 0.9 to 1.0, with an epilogue or input mixing 1.0 to 1.1); FP16, whose staging
+    // converts the links, then loses by repeating it (683 to 4096 blocks 0.8 to 1.0)
+    const int64_t few = inverse || mixes ? 448 : 384;
+    if (a.prec == MOBIUS_F16) return b <= few;
+    // many slices to a link while the fields stay in the Infinity Cache (Ls = 12, 519
+    // blocks, 3: FP64 1.1 to 1.2, FP32 1.1; 16^3 x 32, Ls = 12, FP64: 0.96) or beyond
+    // (Ls = 16, 3 to 12: FP64 1.0 to 1.28), or many right-hand sides on several
+    // rounds of workgroups (1024 to 1536 blocks, 6 and 12: FP64 1.0 to 1.2; 2 or 3 of
+    // them 0.9 to 1.0)
+    if (g.Ls >= 10 && 2 * field_bytes(g, a.prec) <= (int64_t)256 << 20) return true;
+    if ((g.Ls >= 16 && n >= 3) || (n >= 6 && b >= 1024)) return true;
+    if (a.prec == MOBIUS_F32) return b <= few;  // (Ls = 5, 683 blocks: 0.9)
+    // FP64, whose workgroups on one CU run one after the other in effect: by the
+    // fullest CU (324 blocks, 3: 4 against 6, 1.05 to 1.13; 216 blocks, 3: 3 against 3,
+    // 0.85; 432 blocks, 3: 6 against 6, 0.84)
+    return 10 * per_cu(b * n) <= 7 * n * per_cu(b);
+}
+
+}  // namespace
+
 HopParams make_hop_params(const Geometry &g, const OpCoeffs &c, const void *links,
                           const int32_t *nbr, const HopArgs &a)
 {
@@ -1826,14 +1875,6 @@ HopParams make_hop_params(const Geometry &g, const OpCoeffs &c, const void *link
     hp.Ls = g.Ls;
     hp.spw = sites_per_wave(g.Ls);
     hp.nrhs = a.nrhs;
-    // Right-hand sides run side by side, each workgroup staging its links for one
-    // of them, where the links of a parity fit half the 256 MB Infinity Cache;
-    // beyond, a workgroup takes all of them in turn on links staged once.  D_pre,
-    // shared against split: 8^3 x 16, Ls = 8, 12 right-hand sides (128 site
-    // blocks on 256 CUs) FP64 248 / 144 us, FP16 119 / 45 us; 16^3 x 32, Ls = 16,
-    // 12: FP64 4592 / 4241 us, FP16 1266 / 1241 us; 24^3 x 64, Ls = 12, 3: FP64
-    // 5600 / 5801 us, FP16 1610 / 1665 us.
-    hp.split = 8 * g.Vh * link_record_bytes(a.prec) <= (int64_t)128 << 20 ? a.nrhs : 1;
     hp.remap = t.xcd_remap;
     hp.stage_links = t.stage_links && hop_link_lds_bytes(a.prec, g.Ls, false) <= 64 * 1024;
     hp.nt = nt_link_loads(t, g, a.prec);
@@ -1843,6 +1884,7 @@ HopParams make_hop_params(const Geometry &g, const OpCoeffs &c, const void *link
     if (a.prec == MOBIUS_F16 && t.mfma && hp.stage_links && g.Ls % 4 == 0 &&
         hop_link_lds_bytes(a.prec, g.Ls, true) <= 64 * 1024)
         hp.pf = 3;
+    hp.split = rhs_side_by_side(g, a, hp) ? a.nrhs : 1;
     if (split_dirs) {
         hp.split_mfma = hp.pf == 3;
         hp.pf = 4;

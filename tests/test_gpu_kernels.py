@@ -113,3 +113,69 @@ def test_split_hop_same_bits(torch_cuda, dims, Ls, nrhs):
         assert torch.equal(a, b)
         assert [i.iters for i in ia] == [i.iters for i in ib]
     op.close()
+
+
+def _gauss(torch, shape, seed):
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    return torch.view_as_complex(torch.randn(shape + (2,), dtype=torch.float64, device="cuda", generator=gen))
+
+
+# right-hand sides that take turns in a workgroup on links staged once: hops without
+# an I^-1 epilogue on some 400 site blocks, with one on 512 (FP32, FP16: its buffer
+# lies past the links), and every hop where the links outgrow the cache (FP64)
+SHARED = [((12, 12, 12, 16), 8, (0, 1, 2)), ((16, 16, 16, 16), 4, (1, 2)), ((16, 16, 16, 64), 5, (0,))]
+
+
+@pytest.mark.parametrize("dims,Ls,precs", SHARED, ids=[f"{d}-Ls{ls}" for d, ls, _ in SHARED])
+def test_right_hand_sides_sharing_links_same_bits(torch_cuda, dims, Ls, precs):
+    """Each right-hand side has the bits of its own application, in every operator
+    block; cut by maxiter, each solve form the iterates of its solo solve."""
+    torch = torch_cuda
+    from paper_1206_5214_amd import inputs, mobius
+    n = 2
+    U = torch.from_numpy(inputs.random_links(dims, 0.4, np.random.default_rng(3))).cuda()
+    op = mobius.Operator(dims, Ls, 1.8, 0.05, 1.5, 0.5, U)
+    eta = _gauss(torch, op.canon_shape(n), 4)
+    for prec in precs:
+        full = op.pack_full(eta, prec, n)
+        one = [op.pack_full(eta[r], prec) for r in range(n)]
+        fb = op.field_bytes(prec)
+        for o in range(8):
+            for dag in (False, True):
+                got = op.dslash(full if o == mobius.OP_FULL else full[n * fb:], 1, prec, op=o, dag=dag, nrhs=n)
+                for r in range(n):
+                    want = op.dslash(one[r] if o == mobius.OP_FULL else one[r][fb:], 1, prec, op=o, dag=dag)
+                    halves = (r, n + r) if o == mobius.OP_FULL else (r,)
+                    for k, h in enumerate(halves):
+                        assert torch.equal(got[h * fb:(h + 1) * fb], want[k * fb:(k + 1) * fb]), (prec, o, dag, r)
+        del full, one, got, want
+        for kw in [{"form": f} for f in range(4)] + [{"dagger": True}]:
+            opts = dict(tol=1e-12, maxiter=9, inner_prec=prec, check_every=4, **kw)
+            sol = op.solve(eta, **opts)[0]
+            for r in range(n):
+                assert torch.equal(sol[r], op.solve(eta[r], **opts)[0]), (prec, kw, r)
+    op.close()
+
+
+@pytest.mark.parametrize("prec", [0, 1, 2], ids=["f64", "f32", "f16"])
+def test_batch_with_shared_links_same_iterates(torch_cuda, prec):
+    """A batched launch in which one lattice's right-hand sides share their links (the
+    I^-1 buffer then lies past the links for every lattice) and another's do not.
+    FP16: the rows of a site block at Ls = 4 are too large to stage, so that the
+    batch runs the dot-product loop everywhere, and the solo solves are told to."""
+    torch = torch_cuda
+    from paper_1206_5214_amd import inputs, mobius
+    rng = np.random.default_rng(6)
+    ops, srcs = [], []
+    for k, (dims, Ls) in enumerate((((12, 12, 12, 16), 8), ((16, 16, 16, 16), 4), ((4, 4, 4, 6), 8))):
+        U = torch.from_numpy(inputs.random_links(dims, 0.4, rng)).cuda()
+        ops.append(mobius.Operator(dims, Ls, 1.8, 0.05, 1.5, 0.5, U))
+        srcs.append(_gauss(torch, ops[-1].canon_shape(2), 10 + k))
+    opts = dict(tol=1e-12, maxiter=9, inner_prec=prec, check_every=4)
+    sols = mobius.batch_solve(ops, srcs, **opts)[0]
+    for op, src, sol in zip(ops, srcs, sols):
+        if prec == mobius.F16:
+            op.set_tuning(prec, 2, 1, 1, 0, mfma=0)
+        for r in range(2):
+            assert torch.equal(sol[r], op.solve(src[r].contiguous(), **opts)[0]), (op.dims, r)
+        op.close()
