@@ -37,7 +37,7 @@ std::string cache_key(const mobius_ctx *ctx, int prec)
     std::ostringstream k;
     k << ctx->g.L[0] << 'x' << ctx->g.L[1] << 'x' << ctx->g.L[2] << 'x' << ctx->g.L[3] << " Ls"
       << ctx->g.Ls << " brick" << ctx->g.brick[0] << 'x' << ctx->g.brick[1] << 'x'
-      << ctx->g.brick[2] << " prec" << prec << ' ' << arch << " v2";
+      << ctx->g.brick[2] << " prec" << prec << ' ' << arch << " v3";  // raised with the hop kernels
     return k.str();
 }
 
@@ -52,10 +52,9 @@ bool cache_lookup(const std::string &path, const std::string &key, HopTuning &t,
         std::istringstream v(line.substr(bar + 3));
         HopTuning c;
         double u;
-        if (v >> c.prefetch >> c.stage_links >> c.xcd_remap >> c.nt_links >> c.mfma >> u) {
-            // 1: the split form was faster than all of them; absent or 0: it was not tried or was not
-            if (!(v >> c.split_dirs) || c.split_dirs != 1) c.split_dirs = 0;
-            if (c.split_dirs) c.split_dirs = -1;
+        int split;  // 1: the split form was faster than all of them
+        if (v >> c.prefetch >> c.stage_links >> c.xcd_remap >> c.nt_links >> c.mfma >> u >> split) {
+            c.split_dirs = split == 1 ? -1 : 0;
             t = c;
             us = u;
             found = true;

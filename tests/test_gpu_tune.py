@@ -76,6 +76,28 @@ def test_tune_cache(torch_cuda, monkeypatch, tmp_path):
     op2.close()
 
 
+def test_tune_cache_of_other_kernels_is_not_used(torch_cuda, monkeypatch, tmp_path):
+    """Lines that an older library measured on its own kernels (another version in
+    the key, or no split flag at the end) are timed again, and the new line used."""
+    from paper_1206_5214_amd import mobius
+    torch = torch_cuda
+    cache = tmp_path / "tune.txt"
+    monkeypatch.setenv("MOBIUS_TUNE_CACHE", str(cache))
+    op, _ = _op(torch, dims=(4, 4, 4, 8), Ls=8)
+    op.tune(mobius.F64, reps=3)
+    key, values = cache.read_text().strip().split(" | ")
+    words = values.split()
+    words[5] = "123456.5"  # the hop's time
+    old = [key.rsplit(" ", 1)[0] + " v2 | " + " ".join(words[:6]), key + " | " + " ".join(words[:6])]
+    for line in old:
+        cache.write_text(line + "\n")
+        r = op.tune(mobius.F64, reps=3)
+        lines = cache.read_text().splitlines()
+        assert r["hop_us"] != 123456.5 and len(lines) == 2 and lines[0] == line
+        assert op.tune(mobius.F64, reps=3) == r and len(cache.read_text().splitlines()) == 2
+    op.close()
+
+
 def test_tune_rejects_bad_precision(torch_cuda):
     from paper_1206_5214_amd import mobius
     torch = torch_cuda
