@@ -374,17 +374,36 @@ typedef struct {
 
 /* Autotune the hop kernel of this context for storage precision `prec`
  * (MOBIUS_F64/F32/F16): every combination of the launch parameters above is
- * timed on `reps` applications of each parity (<= 0 selects 10), the fastest
- * is kept in the context and used by every later call on it (operator blocks,
- * solves, batches, force).  On small lattices the form that splits the directions
- * over a workgroup's wavefronts is timed too; chosen, it is used with the same
- * bits wherever one lattice runs by itself, and the parameters above serve the
- * other launches.  If the environment variable MOBIUS_TUNE_CACHE
+ * timed on `reps` applications of each parity (<= 0 selects 10).  The fastest is
+ * kept unless the launch parameters of an untuned context, which may differ from
+ * kernel to kernel, are faster on the hops of D_pre and D_pre^+; on small lattices
+ * the form that splits the directions over a workgroup's wavefronts is compared
+ * in the same way.  The result is kept in the context and used by every later
+ * call on it (operator blocks, solves, batches, force); mobius_hop_flags tells
+ * which of these it is.  If the environment variable MOBIUS_TUNE_CACHE
  * names a file, an entry for the same lattice, Ls, site order, precision and
  * device is used without timing, and a new measurement is appended to it.
  * The tuner uses context scratch memory only; caller fields are untouched.
  * Synchronises.  out may be NULL. */
 int mobius_tune(mobius_ctx *ctx, int32_t prec, int32_t reps, mobius_tune_result *out, void *stream);
+
+/* What mobius_tune_result does not hold of a context's hop launches. */
+#define MOBIUS_HOP_SPLIT 1           /* on small lattices the directions are split over the wavefronts
+                                        of a workgroup wherever one lattice runs by itself, with the
+                                        bits of the loop; the parameters serve the other launches */
+#define MOBIUS_HOP_DEPTH_BY_KERNEL 2 /* the prefetch depth is the library's own, which goes by the kernel
+                                        (`prefetch`: that of hops that do not mix their input in s) */
+#define MOBIUS_HOP_SHARED_LINKS 4    /* (reported only) right-hand sides take turns on links staged once */
+
+/* The flags in effect for the hop D_{p,1-p} of nrhs right-hand sides in storage
+ * precision prec (MOBIUS_HOP_SPLIT: such a launch does split), or a negative
+ * error code. */
+int mobius_hop_flags(mobius_ctx *ctx, int32_t prec, int32_t nrhs);
+
+/* Set MOBIUS_HOP_SPLIT and MOBIUS_HOP_DEPTH_BY_KERNEL for one precision: after
+ * mobius_set_tuning, which clears both, the flags that followed an earlier
+ * mobius_tune restore its choice.  Returns MOBIUS_EINVAL for other flags. */
+int mobius_set_hop_flags(mobius_ctx *ctx, int32_t prec, int32_t flags);
 
 /* One candidate site order timed by mobius_tune_brick. */
 typedef struct {
@@ -409,7 +428,8 @@ int mobius_tune_brick(const mobius_params *p, const void *links_c128, int32_t pr
                       int32_t *brick_out, double *us_out, void *stream);
 
 /* Set the hop launch parameters of a context for precision t->prec directly
- * (for example those an earlier mobius_tune reported; t->hop_us is ignored).
+ * (for example those an earlier mobius_tune reported; t->hop_us is ignored), in
+ * the loop over the directions and for every kernel (see mobius_set_hop_flags).
  * Returns MOBIUS_EINVAL for a value outside the ranges above. */
 int mobius_set_tuning(mobius_ctx *ctx, const mobius_tune_result *t);
 

@@ -966,6 +966,31 @@ extern "C" int mobius_tune_brick(const mobius_params *p, const void *links_c128,
     return MOBIUS_OK;
 }
 
+extern "C" int mobius_hop_flags(mobius_ctx *ctx, int32_t prec, int32_t nrhs)
+{
+    g_err.clear();
+    if (int r = check_ctx(ctx)) return r;
+    if (int r = check_prec(prec)) return r;
+    if (nrhs < 1) return fail(MOBIUS_EINVAL, "bad argument to mobius_hop_flags");
+    HopArgs a = hop_args(prec, 0, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr, nrhs);
+    a.tune = &ctx->tune[prec];
+    const HopParams hp = make_hop_params(ctx->g, ctx->c, nullptr, nullptr, a);
+    return (hp.pf == 4 ? MOBIUS_HOP_SPLIT : 0) | (a.tune->prefetch < 0 ? MOBIUS_HOP_DEPTH_BY_KERNEL : 0) |
+           (hp.split < nrhs ? MOBIUS_HOP_SHARED_LINKS : 0);
+}
+
+extern "C" int mobius_set_hop_flags(mobius_ctx *ctx, int32_t prec, int32_t flags)
+{
+    g_err.clear();
+    if (int r = check_ctx(ctx)) return r;
+    if (int r = check_prec(prec)) return r;
+    if (flags & ~(MOBIUS_HOP_SPLIT | MOBIUS_HOP_DEPTH_BY_KERNEL)) return fail(MOBIUS_EINVAL, "unknown hop flags");
+    HopTuning &h = ctx->tune[prec];
+    h.split_dirs = (flags & MOBIUS_HOP_SPLIT) != 0;
+    h.prefetch = flags & MOBIUS_HOP_DEPTH_BY_KERNEL ? -1 : prefetch_depth(h, prec, false);
+    return MOBIUS_OK;
+}
+
 extern "C" int mobius_set_tuning(mobius_ctx *ctx, const mobius_tune_result *t)
 {
     g_err.clear();

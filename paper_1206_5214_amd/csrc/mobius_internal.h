@@ -171,8 +171,8 @@ struct HopTuning {
     int stage_links = 1;   // copy each block's links to LDS once
     int nt_links = -1;     // non-temporal link loads; -1: by precision and size
     int mfma = 1;          // FP16: colour multiply on the matrix cores where the lane map allows
-    int split_dirs = -1;   // directions split over the wavefronts of a workgroup: 0, 1, or -1: by
-                           // the lattice (hop_splits_dirs); the loop parameters above are then unused
+    int split_dirs = 1;    // small lattices split the directions over the wavefronts of a workgroup
+                           // (hop_splits_dirs); the loop parameters above are then unused
 };
 // Site blocks times right-hand sides up to which a hop splits its directions:
 // the split form's workgroups then run in about one round, and its chain of two

@@ -1677,8 +1677,7 @@ int64_t site_kernel_blocks(const Geometry &g)
 
 bool hop_splits_dirs(const Geometry &g, int prec, int nrhs, const HopTuning &t)
 {
-    if (t.split_dirs >= 0) return t.split_dirs != 0;
-    return site_kernel_blocks(g) * nrhs <= SPLIT_BLOCKS[prec];
+    return t.split_dirs && site_kernel_blocks(g) * nrhs <= SPLIT_BLOCKS[prec];
 }
 
 int64_t hop_partials(const Geometry &g, bool split_dirs)

@@ -21,11 +21,12 @@ PREC = {"f64": F64, "f32": F32, "f16": F16}
 (OP_HOP, OP_M5, OP_SCHUR, OP_FULL, OP_SCHUR_RIGHT, OP_HOP_LEFT, OP_SCHUR_LEFT,
  OP_SCHUR_COMPLEMENT) = range(8)
 OK, NOT_CONVERGED = 0, 1
+HOP_SPLIT, HOP_DEPTH_BY_KERNEL, HOP_SHARED_LINKS = 1, 2, 4
 
 EXPORTS = ("mobius_create", "mobius_destroy", "mobius_field_bytes", "mobius_pack",
            "mobius_unpack", "mobius_dslash", "mobius_dslash_dag", "mobius_m5inv",
            "mobius_cg_solve", "mobius_batch_solve", "mobius_propagator4d", "mobius_force", "mobius_force_lie",
-           "mobius_tune", "mobius_set_tuning", "mobius_last_error", "mobius_dslash_noalloc",
+           "mobius_tune", "mobius_set_tuning", "mobius_hop_flags", "mobius_set_hop_flags", "mobius_last_error", "mobius_dslash_noalloc",
            "mobius_bulk5d", "mobius_cg_solve_dag", "mobius_force_wall", "mobius_tune_brick")
 
 
@@ -143,6 +144,8 @@ def lib():
                                         ctypes.POINTER(ctypes.c_double), vp]
         L.mobius_tune.argtypes = [vp, i32, i32, ctypes.POINTER(_TuneResult), vp]
         L.mobius_set_tuning.argtypes = [vp, ctypes.POINTER(_TuneResult)]
+        L.mobius_hop_flags.argtypes = [vp, i32, i32]
+        L.mobius_set_hop_flags.argtypes = [vp, i32, i32]
         L.mobius_last_error.restype = ctypes.c_char_p
         for f in EXPORTS:
             if f not in ("mobius_field_bytes", "mobius_last_error"):
@@ -414,13 +417,25 @@ class Operator:
         precision; returns the chosen parameters and the measured hop time."""
         r = _TuneResult()
         _check(lib().mobius_tune(self._h, prec, reps, ctypes.byref(r), _stream()))
+        flags = self.hop_flags(prec)
         return {"prec": r.prec, "prefetch": r.prefetch, "stage_links": r.stage_links,
-                "xcd_remap": r.xcd_remap, "nt_links": r.nt_links, "mfma": r.mfma, "hop_us": r.hop_us}
+                "xcd_remap": r.xcd_remap, "nt_links": r.nt_links, "mfma": r.mfma,
+                "split": flags & HOP_SPLIT, "depth_by_kernel": (flags & HOP_DEPTH_BY_KERNEL) >> 1,
+                "hop_us": r.hop_us}
 
-    def set_tuning(self, prec, prefetch, stage_links, xcd_remap, nt_links, mfma=0):
-        """Set the hop launch parameters for one precision explicitly."""
+    def set_tuning(self, prec, prefetch, stage_links, xcd_remap, nt_links, mfma=0, split=0, depth_by_kernel=0):
+        """Set the hop launch parameters for one precision explicitly (the entries
+        of tune's result but the time)."""
         r = _TuneResult(prec, prefetch, stage_links, xcd_remap, nt_links, mfma, 0.0)
         _check(lib().mobius_set_tuning(self._h, ctypes.byref(r)))
+        if split or depth_by_kernel:
+            _check(lib().mobius_set_hop_flags(self._h, prec, (HOP_SPLIT if split else 0) |
+                                              (HOP_DEPTH_BY_KERNEL if depth_by_kernel else 0)))
+
+    def hop_flags(self, prec, nrhs=1):
+        """HOP_SPLIT, HOP_DEPTH_BY_KERNEL and HOP_SHARED_LINKS as in effect for the hop
+        of nrhs right-hand sides (see mobius_hop_flags)."""
+        return _check(lib().mobius_hop_flags(self._h, prec, nrhs))
 
     def force(self, phi, tol=1e-12, maxiter=20000, inner_prec=F64, reliable_delta=0.0,
               check_every=0, link_grad=True):

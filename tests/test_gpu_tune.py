@@ -98,6 +98,40 @@ def test_tune_cache_of_other_kernels_is_not_used(torch_cuda, monkeypatch, tmp_pa
     op.close()
 
 
+@pytest.mark.parametrize("prec", [0, 1, 2], ids=["f64", "f32", "f16"])
+def test_tuned_choice_survives_the_round_trip(torch_cuda, monkeypatch, prec):
+    """What tune reports, handed to another operator's set_tuning, launches the same
+    hops: the split form and the depth by kernel included.  set_tuning alone selects
+    the loop, at one depth."""
+    from paper_1206_5214_amd import mobius
+    torch = torch_cuda
+    monkeypatch.delenv("MOBIUS_TUNE_CACHE", raising=False)
+    op, psi = _op(torch, dims=(4, 4, 4, 8), Ls=8)
+    op2, _ = _op(torch, dims=(4, 4, 4, 8), Ls=8)
+    assert op.hop_flags(prec) == mobius.HOP_SPLIT | mobius.HOP_DEPTH_BY_KERNEL  # untuned, 8 site blocks
+    r = op.tune(prec, reps=3)
+    _, o = op.pack(psi, prec)
+    for split in (0, 1):
+        for by_kernel in (0, 1):
+            # the four choices a tuner can make, the one it made among them
+            r.update(split=split, depth_by_kernel=by_kernel)
+            for q in (op, op2):
+                q.set_tuning(**{k: v for k, v in r.items() if k != "hop_us"})
+            want = (mobius.HOP_SPLIT if split else 0) | (mobius.HOP_DEPTH_BY_KERNEL if by_kernel else 0)
+            assert op.hop_flags(prec) == op2.hop_flags(prec) == want
+            # 100 right-hand sides of 8 site blocks are past every precision's threshold
+            assert not op.hop_flags(prec, 100) & mobius.HOP_SPLIT
+            assert torch.equal(op.dslash(o, 1, prec, op=mobius.OP_SCHUR), op2.dslash(o, 1, prec, op=mobius.OP_SCHUR))
+    op.set_tuning(prec, 2, 1, 1, 0)
+    assert op.hop_flags(prec) == 0
+    for flags in (4, 8, -1):
+        assert mobius.lib().mobius_set_hop_flags(op._h, prec, flags) == -22
+    assert mobius.lib().mobius_hop_flags(op._h, prec, 0) == -22 and mobius.lib().mobius_hop_flags(op._h, 7, 1) == -22
+    assert op.hop_flags(prec) == 0
+    op.close()
+    op2.close()
+
+
 def test_tune_rejects_bad_precision(torch_cuda):
     from paper_1206_5214_amd import mobius
     torch = torch_cuda
