@@ -526,6 +526,10 @@ __device__ __forceinline__ void hop_split(const HopParams &hp, int64_t lb, int r
     MOBIUS_PART(2)
     MOBIUS_PART(3)
 #undef MOBIUS_PART
+    // rounded here as in the loop: the last FP16 product must not be contracted into
+    // the epilogue's subtraction
+#pragma unroll
+    for (int c = 0; c < 12; ++c) pin(acc[c]);
     if constexpr (P != MOBIUS_F16) {
         const T mhalf = (T)-0.5;
 #pragma unroll

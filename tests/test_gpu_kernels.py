@@ -136,6 +136,8 @@ def test_right_hand_sides_sharing_links_same_bits(torch_cuda, dims, Ls, precs):
     U = torch.from_numpy(inputs.random_links(dims, 0.4, np.random.default_rng(3))).cuda()
     op = mobius.Operator(dims, Ls, 1.8, 0.05, 1.5, 0.5, U)
     eta = _gauss(torch, op.canon_shape(n), 4)
+    if dims == (16, 16, 16, 64):  # the others: their hop mixes its input or has no epilogue
+        assert op.hop_flags(precs[0], n) & mobius.HOP_SHARED_LINKS
     for prec in precs:
         full = op.pack_full(eta, prec, n)
         one = [op.pack_full(eta[r], prec) for r in range(n)]
@@ -179,3 +181,80 @@ def test_batch_with_shared_links_same_iterates(torch_cuda, prec):
         for r in range(2):
             assert torch.equal(sol[r], op.solve(src[r].contiguous(), **opts)[0]), (op.dims, r)
         op.close()
+
+
+def _slices(Ls):
+    rng = np.random.default_rng(8)
+    return {"b5s": tuple(rng.uniform(1.0, 2.0, Ls)), "c5s": tuple(rng.uniform(0.0, 0.8, Ls))}
+
+
+# the split form, which the small lattices of the oracle tests run by default, against
+# the loop that larger ones run: constant and per-slice coefficients, a chemical
+# potential (the adjoint's own links), matrix-core and dot-product FP16 loops
+@pytest.mark.parametrize("dims,Ls,kw", [((4, 2, 2, 6), 8, {}), ((4, 2, 2, 6), 8, _slices(8)),
+                                        ((4, 4, 2, 2), 5, _slices(5)), ((4, 2, 2, 6), 8, {"mu": 0.3}),
+                                        ((4, 2, 4, 2), 5, {"mu": -0.4})],
+                         ids=["const-Ls8", "slices-Ls8", "slices-Ls5", "mu-Ls8", "mu-Ls5"])
+@pytest.mark.parametrize("prec", [0, 1, 2], ids=["f64", "f32", "f16"])
+def test_split_and_loop_agree_in_every_operator_and_form(torch_cuda, dims, Ls, kw, prec):
+    """Every operator block, the solve forms cut by maxiter and the force, of one and
+    two right-hand sides, bit for bit; each side is asked which form it ran."""
+    torch = torch_cuda
+    mobius, op, eta = _setup(torch, dims, Ls, 2, **kw)
+    full = {1: op.pack_full(eta[0].contiguous(), prec), 2: op.pack_full(eta, prec, 2)}
+    fb = op.field_bytes(prec)
+
+    def attempt(f):
+        try:
+            return f()
+        except mobius.MobiusError as e:  # (the left forms need constant coefficients)
+            return str(e)
+
+    def everything():
+        out = {}
+        for n in (1, 2):
+            src = eta if n == 2 else eta[0].contiguous()
+            for o in range(8):
+                for dag in (False, True):
+                    x = full[n] if o == mobius.OP_FULL else full[n][n * fb:]
+                    out[n, o, dag] = attempt(lambda: op.dslash(x, 1, prec, op=o, dag=dag, nrhs=n))
+            for form in range(4):
+                out[n, "solve", form] = attempt(lambda: op.solve(src, tol=1e-13, maxiter=7, inner_prec=prec,
+                                                                 form=form, check_every=3)[0])
+            out[n, "solve", "dagger"] = attempt(lambda: op.solve(src, tol=1e-13, maxiter=7, inner_prec=prec,
+                                                                 dagger=True, check_every=3)[0])
+        s, gl, gp, _, _ = op.force(eta[0].contiguous(), tol=1e-13, maxiter=7, inner_prec=prec, check_every=3)
+        out["force"] = torch.cat([torch.view_as_real(t).flatten() for t in (gl, gp)] + [torch.tensor([s]).cuda()])
+        return out
+
+    assert op.hop_flags(prec, 2) & mobius.HOP_SPLIT
+    split = everything()
+    for p in {prec, mobius.F64}:  # (a solve's residual and the force run FP64 hops)
+        op.set_tuning(p, 2 if p == mobius.F16 else 0, 1, 1, 0, mfma=1)
+        assert op.hop_flags(p, 1) == op.hop_flags(p, 2) == 0
+    loop = everything()
+    assert sum(isinstance(v, str) for v in split.values()) <= 12
+    for key in split:
+        if isinstance(split[key], str):
+            assert split[key] == loop[key], key
+        else:
+            assert torch.equal(split[key], loop[key]), key
+    op.close()
+
+
+@pytest.mark.parametrize("prec,blocks", [(0, 160), (1, 400), (2, 160)], ids=["f64", "f32", "f16"])
+def test_split_threshold(torch_cuda, prec, blocks):
+    """8 site blocks: the last number of right-hand sides that splits and the first
+    that does not, each right-hand side with the bits of its own application."""
+    torch = torch_cuda
+    n = blocks // 8
+    mobius, op, eta = _setup(torch, (4, 4, 4, 8), 8, n + 1)
+    assert op.hop_flags(prec, n) & mobius.HOP_SPLIT and not op.hop_flags(prec, n + 1) & mobius.HOP_SPLIT
+    fb = op.field_bytes(prec)
+    _, x = op.pack(eta, prec, n + 1)
+    for o in (mobius.OP_HOP, mobius.OP_SCHUR):
+        one = [op.dslash(x[r * fb:(r + 1) * fb], 0 if o == mobius.OP_HOP else 1, prec, op=o) for r in range(n + 1)]
+        for m in (n, n + 1):
+            got = op.dslash(x, 0 if o == mobius.OP_HOP else 1, prec, op=o, nrhs=m)
+            assert torch.equal(got, torch.cat(one[:m])), (o, m)
+    op.close()
