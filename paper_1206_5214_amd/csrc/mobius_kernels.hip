@@ -1654,16 +1654,19 @@ HopTuning &hop_tuning()
 {
     static HopTuning t = [] {
         HopTuning d;
-        const auto given = [&d](const char *name, int &v) {
-            if (const char *e = std::getenv(name)) {
-                v = std::atoi(e);
-                d.split_dirs = 0;  // a loop variant was asked for
-            }
+        const auto given = [](const char *name, int v) {
+            const char *e = std::getenv(name);
+            return e ? std::atoi(e) : v;
         };
-        given("MOBIUS_XCD_REMAP", d.xcd_remap);
-        given("MOBIUS_PREFETCH", d.prefetch);
-        given("MOBIUS_STAGE_LINKS", d.stage_links);
-        given("MOBIUS_NT_LINKS", d.nt_links);
+        d.xcd_remap = given("MOBIUS_XCD_REMAP", d.xcd_remap);
+        d.prefetch = given("MOBIUS_PREFETCH", d.prefetch);
+        d.stage_links = given("MOBIUS_STAGE_LINKS", d.stage_links);
+        d.nt_links = given("MOBIUS_NT_LINKS", d.nt_links);
+        // another loop variant than the default was asked for (the block order is the
+        // split form's too)
+        const HopTuning own;
+        if (d.prefetch != own.prefetch || d.stage_links != own.stage_links || d.nt_links != own.nt_links)
+            d.split_dirs = 0;
         return d;
     }();
     return t;

@@ -132,6 +132,25 @@ def test_tuned_choice_survives_the_round_trip(torch_cuda, monkeypatch, prec):
     op2.close()
 
 
+@pytest.mark.parametrize("env,split", [({"MOBIUS_XCD_REMAP": "1", "MOBIUS_STAGE_LINKS": "1"}, True),
+                                       ({"MOBIUS_XCD_REMAP": "0"}, True), ({"MOBIUS_STAGE_LINKS": "0"}, False),
+                                       ({"MOBIUS_PREFETCH": "1"}, False)])
+def test_environment_selects_the_loop_only_for_another_variant(torch_cuda, env, split):
+    """The process defaults are read once, hence the child process: a hop variable at
+    its default value, or the block order, leaves small lattices their split form."""
+    import os
+    import subprocess
+    code = ("import numpy as np, torch; from paper_1206_5214_amd import inputs, mobius; "
+            "U = torch.from_numpy(inputs.unit_links((4, 4, 4, 4))).cuda(); "
+            "op = mobius.Operator((4, 4, 4, 4), 8, 1.8, 0.1, 1.5, 0.5, U); print('flags', op.hop_flags(0))")
+    out = subprocess.run([sys.executable, "-c", code], env={**os.environ, **env}, capture_output=True, text=True,
+                         timeout=100, cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+    assert out.returncode == 0, out.stderr
+    flags = int(out.stdout.split("flags")[1])
+    from paper_1206_5214_amd import mobius
+    assert bool(flags & mobius.HOP_SPLIT) == split
+
+
 def test_tune_rejects_bad_precision(torch_cuda):
     from paper_1206_5214_amd import mobius
     torch = torch_cuda
