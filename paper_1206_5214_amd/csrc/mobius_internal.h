@@ -294,6 +294,9 @@ constexpr int RING_MAX = 16;
 // their own (24^3 x 64: 22118 partials).
 constexpr int64_t RED_DIRECT = 2048;
 constexpr int RED_PARTS = 64;
+static_assert(SPLIT_BLOCKS[0] * HOP_WAVES <= RED_DIRECT && SPLIT_BLOCKS[1] * HOP_WAVES <= RED_DIRECT &&
+                  SPLIT_BLOCKS[2] * HOP_WAVES <= RED_DIRECT,
+              "the partials of a split hop, in groups, are summed directly");
 
 // CG scalars of one system, kept by the kernels that use them: the p update
 // sets gamma_new and beta, the r update qq, alpha and gamma = gamma_new.

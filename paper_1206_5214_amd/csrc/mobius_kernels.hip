@@ -560,9 +560,11 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(hop_waves
 void hop_kernel(HopParams hp)
 {
     if constexpr (PF == 4) {
+        // (the grid has a row per right-hand side, so one pass; written as a loop it
+        // compiles to fewer instructions: D_pre at 4^4, FP16, 12.0 against 12.6 us)
         for (int r = blockIdx.y; r < hp.nrhs; r += gridDim.y) {
             hop_split<P, DAG, EPI>(hp, logical_block(hp.remap), r);
-            if (r + (int)gridDim.y < hp.nrhs) __syncthreads();  // (more right-hand sides than grid rows)
+            if (r + (int)gridDim.y < hp.nrhs) __syncthreads();
         }
     } else {
         hop_block<P, DAG, EPI, PF>(hp, logical_block(hp.remap), blockIdx.y, gridDim.y);
@@ -1604,11 +1606,9 @@ __global__ __launch_bounds__(BLAS_BLOCK) void reduce_parts_batch(const VecSys *s
                                                                  double *out)
 {
     const VecSys v = sys[blockIdx.y];
-    if (sys_inactive(v, active) || v.nparts <= RED_DIRECT * v.group) return;
-    // in whole summands
-    const int64_t n = (v.nparts + v.group - 1) / v.group;
-    const int64_t a = n * blockIdx.x / RED_PARTS * v.group, b = n * (blockIdx.x + 1) / RED_PARTS * v.group;
-    const double t = block_total(v.partials + a, (b < v.nparts ? b : v.nparts) - a, v.group);
+    if (sys_inactive(v, active) || v.nparts <= RED_DIRECT) return;
+    const int64_t n = v.nparts, a = n * blockIdx.x / RED_PARTS, b = n * (blockIdx.x + 1) / RED_PARTS;
+    const double t = block_total(v.partials + a, b - a, 1);  // (so long a sum is no split hop's)
     if (threadIdx.x == 0) out[(int64_t)blockIdx.y * RED_PARTS + blockIdx.x] = t;
 }
 

@@ -431,8 +431,8 @@ int Batch::setup(mobius_ctx *const *ctxs, int n, const void *const *src, void *c
             h.group = fused_norm && g.split ? HOP_WAVES : 1;
             auto reads = [&](VecSys &w, const VecSys &from) {
                 // (by the system alone: a batch sums as its solo solves)
-                const bool two = from.nparts > RED_DIRECT * from.group;
-                w.redgroup = two ? 1 : from.group;
+                const bool two = from.nparts > RED_DIRECT;
+                w.redgroup = from.group;
                 w.red = two ? part2 + (int64_t)j * RED_PARTS : from.partials;
                 w.nred = two ? RED_PARTS : from.nparts;
             };
