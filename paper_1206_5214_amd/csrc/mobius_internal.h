@@ -36,7 +36,9 @@ namespace mobius {
 // stretch of memory (24^3 x 64, Ls = 12, FP64: eighteen whole cache lines) instead
 // of twelve pieces of a line and a half each, N5 * 16 bytes apart: hops 5 to 11 %
 // (FP64) and 3 to 6 % (FP32) faster there (FP64 adjoint hop 791 to 711 us, D_pre
-// 1956 to 1846 us).
+// 1956 to 1846 us).  At Ls = 4, where a piece is half a line, FP64 gains 3 to 5 %
+// (24^3 x 32: hop 190 to 182 us, D_pre 414 to 399 us) and FP32 up to 3 % (69.0 to 66.7,
+// 191.8 to 191.0 us), packing loses (FP64 124 to 138 us).
 // F16, and the others where a piece of Ls * 16 bytes is no whole number of 64-byte
 // sectors: one structure of arrays over all 5d sites; chunk c of site5 k = i * Ls + s
 // at base + (c * N5 + k) * 16, the F16 norms behind the chunks at base + 3 * N5 * 16.
@@ -176,11 +178,13 @@ struct HopTuning {
 };
 // Site blocks times right-hand sides up to which a hop splits its directions:
 // the split form's workgroups then run in about one round, and its chain of two
-// directions instead of eight is what the launch lasts.  D_pre, unsplit against
-// split (us): FP64 4^4 25.8 / 13.8 (4 blocks), 8^3 x 16 31.5 / 20.7 (128), 12^4
-// 47.2 / 45.9, its adjoint form 41.6 / 45.1 (324); FP32 20.1 / 15.1 (128), 26.8 /
-// 24.4 and 24.4 / 23.2 (324), 39.4 / 38.7 and 31.7 / 36.2 (692); FP16 14.6 / 11.8
-// (4), 15.4 / 13.7 (128), 16.9 / 16.2 and 15.9 / 17.3 (210).
+// directions instead of eight is what the launch lasts.  D_pre and D_pre^+, unsplit
+// against split (us): FP64 64 blocks 28.9 / 16.8 and 31.6 / 22.4, 128 31.3 / 20.0 and
+// 33.7 / 25.5, 140 32.7 / 25.3 and 33.4 / 30.4, 216 33.9 / 32.1 and 35.9 / 36.8, 324
+// 46.6 / 45.7 and 48.2 / 50.7; FP32 128 20.5 / 15.5 and 22.8 / 19.6, 324 27.6 / 24.7 and
+// 29.6 / 27.3, 378 28.0 / 25.7 and 30.4 / 29.1, 692 39.4 / 38.7 and 31.7 / 36.2; FP16 64
+// 15.9 / 12.7 and 18.5 / 16.1, 140 16.3 / 15.5 and 19.3 / 18.8, 216 17.1 / 17.6 and 20.7 /
+// 22.2.  The lines lie below the first loss of either.
 constexpr int64_t SPLIT_BLOCKS[3] = {160, 400, 160};  // FP64, FP32, FP16
 bool hop_splits_dirs(const Geometry &g, int prec, int nrhs, const HopTuning &t);
 // workgroups, and so |out|^2 partials per right-hand side, of a single-lattice hop
@@ -201,7 +205,9 @@ inline int prefetch_depth(const HopTuning &t, int prec, bool mixes_input)
 // 256 MB Infinity Cache anyway (16^3 x 32, Ls = 16: adjoint hop 135 to 126 us;
 // 24^3 x 64, Ls = 12: 711 to 693 us).  FP32 and FP16 gain nothing there (FP32 373
 // and 373 us, FP16 241 and 245 us) and lose where the links are still cached from the
-// last hop (16^3 x 32: FP32 52 to 66 us).
+// last hop (16^3 x 32: FP32 52 to 66 us).  Several right-hand sides, which read them
+// again, gain as well (FP64 D_pre, 3 and 12 of them: 16^3 x 32, Ls = 16 1003 to 991 and
+// 3953 to 3905 us; 24^3 x 64 3: 5301 to 5291 us).
 inline int nt_link_loads(const HopTuning &t, const Geometry &g, int prec)
 {
     if (t.nt_links >= 0) return t.nt_links;
