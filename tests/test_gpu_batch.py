@@ -324,3 +324,36 @@ def test_restart_survives_another_system_finishing(torch_cuda, inner):
     assert torch.equal(both, alone)
     for op in ops:
         op.close()
+
+
+@pytest.mark.parametrize("inner", [1, 2], ids=["mixed_f32", "mixed_f16"])
+def test_deferred_x_update_within_the_solvers_bounds(torch_cuda, monkeypatch, inner):
+    """Two converged solves of one system, x updated at the end of each chunk and in
+    every iteration, differ on the odd sites (the iterated unknown) by no more than
+    the two solves' own error bounds, condition number times Schur residual, whatever
+    the order of the sums.  The condition number is estimated from the CG
+    coefficients, from below: half as much again is allowed."""
+    from paper_1206_5214_amd import inputs, mobius
+    torch = torch_cuda
+    ops, srcs = [], []
+    for dims, Ls, b5, c5, mf, eps, seed in UNEVEN[:2]:
+        rng = np.random.default_rng(seed)
+        U = inputs.random_links(dims, eps, rng)
+        ops.append(mobius.Operator(dims, Ls, 1.8, mf, b5, c5, torch.from_numpy(U).cuda()))
+        srcs.append(torch.from_numpy(inputs.gaussian_spinor(dims, Ls, rng, 2)).cuda())
+    out = []
+    for d in ("1", "0"):
+        monkeypatch.setenv("MOBIUS_DEFER_X", d)
+        sols, infos, rc = mobius.batch_solve(ops, srcs, tol=TOL, maxiter=20000, inner_prec=inner, check_every=5)
+        assert rc == mobius.OK, infos
+        out.append((sols, infos))
+    for j, op in enumerate(ops):
+        x, y, z, t = (torch.arange(n, device="cuda") for n in op.dims)
+        odd = ((t[:, None, None, None] + z[:, None, None] + y[:, None] + x) & 1 == 1)[None, ..., None, None]
+        for r in range(2):
+            a, b = (torch.where(odd, o[0][j][r], 0) for o in out)
+            diff = ((a - b).norm() / b.norm()).item()
+            bound = 1.5 * sum(o[1][j][r].err_bound for o in out)
+            _flush(f"  inner {inner} lattice {j} rhs {r}: {diff:.1e} within {bound:.1e}")
+            assert 0 < bound < 1e-6 and diff <= bound
+        op.close()
