@@ -781,7 +781,8 @@ namespace {
 // I^-1: FP32 198 to 172 and 200 to 177 us, FP64 383 to 365 and 400 to 367 us;
 // 24^3 x 32, Ls = 4: FP64 63.4 to 50.3 and 65.2 to 55.1 us.  With one site to a
 // wavefront (Ls = 36) the pass through LDS costs I^-1 more than it gains (167 to
-// 210 us): such sites, and whole lines, are read and written directly.
+// 210 us): such sites, whole lines and small fields (m5_launch) are read and written
+// directly.
 template <int P>
 struct RecordTile {
     using T = typename Spin<P>::T;
@@ -1942,7 +1943,17 @@ void m5_launch(int kind, int dag, const char *in, char *out, const Geometry &g, 
                int64_t blocks, hipStream_t st)
 {
     const int spw = sites_per_wave(g.Ls);
-    const bool linear = P != MOBIUS_F16 && g.Ls % 8 == 4 && spw > 1;  // (see RecordTile)
+    // (see RecordTile)  A field and its result in the L2s' 32 MB are not bound by lines,
+    // and the passes through LDS lengthen each wavefront's chain: I^-1 of FP64 on
+    // 4 x 10 x 12 x 8, Ls = 4 (1.4 MB) takes 6.3 us as one stretch and 5.1 directly, on
+    // 12^4, Ls = 12 (23 MB) 14.3 and 11.5, of FP32 there (11 MB) 7.5 and 6.4.  Fields past
+    // them gain by the stretch: FP32, 36 MB, Ls = 12 (16^4) 15.8 and 16.4, Ls = 4
+    // (16^2 x 24 x 32) 13.6 and 18.7; FP64, 36 MB, Ls = 4 (16^3 x 24) 15.5 and 16.1.  FP64
+    // with a longer Ls has fewer half lines and gains from later on: Ls = 20 at 76 MB
+    // 32.8 and 31.8, at 120 MB 47.8 and 48.4; Ls = 12 at 72 MB 31.9 and 31.2, at 108 MB
+    // 43.7 and 44.8.
+    const int64_t least = (int64_t)(P == MOBIUS_F64 && g.Ls > 4 ? 96 : 32) << 20;
+    const bool linear = P != MOBIUS_F16 && g.Ls % 8 == 4 && spw > 1 && field_bytes(g, P) >= least;
     const dim3 grid((unsigned)blocks), blk(BLOCK);
 #define MOBIUS_M5(D, K)                                                                             \
     if (linear)                                                                                    \

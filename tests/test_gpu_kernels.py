@@ -80,6 +80,29 @@ def test_s_direction_operators_vs_oracle(torch_cuda, orc, dims, Ls, prec, tol):
     op.close()
 
 
+# the same on fields past the L2s, which move as one stretch in both types (Ls = 4:
+# 32 MB, longer Ls: 32 MB in FP32, 96 MB in FP64), with a partial last wavefront
+@pytest.mark.parametrize("dims,Ls", [((18, 14, 14, 50), 4), ((18, 14, 14, 26), 12), ((14, 14, 10, 34), 20)])
+def test_s_direction_operators_on_large_fields(torch_cuda, orc, dims, Ls):
+    """I and I^-1 and their adjoints in both types against the FP64 oracle, with the
+    tolerances of the small lattices (a lane's sums have the same Ls terms)."""
+    from oracle import Params
+    from paper_1206_5214_amd import inputs
+    from parity import check
+    torch = torch_cuda
+    mobius, op, eta = _setup(torch, dims, Ls, 1)
+    assert op.field_bytes(mobius.F32) >= 32 << 20 and op.field_bytes(mobius.F64) >= (32 if Ls == 4 else 96) << 20
+    p, psi, U = Params(dims, Ls, 1.8, 0.05, 1.5, 0.5), eta.cpu().numpy(), inputs.unit_links(dims)  # (no links enter)
+    for dag in (False, True):
+        m5, inv = orc.m5(p, U, psi, dag=dag), orc.m5inv(p, psi, dag=dag)
+        for prec, tol in ((mobius.F64, 1e-12), (mobius.F32, 2e-5)):
+            halves = op.pack(eta, prec)
+            for ref, got in ((m5, [op.dslash(x, q, prec, op=mobius.OP_M5, dag=dag) for q, x in enumerate(halves)]),
+                             (inv, [op.m5inv(x, prec, dag=dag) for x in halves])):
+                check(op.unpack(*got, prec).cpu().numpy(), ref, tol, (dims, Ls, prec, dag))
+    op.close()
+
+
 # a hop with its directions split over wavefronts (the small lattices' default)
 # against the loop variants that set_tuning asks for: fewer sites than one
 # wavefront's, partial last wavefronts, odd Ls, one site per wavefront, matrix-core
